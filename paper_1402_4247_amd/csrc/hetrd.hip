@@ -26,7 +26,8 @@
 // After the panel the trailing matrix takes the rank-2nb update
 // A22 -= V W^H + W V^H (Procedure 6, on MFMA).
 // Once a panel's trailing matrix has at most 128 rows, the rest of the
-// reduction runs in one launch, unblocked, with the matrix in LDS (tail).
+// reduction runs in one launch, unblocked, with the matrix in registers
+// (hetrd_res.hip).
 // No atomics: every sum is taken in a fixed order, so results are bitwise
 // reproducible run to run.
 #include <type_traits>
@@ -34,6 +35,7 @@
 #include "common.hpp"
 #include "lanes.hpp"
 #include "kernels.hpp"
+#include "reflector.hpp"
 
 namespace kgev {
 
@@ -50,28 +52,6 @@ constexpr int RB = 64;          // rows per workgroup in the column kernels
 // reduction uses (ws.zch: 4 tiles per chunk, or 1 for the one-tile form)
 __device__ __host__ inline int nchunks(int NB, int C) { return (NB - C + ZCH - 1) / ZCH; }
 __device__ __host__ inline int nchunks_z(int NB, int C, int zch) { return zch == 1 ? NB - C : (NB - C + 3) >> 2; }
-
-// Procedure 2's reflector for the sub-column x = (alpha, x_2, ...) with
-// sig2 = |x_2|^2 + ...: beta = -sign(Re alpha) ||x||, tau = (beta - alpha) /
-// beta and the scale 1 / (alpha - beta) applied to x_2, ...; two reciprocals
-// (the latency of a division chain dominates this single-lane step).
-template <typename R>
-__device__ inline void reflector_core(cx<R> alpha, R sig2, cx<R>& tau, cx<R>& scale, R& beta)
-{
-    if (sig2 == (R)0 && alpha.y == (R)0) {
-        tau = czero<cx<R>>();
-        scale = czero<cx<R>>();
-        beta = alpha.x;
-        return;
-    }
-    const R nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sig2);
-    beta = (alpha.x >= (R)0) ? -nrm : nrm;
-    const R ib = (R)1 / beta;
-    tau = mk<R>((beta - alpha.x) * ib, -alpha.y * ib);
-    const R dr = alpha.x - beta, di = alpha.y;
-    const R iden = (R)1 / (dr * dr + di * di);
-    scale = mk<R>(dr * iden, -di * iden);
-}
 
 // Partial norms of column i: lane q takes the per-block partials q, q + 64,
 // ... (pn_first: the first of them, requested with the kernel's first batch
@@ -95,15 +75,6 @@ __device__ inline R pn_rest(const HetrdWs<R>& ws, int64_t b, int i, int lane, R 
     R part = lane < np ? first : (R)0;
     for (int q = lane + 64; q < np; q += 64) part += pn[q];
     return part;
-}
-
-// LDS written by a wave and then read by other lanes of the same wave: a
-// wave-scope fence and a scheduling barrier, no workgroup barrier
-__device__ inline void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // One halving step of the transposing reduction: lanes with the MASK bit set
@@ -864,196 +835,6 @@ __global__ __launch_bounds__(256) void hetrd_update(HetrdWs<R> ws, int i, int p,
     }
 }
 
-// ---------------------------------------------------------------------------
-// The last columns, once the trailing matrix has at most TAIL_M rows: one
-// workgroup per problem holds its lower triangle in LDS (packed by rows,
-// element (r, s), r >= s, at tail_row(r) + s) and reduces it column by
-// column, unblocked: Procedure 2's reflector from the column's norm,
-// y = tau A22 v (Procedure 4), w = y - (tau / 2)(y^H v) v (Procedure 5) and
-// A22 -= v w^H + w v^H (Procedure 6), with the same reflector convention as
-// the blocked columns.  Sums are taken in a fixed order (bitwise
-// reproducible).  It replaces two launches per column, whose fixed cost
-// dominates at this size, by one launch for all of them.
-//
-// The kernel is bound by the latency of its dependent steps, so each column
-// takes five barrier phases: (A) reflector, (B) v, (C) y with the partial
-// sums of y^H v, (D) w, (E) the rank-2 update with the partial squared norms
-// of the next column (rows two and more below its diagonal).  Eight threads
-// share a row in (C) and (E) and take its entries in groups of four, so one
-// LDS round trip serves four of them.
-// over the lanes that agree in lane mod 8: the first three steps of
-// dpp_wave_sum only, so where only the lanes 0 mod 8 hold nonzero values
-// lane 0 ends with the wave's sum
-template <typename T> __device__ inline T dpp_sum_mod8(T v)
-{
-    v = xor_sum<32>(v);
-    v = xor_sum<16>(v);
-    return xor_sum<8>(v);
-}
-
-constexpr int TAIL_M = 128;
-constexpr int TAIL_T = 1024;
-constexpr int TAIL_W = TAIL_T / 64;
-static_assert(TAIL_T / 8 >= TAIL_M, "eight threads per row of the tail's trailing matrix");
-
-// start of row r of the packed lower triangle
-__host__ __device__ constexpr int tail_row(int r) { return r * (r + 1) / 2; }
-
-template <typename R>
-__global__ __launch_bounds__(TAIL_T) void hetrd_tail(HetrdWs<R> ws, int i0)
-{
-    __shared__ cx<R> P[tail_row(TAIL_M)];
-    __shared__ cx<R> sv[TAIL_M], sy[TAIL_M], sw[TAIL_M];
-    __shared__ R red[TAIL_W];
-    __shared__ cx<R> sred[TAIL_W];
-    __shared__ cx<R> sref[2];       // tau, scale
-    const int64_t b = blockIdx.x;
-    const int n = ws.n, M = n - i0, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int r = tid >> 3, q = tid & 7;      // row share of phases C and E
-    const cx<R>* A = ws.A + b * ws.sA;
-    cx<R>* V = ws.V + b * ws.sV;
-    const cx<R> zero = czero<cx<R>>();
-    for (int e = tid; e < M * M; e += TAIL_T) {
-        const int rr = e % M, c = e / M;
-        if (rr >= c) P[tail_row(rr) + c] = A[(int64_t)(i0 + rr) + (int64_t)(i0 + c) * ws.lda];
-    }
-    __syncthreads();
-    {
-        // squared norm of rows 2.. of column 0
-        R part = 0;
-        if (tid >= 2 && tid < M) {
-            const cx<R> x = P[tail_row(tid)];
-            part = x.x * x.x + x.y * x.y;
-        }
-        part = dpp_wave_sum(part);
-        if (lane == 0) red[wv] = part;
-    }
-    __syncthreads();
-    for (int c = 0; c + 1 < M; ++c) {
-        const int i = i0 + c, mm = M - c - 1;     // trailing order below column c
-        // (A) Procedure 2 (wave 0: the sixteen partial norms summed across
-        // lanes, then lane 0)
-        if (wv == 0) {
-            const R sig2 = dpp_sum<TAIL_W>(red[lane & (TAIL_W - 1)]);
-            if (lane == 0) {
-                const cx<R> alpha = P[tail_row(c + 1) + c];
-                cx<R> tau, scale;
-                R beta;
-                reflector_core(alpha, sig2, tau, scale, beta);
-                sref[0] = tau;
-                sref[1] = scale;
-                ws.d[b * n + i] = P[tail_row(c) + c].x;
-                ws.e[b * n + i] = beta;
-                ws.tau[b * n + i] = tau;
-            }
-        }
-        __syncthreads();
-        const cx<R> tau = sref[0];
-        // (B) Procedure 3: v = (1, scale x_1, ...), stored for the back-transformation
-        if (tid < mm) {
-            const cx<R> v = tid == 0 ? mk<R>(1, 0) : cmul(sref[1], P[tail_row(c + 1 + tid) + c]);
-            sv[tid] = v;
-            V[(int64_t)(i + 1 + tid) + (int64_t)i * ws.n] = v;
-        }
-        __syncthreads();
-        // (C) Procedure 4: y = tau A22 v, the row's stored part and then its
-        // mirrored part read down column gr (the same terms in the same order
-        // as one pass over s2 = q, q + 8, ...), combined over the eight
-        // threads in a fixed order; and this wave's rows' share of y^H v
-        {
-            cx<R> acc = zero;
-            if (r < mm) {
-                const int gr = c + 1 + r;
-                const cx<R>* Prow = P + tail_row(gr) + (c + 1);
-                int s2 = q;
-                for (; s2 + 24 <= r; s2 += 32) {
-                    cx<R> a4[4], v4[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        a4[u] = Prow[s2 + 8 * u];
-                        v4[u] = sv[s2 + 8 * u];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) acc = cfma(a4[u], v4[u], acc);
-                }
-                for (; s2 <= r; s2 += 8) acc = cfma(Prow[s2], sv[s2], acc);
-                for (; s2 + 24 < mm; s2 += 32) {
-                    cx<R> a4[4], v4[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int gs = c + 1 + s2 + 8 * u;
-                        a4[u] = P[tail_row(gs) + gr];
-                        v4[u] = sv[s2 + 8 * u];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) acc = cfma(cconj(a4[u]), v4[u], acc);
-                }
-                for (; s2 < mm; s2 += 8) {
-                    const int gs = c + 1 + s2;
-                    acc = cfma(cconj(P[tail_row(gs) + gr]), sv[s2], acc);
-                }
-            }
-            acc.x = dpp_sum<8>(acc.x);
-            acc.y = dpp_sum<8>(acc.y);
-            cx<R> yv = zero;
-            if (q == 0 && r < mm) {
-                const cx<R> y = cmul(tau, acc);
-                sy[r] = y;
-                yv = cmulc(y, sv[r]);
-            }
-            // nonzero only in the lanes with q = 0 (0 mod 8)
-            yv.x = dpp_sum_mod8(yv.x);
-            yv.y = dpp_sum_mod8(yv.y);
-            if (lane == 0) sred[wv] = yv;
-        }
-        __syncthreads();
-        // (D) Procedure 5: w = y - (tau / 2) (y^H v) v
-        cx<R> dot = sred[lane & (TAIL_W - 1)];
-        dot.x = dpp_sum<TAIL_W>(dot.x);
-        dot.y = dpp_sum<TAIL_W>(dot.y);
-        if (tid < mm) {
-            const cx<R> k = cscale(cmul(tau, dot), (R)0.5);
-            sw[tid] = csub(sy[tid], cmul(k, sv[tid]));
-        }
-        __syncthreads();
-        // (E) Procedure 6: A22 -= v w^H + w v^H (lower triangle), and the
-        // partial squared norms of column c + 1 below its sub-diagonal
-        {
-            R part = 0;
-            if (r < mm) {
-                const int gr = c + 1 + r;
-                const cx<R> vr = sv[r], wr = sw[r];
-                cx<R>* Prow = P + tail_row(gr) + (c + 1);
-                int s2 = q;
-                for (; s2 + 24 <= r; s2 += 32) {
-                    cx<R> a4[4], w4[4], v4[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        a4[u] = Prow[s2 + 8 * u];
-                        w4[u] = sw[s2 + 8 * u];
-                        v4[u] = sv[s2 + 8 * u];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) a4[u] = csub(a4[u], cadd(cmulc(w4[u], vr), cmulc(v4[u], wr)));
-                    if (s2 == 0 && r >= 2) part = a4[0].x * a4[0].x + a4[0].y * a4[0].y;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) Prow[s2 + 8 * u] = a4[u];
-                }
-                for (; s2 <= r; s2 += 8) {
-                    cx<R> a = Prow[s2];
-                    a = csub(a, cadd(cmulc(sw[s2], vr), cmulc(sv[s2], wr)));
-                    if (s2 == 0 && r >= 2) part = a.x * a.x + a.y * a.y;
-                    Prow[s2] = a;
-                }
-            }
-            part = dpp_sum_mod8(part);     // nonzero only where q = 0
-            if (lane == 0) red[wv] = part;
-        }
-        __syncthreads();
-    }
-    if (tid == 0) ws.d[b * n + n - 1] = P[tail_row(M - 1) + (M - 1)].x;
-}
-
 }  // namespace
 
 int hetrd_pn(int64_t n) { return (int)((n + RB - 1) / RB); }
@@ -1068,8 +849,9 @@ hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
     // with plain global loads instead.
     const bool buf = (double)sizeof(cx<R>) * (double)ws.lda * (double)n < 2147483648.0;
     for (int p = 0; p <= n - 1; p += nb) {
-        if (n - p <= TAIL_M && p < n - 1) {
-            hipLaunchKernelGGL(hetrd_tail<R>, dim3((unsigned)nk), dim3(TAIL_T), 0, st, ws, p);
+        if (n - p <= HETRD_RES_M && p < n - 1) {
+            const hipError_t e = hetrd_res<R>(st, ws, p, nk);
+            if (e != hipSuccess) return e;
             break;
         }
         dim3 g1((unsigned)((n - p + RB - 1) / RB), (unsigned)nk);

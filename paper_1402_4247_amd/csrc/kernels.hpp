@@ -91,6 +91,11 @@ int hetrd_pn(int64_t n);   // partial norms per column (one per 64-row block)
 
 template <typename R>
 hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws, int64_t nk);
+// columns i0.. of the reduction in one launch with the trailing matrix in
+// registers (hetrd_res.hip); 2 <= n - i0 <= HETRD_RES_M
+constexpr int HETRD_RES_M = 128;
+template <typename R>
+hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk);
 
 // ---------------------------------------------------------------------------
 // divide-and-conquer tridiagonal eigensolver (stedc.hip)

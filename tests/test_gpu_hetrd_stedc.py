@@ -216,3 +216,11 @@ def test_stebz_closed_forms():
     w2 = gpu_stebz(np.zeros((1, m)), np.sqrt(np.arange(1, m) * (m - np.arange(1, m)))[None])[0]
     assert mx(w1 - toe) <= 8 * EPS * 2 * abs(b) * 4
     assert mx(w2 - cle) <= 16 * EPS * m
+
+
+# the resident reduction at the edges of its tiles (16), of its two tile
+# counts (64, 128), at the smallest trailing orders and handed over to with a
+# ragged trailing order; tolerances as above
+@pytest.mark.parametrize("n", [4, 15, 16, 18, 31, 33, 48, 63, 66, 80, 111, 113, 127, 140])
+def test_resident_reduction_edges(n):
+    test_hetrd_matches_oracle(n, 0)
