@@ -75,7 +75,9 @@ typedef struct kgev_ctx kgev_ctx;
 typedef struct {
     int32_t precision;    /* KGEV_PREC_FP64 (default) or KGEV_PREC_FP32_REFINE */
     int32_t want_vectors; /* 1 (default): eigenvalues and eigenvectors; 0: eigenvalues only */
-    int32_t panel_nb;     /* Householder panel width; 0 = tuned default */
+    int32_t panel_nb;     /* Householder panel width; 0 = tuned default.  With a width (or hemv_slots)
+                             given, panels of it run down to trailing order 128; with both 0 the
+                             reduction may leave the panels earlier (the same results to rounding) */
     int32_t refine_iters; /* mixed precision: refinement sweeps, 1..10; 0 = default (3) */
     double s_tol;         /* S(k) is rejected when s_min <= s_tol * s_max; 0 = default 1e-12 */
     int32_t use_graph;    /* 1: capture the whole batched solve as one HIP graph on the first call with

@@ -34,7 +34,7 @@ bool prof_stop(Profiler* p, int64_t* launches, int64_t* seen, double* ms, double
 // Everything that identifies a captured solve: sizes, options, buffers, stream.
 struct GraphKey {
     int64_t n, ld, nk, ldc;
-    int32_t precision, want_vectors, panel_nb, refine_iters, streams, s_method;
+    int32_t precision, want_vectors, panel_nb, refine_iters, streams, s_method, hemv_slots, gemm_slots, groups;
     double s_tol;
     const void *H, *S, *w, *C, *work, *status, *stream;
     bool operator==(const GraphKey& o) const { return memcmp(this, &o, sizeof(GraphKey)) == 0; }
@@ -84,6 +84,7 @@ struct SolvePlan {
     int64_t n, nk;
     int nb, kb;
     int slots1;                // Hermitian-product tile grouping threshold (HetrdWs::slots1)
+    int groups;                // HetrdWs::groups
     int NBmax, CHmax, PN;
     // complex128 arrays
     size_t Aw, Vs, X, G, Wp, tau, ypart, ypartT, pvw, qpart, uwork, cwork, ppart, ndrop;
@@ -101,9 +102,10 @@ struct SolvePlan {
     size_t total;
 };
 
-SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots1 = DEFAULT_SLOTS)
+SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots1 = DEFAULT_SLOTS, int groups = 1)
 {
     SolvePlan p{};
+    p.groups = groups;
     p.slots1 = slots1;
     p.mixed = mixed;
     p.n = n;
@@ -123,7 +125,7 @@ SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots
     // nb-dependent arrays are sized for the widest panel (64), so a tuned
     // width never outgrows a workspace sized by kgev_workspace_bytes
     const size_t nbA = 64;
-    p.Wp = L.add(z * n * nbA * nk);
+    p.Wp = L.add(z * n * nbA * nk);            // (hetrd_res.hip lays its exchange areas over all of it)
     p.tau = L.add(z * n * nk);
     p.ypart = L.add(z * (size_t)p.NBmax * p.NBmax * 64 * nk);
     p.ypartT = L.add(z * (size_t)p.NBmax * p.CHmax * 64 * nk);
@@ -183,6 +185,7 @@ HetrdWs<float> hetrd_ws32(const SolvePlan& p, void* w)
     h.n = (int)p.n;
     h.nb = p.nb;
     h.slots1 = p.slots1;
+    h.groups = p.groups;
     h.NBmax = p.NBmax;
     h.CHmax = p.CHmax;
     h.A = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_A); h.lda = p.n; h.sA = p.n * p.n;
@@ -210,6 +213,7 @@ HetrdWs<double> hetrd_ws(const SolvePlan& p, void* w, double2* A, int64_t lda, i
     h.n = (int)p.n;
     h.nb = p.nb;
     h.slots1 = p.slots1;
+    h.groups = p.groups;
     h.NBmax = p.NBmax;
     h.CHmax = p.CHmax;
     h.A = A; h.lda = lda; h.sA = sA;
@@ -250,11 +254,20 @@ DcWs dc_ws(const SolvePlan& p, void* w, const double* d, const double* e, int* s
     return c;
 }
 
-kgev_opts resolve_opts(const kgev_opts* o)
+// The caller's options with the defaults filled in.  groups: the reduction may
+// hand its last columns to groups of workgroups (hetrd_res.hip); a caller
+// that names a panel width or a tile grouping gets that blocked reduction
+// down to the order one workgroup holds.
+struct SolveOpts : kgev_opts {
+    int32_t groups;
+};
+
+SolveOpts resolve_opts(const kgev_opts* o)
 {
-    kgev_opts r;
+    SolveOpts r;
     kgev_opts_default(&r);
-    if (o) r = *o;
+    if (o) static_cast<kgev_opts&>(r) = *o;
+    r.groups = r.panel_nb == 0 && r.hemv_slots == 0;
     if (r.panel_nb == 0) r.panel_nb = DEFAULT_NB;
     if (r.hemv_slots == 0) r.hemv_slots = DEFAULT_SLOTS;
     if (r.gemm_slots == 0) r.gemm_slots = GEMM_SMALL_SLOTS_DEFAULT;
@@ -282,7 +295,7 @@ bool opts_valid(const kgev_opts& o)
 
 // The tuner's values for the fields the caller left 0 (user: the caller's
 // options, null for all defaults).
-void apply_tuned(const kgev_ctx* ctx, int64_t n, const kgev_opts* user, kgev_opts& o)
+void apply_tuned(const kgev_ctx* ctx, int64_t n, const kgev_opts* user, SolveOpts& o)
 {
     auto it = ctx->tuned.find({n, o.precision});
     if (it == ctx->tuned.end()) return;
@@ -423,7 +436,7 @@ kgev_status eigen_hh_mixed(const SolvePlan& p, void* w, hipStream_t st, double* 
 // Part 2 also written there.
 // nreal: per problem, the order of an embedded pencil (its padded
 // directions of S sort last), or nullptr
-kgev_status solve_device(const SolvePlan& p, const kgev_opts& o, void* w, hipStream_t st, const double2* H,
+kgev_status solve_device(const SolvePlan& p, const SolveOpts& o, void* w, hipStream_t st, const double2* H,
                          const double2* S, int64_t ld, double* dw, double2* dC, int64_t ldc, int32_t* d_status,
                          const double2* Xin = nullptr, double2* Xout = nullptr, const int* nreal = nullptr)
 {
@@ -507,13 +520,13 @@ struct Groups {
     SolvePlan p;
 };
 
-Groups make_groups(int64_t n, int64_t nk, const kgev_opts& o)
+Groups make_groups(int64_t n, int64_t nk, const SolveOpts& o)
 {
     Groups g;
     g.G = (int)std::min<int64_t>(o.streams, nk);
     g.gsz = (nk + g.G - 1) / g.G;
     g.G = (int)((nk + g.gsz - 1) / g.gsz);
-    g.p = make_plan(n, g.gsz, o.panel_nb, o.precision == KGEV_PREC_FP32_REFINE, o.hemv_slots);
+    g.p = make_plan(n, g.gsz, o.panel_nb, o.precision == KGEV_PREC_FP32_REFINE, o.hemv_slots, o.groups);
     g.region = (g.p.total + 255) & ~(size_t)255;
     return g;
 }
@@ -533,7 +546,7 @@ kgev_status ensure_aux(kgev_ctx* ctx, int G)
     return KGEV_OK;
 }
 
-kgev_status solve_grouped(kgev_ctx* ctx, const Groups& g, const kgev_opts& o, void* w, hipStream_t st,
+kgev_status solve_grouped(kgev_ctx* ctx, const Groups& g, const SolveOpts& o, void* w, hipStream_t st,
                           const double2* H, const double2* S, int64_t ld, int64_t nk, double* dw, double2* dC,
                           int64_t ldc, int32_t* d_status, const int* nreal = nullptr)
 {
@@ -544,7 +557,7 @@ kgev_status solve_grouped(kgev_ctx* ctx, const Groups& g, const kgev_opts& o, vo
     KCHECK(hipEventRecord(ctx->ev[0], st));
     for (int q = 0; q < g.G; ++q) {
         const int64_t k0 = q * g.gsz, cnt = std::min<int64_t>(g.gsz, nk - k0);
-        const SolvePlan pq = (cnt == g.gsz) ? g.p : make_plan(n, cnt, o.panel_nb, o.precision == KGEV_PREC_FP32_REFINE, o.hemv_slots);
+        const SolvePlan pq = (cnt == g.gsz) ? g.p : make_plan(n, cnt, o.panel_nb, o.precision == KGEV_PREC_FP32_REFINE, o.hemv_slots, o.groups);
         hipStream_t s = q == 0 ? st : ctx->aux[q - 1];
         if (q > 0) KCHECK(hipStreamWaitEvent(s, ctx->ev[0], 0));
         r = solve_device(pq, o, static_cast<char*>(w) + (size_t)q * g.region, s, H + k0 * ld * n, S + k0 * ld * n,
@@ -604,7 +617,7 @@ struct ClassLayout {
     Groups grp;
 };
 
-ClassLayout class_layout(const kgev_problem* probs, const BatchClass& c, const kgev_opts& o)
+ClassLayout class_layout(const kgev_problem* probs, const BatchClass& c, const SolveOpts& o)
 {
     ClassLayout L{};
     const int64_t N = c.N, K = c.K;
@@ -627,10 +640,10 @@ ClassLayout class_layout(const kgev_problem* probs, const BatchClass& c, const k
     return L;
 }
 
-kgev_status solve_class(kgev_ctx* ctx, const kgev_problem* probs, const BatchClass& c, const kgev_opts& o0,
+kgev_status solve_class(kgev_ctx* ctx, const kgev_problem* probs, const BatchClass& c, const SolveOpts& o0,
                         void* w, hipStream_t st, const kgev_opts* user)
 {
-    kgev_opts o = o0;
+    SolveOpts o = o0;
     apply_tuned(ctx, c.N, user, o);
     const ClassLayout L = class_layout(probs, c, o);
     char* base = static_cast<char*>(w);
@@ -790,7 +803,7 @@ void kgev_destroy(kgev_ctx* ctx)
 size_t kgev_workspace_bytes(int64_t n, int64_t nk, const kgev_opts* opts)
 {
     if (n < 1 || nk < 1) return 0;
-    kgev_opts o = resolve_opts(opts);
+    SolveOpts o = resolve_opts(opts);
     const Groups g = make_groups(n, nk, o);
     return g.region * (size_t)g.G;
 }
@@ -806,14 +819,8 @@ kgev_status kgev_solve_k_device(kgev_ctx* ctx, const kgev_z* dH, const kgev_z* d
     if (ld < n) return -5;
     if (nk < 1) return -6;
     if (!dw) return -7;
-    if (!opts || opts->panel_nb == 0 || opts->hemv_slots == 0 || opts->gemm_slots == 0) {
-        kgev_opts t = resolve_opts(opts);
-        if (ctx->tuned.count({n, t.precision})) {
-            apply_tuned(ctx, n, opts, t);     // every field now set: the call below does not come back here
-            return kgev_solve_k_device(ctx, dH, dS, n, ld, nk, dw, dC, ldc, dwork, work_bytes, d_status, &t, stream);
-        }
-    }
-    kgev_opts o = resolve_opts(opts);
+    SolveOpts o = resolve_opts(opts);
+    apply_tuned(ctx, n, opts, o);
     if (!opts_valid(o)) return -10;
     if (o.want_vectors && (!dC || ldc < n)) return -8;
     DevGuard g(ctx->device);
@@ -838,6 +845,7 @@ kgev_status kgev_solve_k_device(kgev_ctx* ctx, const kgev_z* dH, const kgev_z* d
     key.n = n; key.ld = ld; key.nk = nk; key.ldc = o.want_vectors ? ldc : 0;
     key.precision = o.precision; key.want_vectors = o.want_vectors; key.panel_nb = o.panel_nb;
     key.refine_iters = o.refine_iters; key.streams = o.streams; key.s_method = o.s_method; key.s_tol = o.s_tol;
+    key.hemv_slots = o.hemv_slots; key.gemm_slots = o.gemm_slots; key.groups = o.groups;
     key.H = dH; key.S = dS; key.w = dw; key.C = o.want_vectors ? dC : nullptr; key.work = w; key.status = d_status;
     key.stream = stream;
     for (size_t q = 0; q < ctx->graphs.size(); ++q)
@@ -882,7 +890,7 @@ kgev_status kgev_solve_k_device_noalloc(kgev_ctx* ctx, const kgev_z* dH, const k
     if (ld < n) return -5;
     if (nk < 1) return -6;
     if (!dw) return -7;
-    kgev_opts o = resolve_opts(opts);
+    SolveOpts o = resolve_opts(opts);
     apply_tuned(ctx, n, opts, o);
     if (!opts_valid(o)) return -10;
     if (o.want_vectors && (!dC || ldc < n)) return -8;
@@ -906,7 +914,7 @@ size_t kgev_batch_workspace_bytes(const kgev_problem* probs, int64_t count, cons
     if (!probs || count < 1) return 0;
     for (int64_t q = 0; q < count; ++q)
         if (probs[q].n < 1 || probs[q].nk < 1) return 0;
-    const kgev_opts o = resolve_opts(opts);
+    const SolveOpts o = resolve_opts(opts);
     size_t mx = 0;
     for (const BatchClass& c : batch_classes(probs, count)) mx = std::max(mx, class_layout(probs, c, o).total);
     return mx;
@@ -918,7 +926,7 @@ kgev_status kgev_solve_batch_device(kgev_ctx* ctx, const kgev_problem* probs, in
     if (!ctx) return -1;
     if (!probs) return -2;
     if (count < 1) return -3;
-    const kgev_opts o = resolve_opts(opts);
+    const SolveOpts o = resolve_opts(opts);
     if (!opts_valid(o)) return -5;
     for (int64_t q = 0; q < count; ++q) {
         const kgev_problem& pr = probs[q];
@@ -936,7 +944,7 @@ kgev_status kgev_solve_batch_device(kgev_ctx* ctx, const kgev_problem* probs, in
         if (r != KGEV_OK) return r;
         w = ctx->work;
     }
-    kgev_opts oe = o;     // the kernels are launched directly (a graph, if any, is taken around all of them)
+    SolveOpts oe = o;     // the kernels are launched directly (a graph, if any, is taken around all of them)
     oe.use_graph = 0;
     const std::vector<BatchClass> classes = batch_classes(probs, count);
     auto run_all = [&](hipStream_t st) -> kgev_status {
@@ -1012,13 +1020,13 @@ kgev_status kgev_solve_k_x_device(kgev_ctx* ctx, const kgev_z* dH, const kgev_z*
     if (nk < 1) return -6;
     if (!dw) return -7;
     if (!dX) return -10;
-    kgev_opts o = resolve_opts(opts);
+    SolveOpts o = resolve_opts(opts);
     apply_tuned(ctx, n, opts, o);
     if (!opts_valid(o)) return -15;
     if (o.want_vectors && (!dC || ldc < n)) return -8;
     if (x_mode == KGEV_X_REUSE && o.s_method == KGEV_S_PRUNE) return KGEV_EUNSUPPORTED;
     DevGuard g(ctx->device);
-    SolvePlan p = make_plan(n, nk, o.panel_nb, o.precision == KGEV_PREC_FP32_REFINE, o.hemv_slots);
+    SolvePlan p = make_plan(n, nk, o.panel_nb, o.precision == KGEV_PREC_FP32_REFINE, o.hemv_slots, o.groups);
     void* w = dwork;
     if (w) {
         if (work_bytes < p.total) return -13;
@@ -1043,7 +1051,7 @@ kgev_status kgev_solve_k(kgev_ctx* ctx, const kgev_z* H, const kgev_z* S, int64_
     if (n < 1) return -4;
     if (nk < 1) return -5;
     if (!w) return -6;
-    kgev_opts o = resolve_opts(opts);
+    SolveOpts o = resolve_opts(opts);
     if (!opts_valid(o)) return -8;
     if (o.want_vectors && !C) return -7;
     DevGuard g(ctx->device);
@@ -1067,7 +1075,7 @@ kgev_status kgev_solve_k(kgev_ctx* ctx, const kgev_z* H, const kgev_z* S, int64_
     KCHECK(hipMemcpyAsync(base + oS, S, mb, hipMemcpyHostToDevice, st));
     kgev_status r = kgev_solve_k_device(ctx, (const kgev_z*)(base + oH), (const kgev_z*)(base + oS), n, n, nk,
                                         (double*)(base + ow), o.want_vectors ? (kgev_z*)(base + oC) : nullptr, n,
-                                        nullptr, 0, (int32_t*)(base + ost), &o, st);
+                                        nullptr, 0, (int32_t*)(base + ost), opts, st);
     if (r != KGEV_OK) return r;
     KCHECK(hipMemcpyAsync(w, base + ow, sizeof(double) * n * nk, hipMemcpyDeviceToHost, st));
     if (o.want_vectors) KCHECK(hipMemcpyAsync(C, base + oC, mb, hipMemcpyDeviceToHost, st));
@@ -1094,11 +1102,11 @@ kgev_status kgev_hetrd_device(kgev_ctx* ctx, kgev_z* dA, int64_t n, int64_t lda,
     if (!de) return -7;
     if (!dtau) return -8;
     if (!dV) return -9;
-    kgev_opts o = resolve_opts(opts);
+    SolveOpts o = resolve_opts(opts);
     if (o.panel_nb < 1 || o.panel_nb > 64 || o.hemv_slots < 1 || o.gemm_slots < 1) return -10;
     DevGuard g(ctx->device);
     const TileScope tiles(o.gemm_slots);
-    SolvePlan p = make_plan(n, nk, o.panel_nb, false, o.hemv_slots);
+    SolvePlan p = make_plan(n, nk, o.panel_nb, false, o.hemv_slots, o.groups);
     kgev_status r = ensure_work(ctx, p.total);
     if (r != KGEV_OK) return r;
     hipStream_t st = (hipStream_t)stream;
@@ -1176,11 +1184,11 @@ kgev_status kgev_eigh_device(kgev_ctx* ctx, const kgev_z* dA, int64_t n, int64_t
     if (lda < n) return -4;
     if (nk < 1) return -5;
     if (!dw) return -6;
-    kgev_opts o = resolve_opts(opts);
+    SolveOpts o = resolve_opts(opts);
     if (o.panel_nb < 1 || o.panel_nb > 64 || o.hemv_slots < 1 || o.gemm_slots < 1) return -9;
     DevGuard g(ctx->device);
     const TileScope tiles(o.gemm_slots);
-    SolvePlan p = make_plan(n, nk, o.panel_nb, false, o.hemv_slots);
+    SolvePlan p = make_plan(n, nk, o.panel_nb, false, o.hemv_slots, o.groups);
     kgev_status r = ensure_work(ctx, p.total);
     if (r != KGEV_OK) return r;
     hipStream_t st = (hipStream_t)stream;

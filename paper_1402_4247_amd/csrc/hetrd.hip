@@ -25,9 +25,8 @@
 //       partials.
 // After the panel the trailing matrix takes the rank-2nb update
 // A22 -= V W^H + W V^H (Procedure 6, on MFMA).
-// Once a panel's trailing matrix has at most 128 rows, the rest of the
-// reduction runs in one launch, unblocked, with the matrix in registers
-// (hetrd_res.hip).
+// Once a panel's trailing matrix is small enough, the rest of the reduction
+// runs in one launch, unblocked, with the matrix in registers (hetrd_res.hip).
 // No atomics: every sum is taken in a fixed order, so results are bitwise
 // reproducible run to run.
 #include <type_traits>
@@ -848,8 +847,9 @@ hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
     // Buffer offsets are 32-bit: a matrix (ld x n) of 2 GiB or more is read
     // with plain global loads instead.
     const bool buf = (double)sizeof(cx<R>) * (double)ws.lda * (double)n < 2147483648.0;
+    const int limit = hetrd_res_order(n, nb, nk, ws.groups);
     for (int p = 0; p <= n - 1; p += nb) {
-        if (n - p <= HETRD_RES_M && p < n - 1) {
+        if (n - p <= limit && p < n - 1) {
             const hipError_t e = hetrd_res<R>(st, ws, p, nk);
             if (e != hipSuccess) return e;
             break;

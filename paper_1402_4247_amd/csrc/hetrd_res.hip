@@ -29,6 +29,8 @@
 // measured 269 us, __syncthreads() for both barriers (which waits for the
 // stores of v) with run-time tile bounds 359 us.
 // Sums are taken in a fixed order: results are bitwise reproducible.
+#include <stdint.h>
+
 #include <type_traits>
 #include <utility>
 
@@ -40,6 +42,11 @@
 namespace kgev {
 
 namespace {
+
+// how long a workgroup of a group waits for the others to start, in ticks of
+// the 100 MHz wall clock: 200 ms
+constexpr int64_t GROUP_WAIT_TICKS = 20000000;
+thread_local int64_t tl_group_wait_ticks = GROUP_WAIT_TICKS;
 
 constexpr int RT_T = 512;           // threads of a workgroup
 constexpr int RT_W = RT_T / WAVE;   // waves: tile row R belongs to wave R mod RT_W
@@ -62,6 +69,44 @@ __device__ inline void lds_barrier()
 template <typename Fn, int... K> __device__ __attribute__((always_inline)) inline void for_tiles(Fn& f, std::integer_sequence<int, K...>)
 {
     (f(std::integral_constant<int, K>{}), ...);
+}
+
+// Sum of KC values per lane over the four lane groups.  Where the count halves,
+// the set is halved across lane bit 5, then bit 4 (each lane group ends with
+// its share); otherwise every group adds and one of them passes the sum on.
+// f(k, sum) is called by the lanes that hold sum k.
+template <typename R, int KC, typename Fn>
+__device__ __attribute__((always_inline)) inline void sum_lane_groups(cx<R> (&v)[KC], int lk, Fn f)
+{
+    constexpr int K1 = KC % 2 == 0 ? KC / 2 : KC, K2 = K1 % 2 == 0 ? K1 / 2 : K1;
+#pragma unroll
+    for (int k = 0; k < K1; ++k) {
+        if constexpr (K1 < KC) {
+            swap_across<32>(v[k].x, v[k + K1].x);
+            swap_across<32>(v[k].y, v[k + K1].y);
+            v[k] = cadd(v[k], v[k + K1]);
+        } else {
+            v[k].x = xor_sum<32>(v[k].x);
+            v[k].y = xor_sum<32>(v[k].y);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < K2; ++k) {
+        if constexpr (K2 < K1) {
+            swap_across<16>(v[k].x, v[k + K2].x);
+            swap_across<16>(v[k].y, v[k + K2].y);
+            v[k] = cadd(v[k], v[k + K2]);
+        } else {
+            v[k].x = xor_sum<16>(v[k].x);
+            v[k].y = xor_sum<16>(v[k].y);
+        }
+    }
+    const bool holds = (K1 < KC || !(lk & 2)) && (K2 < K1 || !(lk & 1));
+    const int k0 = (K1 < KC && (lk & 2) ? K1 : 0) + (K2 < K1 && (lk & 1) ? K2 : 0);
+    if (holds) {
+#pragma unroll
+        for (int k = 0; k < K2; ++k) f(k0 + k, v[k]);
+    }
 }
 
 // RT tile rows per wave, KC tile columns: the trailing order is at most
@@ -191,26 +236,12 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
                 ws.tau[b * n + i] = tau;
             }
         }
-        // over the four lane groups: halve the set of columns across lane bit
-        // 5, then bit 4, so that lane group lk ends with a quarter of them
-        static_assert(KC % 4 == 0, "four lane groups");
         R qs = 0;
-#pragma unroll
-        for (int k = 0; k < KC / 2; ++k) {
-            swap_across<32>(za[k].x, za[k + KC / 2].x);
-            swap_across<32>(za[k].y, za[k + KC / 2].y);
-            za[k] = cadd(za[k], za[k + KC / 2]);
-        }
-#pragma unroll
-        for (int k = 0; k < KC / 4; ++k) {
-            swap_across<16>(za[k].x, za[k + KC / 4].x);
-            swap_across<16>(za[k].y, za[k + KC / 4].y);
-            za[k] = cadd(za[k], za[k + KC / 4]);
-            const int kk = k + ((lk & 2) ? KC / 2 : 0) + ((lk & 1) ? KC / 4 : 0);
-            zp[w][kk * 16 + li] = za[k];
-            const cx<R> xc = x[kk * 16 + li];
-            qs = fma(xc.x, za[k].x, fma(xc.y, za[k].y, qs));
-        }
+        sum_lane_groups<R, KC>(za, lk, [&](int k, cx<R> v) {
+            zp[w][k * 16 + li] = v;
+            const cx<R> xc = x[k * 16 + li];
+            qs = fma(xc.x, v.x, fma(xc.y, v.y, qs));
+        });
         qs = dpp_wave_sum(qs);
         if (lane == 0) sq[w] = qs;
         lds_barrier();
@@ -255,18 +286,548 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
     for_tiles(columns, std::make_integer_sequence<int, NT>{});
 }
 
+
+// ---------------------------------------------------------------------------
+// The same reduction by a group of G workgroups per problem, for trailing
+// orders one workgroup's registers do not hold.  Member g owns the tile columns
+// g, g + G, ... (KC of them at most) over all tile rows; x, v and w are kept
+// by every member.  A member's column sums are complete, so one exchange per
+// column joins the group: each member publishes z_s and A(s, c+1) of its
+// columns and its share of q, and every member reads all of them.
+//
+// The exchange is the data itself: a slot that holds SENTINEL (a NaN no
+// arithmetic produces; a value with its bits is published as another NaN) has
+// not been published.  Slots form a ring of three: whoever has read every
+// member's column c knows that every member has read column c - 1, so the
+// owner clears the slots of column c - 1 then and publishes column c + 1 after
+// the clears have reached memory; a reader of column c + 2 (the same slot) has
+// read column c + 1 first and cannot see column c - 1's values.
+//
+// The members of a group must run together.  Workgroups take their (problem,
+// member) from a counter when they start, so groups fill in order and at most
+// one group of a launch is partly placed; a member waits for the others to
+// start for a bounded time, after which the group is given up (the last one to
+// arrive and the one that gives up decide by an atomic on the same word) and
+// hetrd_memory reduces that problem instead.  Once all have started, every
+// wait ends; the poll is bounded all the same.  A group has at most 64 members
+// of the 256 compute units, so four launches on different streams (the
+// hardware queues of a process) cannot hold each other's partly placed groups.
+//
+// Bound by the latency of a column: the exchange (a store and a polled load
+// through the coherent level, about half of it), one workgroup barrier on
+// each side of it and phase B's chain: 3.0 us a column at order 200, 3.4 us at
+// 512, 4.8 us at 1024 (one problem), against 11-13 us for the two launches of
+// a blocked column.
+constexpr uint64_t SENTINEL = 0xFFF4DEADFFF4BEEFull;   // two NaNs as well for a pair of floats
+constexpr uint32_t GIVEN_UP = 0x80000000u;
+constexpr int GROUP_MAX = 64;             // members of a group at most
+constexpr int GROUP_MIN = 160;            // orders up to this stay with panels and one workgroup
+constexpr int POLLS_MAX = 1 << 21;
+
+template <typename T> __device__ __attribute__((always_inline)) inline T load_agent(const T* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T> __device__ __attribute__((always_inline)) inline void store_agent(T* p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The exchange area of one problem, in the panel buffer W (which the blocked
+// columns before have finished with; 64 n complex values a problem): a header
+// of two 64-bit words {members started | GIVEN_UP, next ticket (problem 0
+// only)}, then three slots of {z (MP complex), A(:, c+1) (MP complex), q (GROUP_MAX)}.
+template <typename R> struct Exchange {
+    static constexpr int WPC = 2 * sizeof(R) / 8;      // 64-bit words per complex value
+    uint64_t* base;
+    int MP;
+    __device__ __host__ Exchange(const HetrdWs<R>& ws, int64_t b, int M)
+        : base(reinterpret_cast<uint64_t*>(ws.W + b * 64 * (int64_t)ws.n)), MP((M + 15) & ~15) {}
+    __device__ uint32_t* started() const { return reinterpret_cast<uint32_t*>(base); }
+    __device__ uint32_t* ticket() const { return reinterpret_cast<uint32_t*>(base + 1); }
+    __device__ __host__ int slot_words() const { return 2 * WPC * MP + GROUP_MAX; }
+    __device__ uint64_t* slot(int q) const { return base + 2 + (int64_t)q * slot_words(); }
+    // word c of value s of list l (0: z, 1: A(:, c+1)) in a slot
+    __device__ int at(int l, int s, int c) const { return (l * WPC + c) * MP + s; }
+    __device__ int at_q(int g) const { return 2 * WPC * MP + g; }
+};
+
+__device__ inline uint64_t word_of(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    return u == SENTINEL ? 0x7FF8000000000000ull : u;
+}
+__device__ inline uint64_t word_of(float lo, float hi)
+{
+    const uint64_t u = (uint64_t)__float_as_uint(lo) | ((uint64_t)__float_as_uint(hi) << 32);
+    return u == SENTINEL ? 0x7FC000007FC00000ull : u;
+}
+
+// values from published words
+template <typename R> __device__ inline cx<R> value_of(const uint64_t* u)
+{
+    if constexpr (sizeof(R) == 8)
+        return mk<R>(__longlong_as_double((long long)u[0]), __longlong_as_double((long long)u[1]));
+    else
+        return mk<R>(__uint_as_float((uint32_t)u[0]), __uint_as_float((uint32_t)(u[0] >> 32)));
+}
+
+template <typename R> __device__ inline R q_of(uint64_t u)
+{
+    if constexpr (sizeof(R) == 8) return __longlong_as_double((long long)u);
+    else return __uint_as_float((uint32_t)u);
+}
+
+template <typename R>
+__global__ __launch_bounds__(256) void k_exchange_init(HetrdWs<R> ws, int M)
+{
+    const Exchange<R> ex(ws, blockIdx.y, M);
+    const int words = 2 + 3 * ex.slot_words();
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q < words) ex.base[q] = q < 2 ? 0 : SENTINEL;
+}
+
+template <typename R, int RT, int KC>
+__global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G, int64_t wait_ticks)
+{
+    using M_ = Mfma<R>;
+    using Ex = Exchange<R>;
+    constexpr int MPX = RT * RT_W * 16;          // largest order
+    constexpr int SP = (MPX + RT_T - 1) / RT_T;  // rows per thread
+    constexpr int FS = MPX + 16;
+    constexpr int WPC = Ex::WPC;
+    static_assert(KC * 16 < RT_T, "a thread per owned column and one for q");
+    __shared__ R F[4][FS];
+    __shared__ cx<R> x[MPX];
+    __shared__ cx<R> zp[RT_W][KC * 16];
+    __shared__ cx<R> hrow[KC * 16];
+    __shared__ R red[RT_W], sq[RT_W];
+    __shared__ cx<R> salpha;
+    __shared__ int sgo, sdead;
+    __shared__ uint32_t sticket;
+
+    const int n = ws.n, M = n - i0;
+    const int nt = (M + 15) >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const cx<R> zero = czero<cx<R>>();
+
+    // which problem and member, and whether all members have started
+    if (tid == 0) {
+        sticket = __hip_atomic_fetch_add(Ex(ws, 0, M).ticket(), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sdead = 0;
+        uint32_t* started = Ex(ws, (int64_t)(sticket / (uint32_t)G), M).started();
+        uint32_t seen = 1u + __hip_atomic_fetch_add(started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int64_t t0 = wall_clock64();
+        while (seen < (uint32_t)G) {
+            if ((int64_t)wall_clock64() - t0 >= wait_ticks) {
+                // gives the group up unless the last member arrives first
+                uint32_t expect = seen;
+                if (__hip_atomic_compare_exchange_strong(started, &expect, seen | GIVEN_UP, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    expect = seen | GIVEN_UP;
+                seen = expect;
+            } else {
+                __builtin_amdgcn_s_sleep(8);
+                seen = load_agent(started);
+            }
+        }
+        sgo = seen == (uint32_t)G;      // a group given up has GIVEN_UP set
+    }
+    __syncthreads();
+    if (!sgo) return;
+    const int64_t b = __builtin_amdgcn_readfirstlane((int)(sticket / (uint32_t)G));
+    const int g = __builtin_amdgcn_readfirstlane((int)(sticket % (uint32_t)G));
+    const Ex ex(ws, b, M);
+    const cx<R>* A = ws.A + b * ws.sA + (int64_t)i0 + (int64_t)i0 * ws.lda;
+    const int64_t lda = ws.lda;
+    cx<R>* V = ws.V + b * ws.sV;
+
+    acc4<R> tr[RT][KC], ti[RT][KC];
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = (w + RT_W * q) * 16 + M_::row(lk, r), col = (g + G * k) * 16 + li;
+                cx<R> a = zero;
+                if (row < M && col < M) {
+                    const bool low = row >= col;
+                    a = A[low ? (int64_t)row + (int64_t)col * lda : (int64_t)col + (int64_t)row * lda];
+                    a.y = row == col ? (R)0 : (low ? a.y : -a.y);
+                }
+                tr[q][k][r] = a.x;
+                ti[q][k][r] = a.y;
+            }
+    R nrm = 0;
+    for (int e = tid; e < 4 * FS; e += RT_T) (&F[0][0])[e] = (R)0;
+#pragma unroll
+    for (int u = 0; u < SP; ++u) {
+        const int s = tid + RT_T * u;
+        const cx<R> a = csel(s < M, A[s < M ? s : 0], zero);
+        const cx<R> a2 = csel(s >= 2, a, zero);
+        if (s < MPX) x[s] = a2;
+        nrm += a2.x * a2.x + a2.y * a2.y;
+        if (s == 0 && g == 0) ws.d[b * n + i0] = a.x;
+        if (s == 1) salpha = a;
+    }
+    nrm = dpp_wave_sum(nrm);
+    if (lane == 0) red[w] = nrm;
+    lds_barrier();
+
+    int ring = 0;                       // c mod 3
+    for (int c = 0; c + 1 < M; ++c) {
+        const int c1 = c + 1, i = i0 + c, k1 = c1 >> 4;
+        uint64_t* const cur = ex.slot(ring);
+        uint64_t* const old = ex.slot(ring == 0 ? 1 : ring == 1 ? 2 : 0);     // column c - 2's, c + 1's next
+        const int own = (g + G * (tid >> 4)) * 16 + (tid & 15);       // this thread's owned column
+        // ---- clear the slots of column c - 2 (every member has read them)
+        if (tid < KC * 16 && own < M) {
+#pragma unroll
+            for (int u = 0; u < WPC; ++u) {
+                store_agent(old + ex.at(0, own, u), SENTINEL);
+                store_agent(old + ex.at(1, own, u), SENTINEL);
+            }
+        }
+        if (tid == KC * 16) store_agent(old + ex.at_q(g), SENTINEL);
+        // ---- A: pending update, column sums
+        R opB[KC];
+        cx<R> za[KC];
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            const int C = g + G * k;
+            opB[k] = F[lk ^ 2][(C < nt ? C : 0) * 16 + li];
+            za[k] = zero;
+        }
+#pragma unroll
+        for (int q = 0; q < RT; ++q) {
+            const int Rt = w + RT_W * q;
+            if (Rt >= k1 && Rt < nt) {
+                const R are = -F[lk][Rt * 16 + li], aim = -F[lk ^ 1][Rt * 16 + li];
+#pragma unroll
+                for (int k = 0; k < KC; ++k)
+                    if (g + G * k >= k1 && g + G * k < nt) {
+                        tr[q][k] = M_::mma(are, opB[k], tr[q][k]);
+                        ti[q][k] = M_::mma(aim, (lk & 1) ? -opB[k] : opB[k], ti[q][k]);
+                    }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < RT; ++q) {
+            const int Rt = w + RT_W * q;
+            if (Rt >= k1 && Rt < nt) {
+                cx<R> xr[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) xr[r] = x[Rt * 16 + M_::row(lk, r)];
+#pragma unroll
+                for (int k = 0; k < KC; ++k)
+                    if (g + G * k >= k1 && g + G * k < nt) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) za[k] = cfmac(mk<R>(tr[q][k][r], ti[q][k][r]), xr[r], za[k]);
+                    }
+                if (Rt == k1) {
+                    const int rr = row_r<R>(c1 & 15);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (r == rr && lk == row_lk<R>(c1 & 15)) {
+#pragma unroll
+                            for (int k = 0; k < KC; ++k) hrow[k * 16 + li] = mk<R>(tr[q][k][r], -ti[q][k][r]);
+                        }
+                }
+            }
+        }
+        R qs = 0;
+        sum_lane_groups<R, KC>(za, lk, [&](int k, cx<R> v) {
+            zp[w][k * 16 + li] = v;
+            const int s = (g + G * k) * 16 + li;
+            const cx<R> xc = x[s < MPX ? s : 0];
+            qs = fma(xc.x, v.x, fma(xc.y, v.y, qs));
+        });
+        qs = dpp_wave_sum(qs);
+        if (lane == 0) sq[w] = qs;
+        lds_barrier();
+        // ---- publish (after this wave's clears have reached memory)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (tid < KC * 16 && own >= c1 && own < M) {
+            const cx<R> z = cadd(cadd(cadd(zp[0][tid], zp[1][tid]), cadd(zp[2][tid], zp[3][tid])),
+                                 cadd(cadd(zp[4][tid], zp[5][tid]), cadd(zp[6][tid], zp[7][tid])));
+            const cx<R> h = hrow[tid];
+            if constexpr (WPC == 2) {
+                store_agent(cur + ex.at(0, own, 0), word_of(z.x));
+                store_agent(cur + ex.at(0, own, 1), word_of(z.y));
+                store_agent(cur + ex.at(1, own, 0), word_of(h.x));
+                store_agent(cur + ex.at(1, own, 1), word_of(h.y));
+            } else {
+                store_agent(cur + ex.at(0, own, 0), word_of(z.x, z.y));
+                store_agent(cur + ex.at(1, own, 0), word_of(h.x, h.y));
+            }
+        }
+        if (tid == KC * 16) {
+            const R q = ((sq[0] + sq[1]) + (sq[2] + sq[3])) + ((sq[4] + sq[5]) + (sq[6] + sq[7]));
+            if constexpr (WPC == 2) store_agent(cur + ex.at_q(g), word_of(q));
+            else store_agent(cur + ex.at_q(g), word_of(q, (R)0));
+        }
+        // ---- Procedure 2, in every wave, while the columns travel
+        cx<R> tau, scale;
+        R beta;
+        {
+            const R sig2 = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+            reflector_core(salpha, sig2, tau, scale, beta);
+        }
+        // ---- read every member's columns
+        uint64_t uz[SP][WPC], uh[SP][WPC], u1[2 * WPC], uq;
+        for (int polls = 0;; ++polls) {
+            bool missing = false;
+            auto get = [&](int word) {
+                const uint64_t v = load_agent(cur + word);
+                missing |= v == SENTINEL;
+                return v;
+            };
+#pragma unroll
+            for (int u = 0; u < SP; ++u) {
+                const int s = tid + RT_T * u;
+                if (s >= c1 && s < M) {
+#pragma unroll
+                    for (int e = 0; e < WPC; ++e) {
+                        uz[u][e] = get(ex.at(0, s, e));
+                        uh[u][e] = get(ex.at(1, s, e));
+                    }
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < WPC; ++e) {
+                u1[e] = get(ex.at(0, c1, e));
+                u1[WPC + e] = get(ex.at(1, c1, e));
+            }
+            uq = 0;
+            if (lane < G) uq = get(ex.at_q(lane));
+            if (!__any(missing)) break;
+            if (polls >= POLLS_MAX) {
+                sdead = 1;
+                break;
+            }
+        }
+        // ---- B
+        R qq = q_of<R>(uq);        // zero where there is no member
+        qq = dpp_wave_sum(qq);
+        const cx<R> z1 = value_of<R>(u1), h1 = value_of<R>(u1 + WPC);
+        const R hoo = h1.x;
+        const cx<R> sz = cmul(scale, z1);
+        const R vav = hoo + (R)2 * sz.x + (scale.x * scale.x + scale.y * scale.y) * qq;
+        const R a2 = (R)-0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
+        const cx<R> w1 = cadd(cmul(tau, cadd(mk<R>(hoo, 0), sz)), mk<R>(a2, 0));
+        nrm = 0;
+#pragma unroll
+        for (int u = 0; u < SP; ++u) {
+            const int s = tid + RT_T * u;
+            if (s < MPX) {
+                cx<R> vs = zero, wv = zero, xn = zero;
+                if (s >= c1 && s < M) {
+                    const cx<R> z = value_of<R>(uz[u]), h = value_of<R>(uh[u]);
+                    vs = csel(s == c1, mk<R>(1, 0), cmul(scale, x[s]));
+                    wv = csel(s == c1, w1, cfma(tau, cfma(scale, z, h), cscale(vs, a2)));
+                    // x'_s = h_s - (v_s conj(w_{c+1}) + w_s)
+                    xn = csub(h, cadd(cmulc(w1, vs), wv));
+                    if (c % G == g) V[(int64_t)(i0 + s) + (int64_t)i * n] = vs;
+                    if (s == c1 && g == 0) ws.d[b * n + i + 1] = hoo - (R)2 * w1.x;
+                    if (s == c1 + 1) salpha = xn;
+                    xn = csel(s >= c1 + 2, xn, zero);
+                    nrm += xn.x * xn.x + xn.y * xn.y;
+                }
+                F[0][s] = vs.x;
+                F[1][s] = vs.y;
+                F[2][s] = wv.x;
+                F[3][s] = wv.y;
+                x[s] = xn;
+            }
+        }
+        if (tid == 0 && g == 0) {
+            ws.e[b * n + i] = beta;
+            ws.tau[b * n + i] = tau;
+        }
+        nrm = dpp_wave_sum(nrm);
+        if (lane == 0) red[w] = nrm;
+        lds_barrier();
+        if (sdead) {
+            if (tid == 0) __hip_atomic_fetch_or(ex.started(), GIVEN_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        ring = ring == 2 ? 0 : ring + 1;
+    }
+}
+
+// The problems whose group was given up: one workgroup each, with the
+// trailing matrix (lower triangle) in memory.  Reached only when other work
+// holds the GPU's compute units for longer than the members' wait, so it is
+// written for being right, not for speed.
+template <typename R>
+__global__ __launch_bounds__(1024) void hetrd_memory(HetrdWs<R> ws, int i0, int G)
+{
+    constexpr int T = 1024, W = T / WAVE;
+    __shared__ cx<R> sv[HETRD_GROUP_M], sw[HETRD_GROUP_M];
+    __shared__ R red[2][W];
+    const int64_t b = blockIdx.x;
+    const int n = ws.n, M = n - i0, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (*Exchange<R>(ws, b, M).started() == (uint32_t)G) return;
+    cx<R>* A = ws.A + b * ws.sA + (int64_t)i0 + (int64_t)i0 * ws.lda;
+    const int64_t lda = ws.lda;
+    cx<R>* V = ws.V + b * ws.sV;
+    auto block_sum = [&](R v, R* sh) {
+        v = dpp_wave_sum(v);
+        if (lane == 0) sh[w] = v;
+        __syncthreads();
+        R t = 0;
+        for (int q = 0; q < W; ++q) t += sh[q];
+        return t;
+    };
+    if (tid == 0) ws.d[b * n + i0] = A[0].x;
+    for (int c = 0; c + 1 < M; ++c) {
+        const int c1 = c + 1, i = i0 + c;
+        R part = 0;
+        for (int s = c1 + 1 + tid; s < M; s += T) {
+            const cx<R> a = A[s + c * lda];
+            part += a.x * a.x + a.y * a.y;
+        }
+        const R sig2 = block_sum(part, red[0]);
+        cx<R> tau, scale;
+        R beta;
+        reflector_core(A[c1 + c * lda], sig2, tau, scale, beta);
+        for (int s = c1 + tid; s < M; s += T) {
+            const cx<R> v = csel(s == c1, mk<R>(1, 0), cmul(scale, A[s + c * lda]));
+            sv[s] = v;
+            V[(int64_t)(i0 + s) + (int64_t)i * n] = v;
+        }
+        __syncthreads();
+        // y = tau A22 v and v^H A22 v
+        part = 0;
+        for (int r = c1 + tid; r < M; r += T) {
+            cx<R> y = czero<cx<R>>();
+            for (int s = c1; s < r; ++s) y = cfma(A[r + s * lda], sv[s], y);
+            y = cfma(mk<R>(A[r + r * lda].x, 0), sv[r], y);
+            for (int s = r + 1; s < M; ++s) y = cfmac(A[s + r * lda], sv[s], y);
+            part += sv[r].x * y.x + sv[r].y * y.y;
+            sw[r] = cmul(tau, y);
+        }
+        const R vav = block_sum(part, red[1]);
+        const R a2 = (R)-0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
+        for (int r = c1 + tid; r < M; r += T) sw[r] = cadd(sw[r], cscale(sv[r], a2));
+        __syncthreads();
+        for (int r = c1 + tid; r < M; r += T)
+            for (int s = c1; s <= r; ++s)
+                A[r + s * lda] = csub(A[r + s * lda], cadd(cmulc(sw[s], sv[r]), cmulc(sv[s], sw[r])));
+        __syncthreads();
+        if (tid == 0) {
+            ws.e[b * n + i] = beta;
+            ws.tau[b * n + i] = tau;
+            ws.d[b * n + i + 1] = A[c1 + c1 * lda].x;
+        }
+    }
+}
+
+template <typename R, int RT, int KC>
+hipError_t launch_group(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk)
+{
+    const int M = ws.n - i0, nt = (M + 15) / 16;
+    const int G = (nt + KC - 1) / KC;
+    if (nt > RT * RT_W || G > GROUP_MAX) return hipErrorInvalidValue;
+    const Exchange<R> ex(ws, 0, M);
+    const int words = 2 + 3 * ex.slot_words();
+    hipLaunchKernelGGL(k_exchange_init<R>, dim3((unsigned)((words + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws, M);
+    hipLaunchKernelGGL((hetrd_group<R, RT, KC>), dim3((unsigned)(nk * G)), dim3(RT_T), 0, st, ws, i0, G,
+                       tl_group_wait_ticks);
+    hipLaunchKernelGGL(hetrd_memory<R>, dim3((unsigned)nk), dim3(1024), 0, st, ws, i0, G);
+    return hipGetLastError();
+}
+
+constexpr int CUS = 256;    // compute units: a workgroup of a group fills one
+
+// For each largest order: the widest share of a member (tile columns), set by
+// the registers (RT * KC tiles of 16 each in FP64), and the microseconds a
+// column takes with that share when the groups fill the chip (measured at
+// 256 x 64, 384 x 32, 512 x 16, 640 x 12, 768 x 5 and 1024 x 4 problems).
+struct GroupShape {
+    int M, KC;
+    double us;
+};
+constexpr GroupShape GROUP_SHAPES[] = {{256, 4, 3.8}, {384, 3, 4.4},  {512, 2, 4.4},
+                                       {640, 2, 5.7}, {768, 1, 4.5}, {1024, 1, 5.2}};
+
+// How often the chip is filled with whole groups.  Where groups take turns and
+// do not divide the chip, the partly placed one holds compute units idle:
+// measured 2.7 times one round for 24 problems of order 640 (12 at once).
+double group_rounds(int M, int KC, int64_t nk)
+{
+    const int64_t G = ((M + 15) / 16 + KC - 1) / KC, at_once = CUS / G;
+    const int64_t rounds = (nk + at_once - 1) / at_once;
+    return (double)rounds + (rounds > 1 && CUS % G != 0 ? 0.7 : 0.0);
+}
+
 }  // namespace
+
+// The hand-over order with the least estimated time for the whole reduction:
+// blocked columns at 12 us plus 4 TB/s over the lower triangles (two launches
+// and the HBM reads of a column; 16 us at m = 192, 33 us at m = 390 and 90 us at
+// m = 780 with 64 problems, 11 us at m = 500 with one), then the groups' columns
+// times their rounds.  512 columns: 1 problem 5.1 -> 1.75 ms, 8 problems 5.2 ->
+// 2.1 ms, 64 problems (4 rounds) 11.0 -> 8.2 ms; 1024 columns of one problem
+// 11.3 -> 4.9 ms.
+int hetrd_res_order(int n, int nb, int64_t nk, int groups)
+{
+    int best = HETRD_RES_M;
+    if (!groups || n <= GROUP_MIN) return best;
+    double least = 0.0;
+    for (int q = -1; q < (int)(sizeof(GROUP_SHAPES) / sizeof(GROUP_SHAPES[0])); ++q) {
+        const int cap = q < 0 ? HETRD_RES_M : GROUP_SHAPES[q].M;
+        const int p = n > cap ? (n - cap + nb - 1) / nb * nb : 0;      // the hand-over column
+        const int M = n - p;
+        if (q >= 0 && M <= HETRD_RES_M) continue;
+        const double dn = n, dM = M;
+        double us = 12.0 * (dn - dM) + 8.0 * (double)nk / 4.0e6 * (dn * dn * dn - dM * dM * dM) / 3.0;
+        us += q < 0 ? 2.0 * dM : group_rounds(M, GROUP_SHAPES[q].KC, nk) * dM * GROUP_SHAPES[q].us;
+        if (q < 0 || us < least) {
+            least = us;
+            best = cap;
+        }
+    }
+    return best;
+}
 
 template <typename R>
 hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk)
 {
-    if (ws.n - i0 <= 64)
-        hipLaunchKernelGGL((hetrd_resident<R, 1, 4>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
-    else
-        hipLaunchKernelGGL((hetrd_resident<R, 1, 8>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
-    return hipGetLastError();
+    const int M = ws.n - i0;
+    if (M <= 128) {
+        if (M <= 64)
+            hipLaunchKernelGGL((hetrd_resident<R, 1, 4>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
+        else
+            hipLaunchKernelGGL((hetrd_resident<R, 1, 8>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
+        return hipGetLastError();
+    }
+    // The narrowest shares that all run at once (more compute units per column);
+    // where not even the widest do, the widest, so that the groups take turns
+    // in as few rounds as possible.  The sums do not depend on the share.
+    auto fits = [&](int KC) { return group_rounds(M, KC, nk) < 1.5; };
+    if (M <= 256) {
+        if (fits(1)) return launch_group<R, 2, 1>(st, ws, i0, nk);
+        if (fits(2)) return launch_group<R, 2, 2>(st, ws, i0, nk);
+        return launch_group<R, 2, 4>(st, ws, i0, nk);
+    }
+    if (M <= 384) return fits(1) ? launch_group<R, 3, 1>(st, ws, i0, nk) : launch_group<R, 3, 3>(st, ws, i0, nk);
+    if (M <= 512) return fits(1) ? launch_group<R, 4, 1>(st, ws, i0, nk) : launch_group<R, 4, 2>(st, ws, i0, nk);
+    if (M <= 640) return fits(1) ? launch_group<R, 5, 1>(st, ws, i0, nk) : launch_group<R, 5, 2>(st, ws, i0, nk);
+    if (M <= 768) return launch_group<R, 6, 1>(st, ws, i0, nk);
+    if (M <= HETRD_GROUP_M) return launch_group<R, 8, 1>(st, ws, i0, nk);
+    return hipErrorInvalidValue;
 }
 template hipError_t hetrd_res<double>(hipStream_t, const HetrdWs<double>&, int, int64_t);
 template hipError_t hetrd_res<float>(hipStream_t, const HetrdWs<float>&, int, int64_t);
 
 }  // namespace kgev
+
+// For tests: the wait for a group's members to start, in 100 MHz ticks, for the
+// calling thread (0 gives every group up at once; negative: the default).
+extern "C" void kgev_internal_group_wait(int64_t ticks)
+{
+    kgev::tl_group_wait_ticks = ticks < 0 ? kgev::GROUP_WAIT_TICKS : ticks;
+}

@@ -69,9 +69,10 @@ struct HetrdWs {
     int zch;                   // tiles per chunk of the Hermitian product (set by hetrd: 4, or 1)
     int slots1;                // a column takes one-tile chunks when four-tile chunks would launch
                                // fewer workgroups than this over all problems (0: 768)
+    int groups;                // the last columns may go to groups of workgroups (hetrd_res.hip)
     cx<R>* A; int64_t lda, sA; // matrix (lower), reduced in place
     cx<R>* V; int64_t sV;      // reflectors, n x n, ld n (zero outside the reflector rows)
-    cx<R>* W; int64_t sW;      // panel W, n x nb, ld n
+    cx<R>* W; int64_t sW;      // panel W, n x nb, ld n; the buffer holds 64 n values per problem
     R* d; R* e; cx<R>* tau;    // stride n per problem
     // The per-column partials below come in two buffers selected by the
     // parity of the column they describe: the kernel that consumes column
@@ -92,10 +93,13 @@ int hetrd_pn(int64_t n);   // partial norms per column (one per 64-row block)
 template <typename R>
 hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws, int64_t nk);
 // columns i0.. of the reduction in one launch with the trailing matrix in
-// registers (hetrd_res.hip); 2 <= n - i0 <= HETRD_RES_M
-constexpr int HETRD_RES_M = 128;
+// registers (hetrd_res.hip), of one workgroup per problem up to order
+// HETRD_RES_M and of a group of workgroups up to HETRD_GROUP_M; 2 <= n - i0
+constexpr int HETRD_RES_M = 128, HETRD_GROUP_M = 1024;
 template <typename R>
 hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk);
+// the order at which nk reductions of order n in panels of nb hand over to it
+int hetrd_res_order(int n, int nb, int64_t nk, int groups);
 
 // ---------------------------------------------------------------------------
 // divide-and-conquer tridiagonal eigensolver (stedc.hip)

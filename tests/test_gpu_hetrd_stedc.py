@@ -224,3 +224,50 @@ def test_stebz_closed_forms():
 @pytest.mark.parametrize("n", [4, 15, 16, 18, 31, 33, 48, 63, 66, 80, 111, 113, 127, 140])
 def test_resident_reduction_edges(n):
     test_hetrd_matches_oracle(n, 0)
+
+
+# groups of workgroups: orders at the edges of their shapes (256, 384, 512) and
+# of their tiles, more problems than run at once, and the panels before the
+# hand-over
+@pytest.mark.parametrize("n", [161, 175, 256, 257, 272, 385, 520])
+def test_group_reduction_matches_oracle(n):
+    test_hetrd_matches_oracle(n, 0)
+
+
+def spectrum_check(n, nk, seed):
+    """T and V of nk reductions against the matrices: the spectrum of T, and
+    Q^H A Q = T through the reflectors of the first and last problem."""
+    rng = np.random.default_rng(seed)
+    As = np.stack([rand_herm(rng, n) for _ in range(nk)])
+    d, e, tau, V = gpu_hetrd(As)
+    for q in sorted({0, nk // 2, nk - 1}):
+        tol = 64 * n * EPS * np.linalg.norm(As[q])
+        T = np.diag(d[q]) + np.diag(e[q, : n - 1], 1) + np.diag(e[q, : n - 1], -1)
+        assert mx(np.linalg.eigvalsh(T) - np.linalg.eigvalsh(As[q])) <= tol
+        B = As[q].copy()
+        for i in range(n - 1):
+            v, t = V[q][:, i], tau[q, i]
+            B -= np.outer(np.conj(t) * v, v.conj() @ B)   # H_i^H B, H_i = I - t v v^H
+        for i in range(n - 1):
+            v, t = V[q][:, i], tau[q, i]
+            B -= np.outer(B @ v, t * v.conj())            # ... B H_i
+        assert mx(B - T) <= tol
+
+
+@pytest.mark.parametrize("n,nk", [(200, 70), (500, 20), (640, 1), (641, 2), (768, 3), (900, 2), (1024, 1), (1090, 1)])
+def test_group_reduction_spectrum(n, nk):
+    spectrum_check(n, nk, 31 * n + nk)
+
+
+def test_group_given_up_is_reduced_in_memory():
+    """No member waits for the others: every group is given up and the
+    problems are reduced with the matrix in memory, with the same results."""
+    import ctypes
+    lib = K().lib
+    lib.kgev_internal_group_wait.argtypes = [ctypes.c_int64]
+    try:
+        lib.kgev_internal_group_wait(0)
+        test_hetrd_matches_oracle(230, 0)
+        spectrum_check(300, 5, 77)
+    finally:
+        lib.kgev_internal_group_wait(-1)
