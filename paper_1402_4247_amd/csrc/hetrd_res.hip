@@ -293,15 +293,20 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
 // g, g + G, ... (KC of them at most) over all tile rows; x, v and w are kept
 // by every member.  A member's column sums are complete, so one exchange per
 // column joins the group: each member publishes z_s and A(s, c+1) of its
-// columns and its share of q, and every member reads all of them.
+// columns, and every member reads all of them (each line once per member: with
+// every wave also reading z_{c+1} and the members' shares of q, 3.0 us a column
+// at order 200 instead of 2.6).
 //
 // The exchange is the data itself: a slot that holds SENTINEL (a NaN no
 // arithmetic produces; a value with its bits is published as another NaN) has
 // not been published.  Slots form a ring of three: whoever has read every
-// member's column c knows that every member has read column c - 1, so the
-// owner clears the slots of column c - 1 then and publishes column c + 1 after
-// the clears have reached memory; a reader of column c + 2 (the same slot) has
-// read column c + 1 first and cannot see column c - 1's values.
+// member's column c knows that every member has read column c - 1, so an
+// owner clears its slots of column c - 1 then, and publishes column c + 1 only
+// after the clears have reached memory; a reader of column c + 2 (the same
+// slots) has read that owner's column c + 1 first, so it cannot see column
+// c - 1's values.  A member publishes as long as it has unfinished columns and
+// leaves, without reading, once it has none: whoever still reads still
+// publishes, so the others' knowledge covers it.
 //
 // The members of a group must run together.  Workgroups take their (problem,
 // member) from a counter when they start, so groups fill in order and at most
@@ -313,11 +318,11 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
 // of the 256 compute units, so four launches on different streams (the
 // hardware queues of a process) cannot hold each other's partly placed groups.
 //
-// Bound by the latency of a column: the exchange (a store and a polled load
-// through the coherent level, about half of it), one workgroup barrier on
-// each side of it and phase B's chain: 3.0 us a column at order 200, 3.4 us at
-// 512, 4.8 us at 1024 (one problem), against 11-13 us for the two launches of
-// a blocked column.
+// Bound by the latency of a column: the exchange (a store and a load through
+// the coherent level, 0.5-0.7 us between any two compute units), three
+// workgroup barriers and phase B's chain: 2.3 us a column at order 200, 2.75 us
+// at 512, 3.8 us at 1024 (one problem), against 11-13 us for the two launches
+// of a blocked column.
 constexpr uint64_t SENTINEL = 0xFFF4DEADFFF4BEEFull;   // two NaNs as well for a pair of floats
 constexpr uint32_t GIVEN_UP = 0x80000000u;
 constexpr int GROUP_MAX = 64;             // members of a group at most
@@ -336,7 +341,7 @@ template <typename T> __device__ __attribute__((always_inline)) inline void stor
 // The exchange area of one problem, in the panel buffer W (which the blocked
 // columns before have finished with; 64 n complex values a problem): a header
 // of two 64-bit words {members started | GIVEN_UP, next ticket (problem 0
-// only)}, then three slots of {z (MP complex), A(:, c+1) (MP complex), q (GROUP_MAX)}.
+// only)}, then three slots of {z (MP complex), A(:, c+1) (MP complex)}.
 template <typename R> struct Exchange {
     static constexpr int WPC = 2 * sizeof(R) / 8;      // 64-bit words per complex value
     uint64_t* base;
@@ -345,11 +350,10 @@ template <typename R> struct Exchange {
         : base(reinterpret_cast<uint64_t*>(ws.W + b * 64 * (int64_t)ws.n)), MP((M + 15) & ~15) {}
     __device__ uint32_t* started() const { return reinterpret_cast<uint32_t*>(base); }
     __device__ uint32_t* ticket() const { return reinterpret_cast<uint32_t*>(base + 1); }
-    __device__ __host__ int slot_words() const { return 2 * WPC * MP + GROUP_MAX; }
+    __device__ __host__ int slot_words() const { return 2 * WPC * MP; }
     __device__ uint64_t* slot(int q) const { return base + 2 + (int64_t)q * slot_words(); }
     // word c of value s of list l (0: z, 1: A(:, c+1)) in a slot
     __device__ int at(int l, int s, int c) const { return (l * WPC + c) * MP + s; }
-    __device__ int at_q(int g) const { return 2 * WPC * MP + g; }
 };
 
 __device__ inline uint64_t word_of(double v)
@@ -372,12 +376,6 @@ template <typename R> __device__ inline cx<R> value_of(const uint64_t* u)
         return mk<R>(__uint_as_float((uint32_t)u[0]), __uint_as_float((uint32_t)(u[0] >> 32)));
 }
 
-template <typename R> __device__ inline R q_of(uint64_t u)
-{
-    if constexpr (sizeof(R) == 8) return __longlong_as_double((long long)u);
-    else return __uint_as_float((uint32_t)u);
-}
-
 template <typename R>
 __global__ __launch_bounds__(256) void k_exchange_init(HetrdWs<R> ws, int M)
 {
@@ -396,13 +394,14 @@ __global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G
     constexpr int SP = (MPX + RT_T - 1) / RT_T;  // rows per thread
     constexpr int FS = MPX + 16;
     constexpr int WPC = Ex::WPC;
-    static_assert(KC * 16 < RT_T, "a thread per owned column and one for q");
+    static_assert(KC * 16 <= WAVE, "a lane of the first wave per owned column");
     __shared__ R F[4][FS];
     __shared__ cx<R> x[MPX];
     __shared__ cx<R> zp[RT_W][KC * 16];
     __shared__ cx<R> hrow[KC * 16];
     __shared__ R red[RT_W], sq[RT_W];
-    __shared__ cx<R> salpha;
+    __shared__ cx<R> salpha, sref[2], sz1;   // x_{c+1}; tau, scale; z_{c+1}
+    __shared__ R shoo;                       // A(c+1, c+1)
     __shared__ int sgo, sdead;
     __shared__ uint32_t sticket;
 
@@ -476,57 +475,74 @@ __global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G
     if (lane == 0) red[w] = nrm;
     lds_barrier();
 
+    // wave 0 publishes: lane's local column, its share of it, and the column
+    constexpr int PARTS = KC == 1 ? (WPC == 2 ? 4 : 2) : KC == 2 ? 2 : 1;
+    const int pcol = lane / PARTS, part = lane % PARTS;
+    const int own = pcol < KC * 16 ? (g + G * (pcol >> 4)) * 16 + (pcol & 15) : M;
+    const int last = g + G * ((nt - 1 - g) / G);          // this member's last tile column
     int ring = 0;                       // c mod 3
     for (int c = 0; c + 1 < M; ++c) {
         const int c1 = c + 1, i = i0 + c, k1 = c1 >> 4;
         uint64_t* const cur = ex.slot(ring);
-        uint64_t* const old = ex.slot(ring == 0 ? 1 : ring == 1 ? 2 : 0);     // column c - 2's, c + 1's next
-        const int own = (g + G * (tid >> 4)) * 16 + (tid & 15);       // this thread's owned column
-        // ---- clear the slots of column c - 2 (every member has read them)
-        if (tid < KC * 16 && own < M) {
-#pragma unroll
-            for (int u = 0; u < WPC; ++u) {
-                store_agent(old + ex.at(0, own, u), SENTINEL);
-                store_agent(old + ex.at(1, own, u), SENTINEL);
-            }
-        }
-        if (tid == KC * 16) store_agent(old + ex.at_q(g), SENTINEL);
-        // ---- A: pending update, column sums
+        uint64_t* const old = ex.slot(ring == 0 ? 2 : ring - 1);     // column c - 1's, c + 2's next
+        // ---- A: pending update and column sums of the live tiles (the
+        // operands of the next tile row are requested ahead, whether it is
+        // live or not: no wait inside the branches)
         R opB[KC];
         cx<R> za[KC];
+        bool livek[KC];
 #pragma unroll
         for (int k = 0; k < KC; ++k) {
             const int C = g + G * k;
             opB[k] = F[lk ^ 2][(C < nt ? C : 0) * 16 + li];
+            livek[k] = C >= k1 && C < nt;
             za[k] = zero;
         }
+        constexpr bool AHEAD = RT * KC < 8;      // (the registers of more tiles leave no room)
+        R are = AHEAD ? F[lk][w * 16 + li] : (R)0, aim = AHEAD ? F[lk ^ 1][w * 16 + li] : (R)0;
 #pragma unroll
         for (int q = 0; q < RT; ++q) {
             const int Rt = w + RT_W * q;
+            if (!AHEAD) {
+                are = F[lk][Rt * 16 + li];
+                aim = F[lk ^ 1][Rt * 16 + li];
+            }
+            const R nre = -are, nim = -aim;
+            if (AHEAD && q + 1 < RT) {
+                are = F[lk][(Rt + RT_W) * 16 + li];
+                aim = F[lk ^ 1][(Rt + RT_W) * 16 + li];
+            }
             if (Rt >= k1 && Rt < nt) {
-                const R are = -F[lk][Rt * 16 + li], aim = -F[lk ^ 1][Rt * 16 + li];
 #pragma unroll
                 for (int k = 0; k < KC; ++k)
-                    if (g + G * k >= k1 && g + G * k < nt) {
-                        tr[q][k] = M_::mma(are, opB[k], tr[q][k]);
-                        ti[q][k] = M_::mma(aim, (lk & 1) ? -opB[k] : opB[k], ti[q][k]);
+                    if (livek[k]) {
+                        tr[q][k] = M_::mma(nre, opB[k], tr[q][k]);
+                        ti[q][k] = M_::mma(nim, (lk & 1) ? -opB[k] : opB[k], ti[q][k]);
                     }
             }
         }
+        cx<R> xn4[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xn4[r] = csel(AHEAD, x[w * 16 + M_::row(lk, r)], zero);
 #pragma unroll
         for (int q = 0; q < RT; ++q) {
             const int Rt = w + RT_W * q;
-            if (Rt >= k1 && Rt < nt) {
-                cx<R> xr[4];
+            cx<R> xr[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) xr[r] = x[Rt * 16 + M_::row(lk, r)];
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (AHEAD) xr[r] = xn4[r];
+                else xr[r] = x[Rt * 16 + M_::row(lk, r)];
+                if (AHEAD && q + 1 < RT) xn4[r] = x[(Rt + RT_W) * 16 + M_::row(lk, r)];
+            }
+            if (Rt >= k1 && Rt < nt) {
 #pragma unroll
                 for (int k = 0; k < KC; ++k)
-                    if (g + G * k >= k1 && g + G * k < nt) {
+                    if (livek[k]) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) za[k] = cfmac(mk<R>(tr[q][k][r], ti[q][k][r]), xr[r], za[k]);
                     }
                 if (Rt == k1) {
+                    // this wave holds row c + 1: A(:, c+1) is its conjugate
                     const int rr = row_r<R>(c1 & 15);
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
@@ -537,83 +553,135 @@ __global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G
                 }
             }
         }
-        R qs = 0;
-        sum_lane_groups<R, KC>(za, lk, [&](int k, cx<R> v) {
-            zp[w][k * 16 + li] = v;
-            const int s = (g + G * k) * 16 + li;
-            const cx<R> xc = x[s < MPX ? s : 0];
-            qs = fma(xc.x, v.x, fma(xc.y, v.y, qs));
-        });
-        qs = dpp_wave_sum(qs);
-        if (lane == 0) sq[w] = qs;
+        sum_lane_groups<R, KC>(za, lk, [&](int k, cx<R> v) { zp[w][k * 16 + li] = v; });
         lds_barrier();
-        // ---- publish (after this wave's clears have reached memory)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (tid < KC * 16 && own >= c1 && own < M) {
-            const cx<R> z = cadd(cadd(cadd(zp[0][tid], zp[1][tid]), cadd(zp[2][tid], zp[3][tid])),
-                                 cadd(cadd(zp[4][tid], zp[5][tid]), cadd(zp[6][tid], zp[7][tid])));
-            const cx<R> h = hrow[tid];
-            if constexpr (WPC == 2) {
-                store_agent(cur + ex.at(0, own, 0), word_of(z.x));
-                store_agent(cur + ex.at(0, own, 1), word_of(z.y));
-                store_agent(cur + ex.at(1, own, 0), word_of(h.x));
-                store_agent(cur + ex.at(1, own, 1), word_of(h.y));
-            } else {
-                store_agent(cur + ex.at(0, own, 0), word_of(z.x, z.y));
-                store_agent(cur + ex.at(1, own, 0), word_of(h.x, h.y));
+        if (w == 0) {
+            // ---- publish, after the last clears have reached memory
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // PARTS lanes per column: each adds its share of the waves and
+            // stores its share of the words (the pairwise sums are the same
+            // for any PARTS)
+            cx<R> v[RT_W / PARTS];
+#pragma unroll
+            for (int u = 0; u < RT_W / PARTS; ++u) v[u] = zp[part * (RT_W / PARTS) + u][pcol < KC * 16 ? pcol : 0];
+            const cx<R> h1 = hrow[pcol < KC * 16 ? pcol : 0];
+#pragma unroll
+            for (int st = 1; st < RT_W / PARTS; st *= 2)
+#pragma unroll
+                for (int u = 0; u < RT_W / PARTS; u += 2 * st) v[u] = cadd(v[u], v[u + st]);
+            cx<R> zs = v[0];
+            if constexpr (PARTS >= 2) {
+                zs.x = dpp_sum<PARTS>(zs.x);
+                zs.y = dpp_sum<PARTS>(zs.y);
+            }
+            if (own >= c1 && own < M) {
+                uint64_t word[2 * WPC];
+                if constexpr (WPC == 2) {
+                    word[0] = word_of(zs.x);
+                    word[1] = word_of(zs.y);
+                    word[2] = word_of(h1.x);
+                    word[3] = word_of(h1.y);
+                } else {
+                    word[0] = word_of(zs.x, zs.y);
+                    word[1] = word_of(h1.x, h1.y);
+                }
+#pragma unroll
+                for (int e = 0; e < 2 * WPC; ++e)
+                    if (e % PARTS == part) store_agent(cur + e * ex.MP + own, word[e]);
+            }
+        } else if (w == RT_W - 1) {
+            // ---- Procedure 2 while the columns travel
+            const R sig2 = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+            cx<R> tau, scale;
+            R beta;
+            reflector_core(salpha, sig2, tau, scale, beta);
+            if (lane == 0) {
+                sref[0] = tau;
+                sref[1] = scale;
+                if (last == nt - 1) {
+                    ws.e[b * n + i] = beta;
+                    ws.tau[b * n + i] = tau;
+                }
             }
         }
-        if (tid == KC * 16) {
-            const R q = ((sq[0] + sq[1]) + (sq[2] + sq[3])) + ((sq[4] + sq[5]) + (sq[6] + sq[7]));
-            if constexpr (WPC == 2) store_agent(cur + ex.at_q(g), word_of(q));
-            else store_agent(cur + ex.at_q(g), word_of(q, (R)0));
-        }
-        // ---- Procedure 2, in every wave, while the columns travel
-        cx<R> tau, scale;
-        R beta;
-        {
-            const R sig2 = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
-            reflector_core(salpha, sig2, tau, scale, beta);
-        }
+        // a member whose columns are finished has nothing left to do (and
+        // must not read on: the others no longer wait for it)
+        const int k1n = (c1 + 1) >> 4;
+        if (last < k1n && last != nt - 1) return;
         // ---- read every member's columns
-        uint64_t uz[SP][WPC], uh[SP][WPC], u1[2 * WPC], uq;
-        for (int polls = 0;; ++polls) {
-            bool missing = false;
-            auto get = [&](int word) {
-                const uint64_t v = load_agent(cur + word);
-                missing |= v == SENTINEL;
-                return v;
-            };
+        cx<R> z[SP], h[SP];
+        R qs = 0;
+        if (w * WAVE < M) {
+            uint64_t uz[SP][WPC], uh[SP][WPC];
+            bool wants[SP];
+#pragma unroll
+            for (int u = 0; u < SP; ++u) wants[u] = tid + RT_T * u >= c1 && tid + RT_T * u < M;
+            // The columns arrive 0.5 us and more after they were published; a poll
+            // issued before that only loads the fabric that carries them (512
+            // x 8 problems: 4.0 us a column without this wait, 2.8 with 770
+            // cycles; the reflector's wave has used most of it already).
+            if (w == RT_W - 1) __builtin_amdgcn_s_sleep(4);
+            else __builtin_amdgcn_s_sleep(12);
+            for (int polls = 0;; ++polls) {
+                bool missing = false;
+#pragma unroll
+                for (int u = 0; u < SP; ++u) {
+                    const int s = tid + RT_T * u;
+                    if (wants[u]) {
+                        bool none = false;
+#pragma unroll
+                        for (int e = 0; e < WPC; ++e) {
+                            uz[u][e] = load_agent(cur + ex.at(0, s, e));
+                            uh[u][e] = load_agent(cur + ex.at(1, s, e));
+                        }
+#pragma unroll
+                        for (int e = 0; e < WPC; ++e) none |= uz[u][e] == SENTINEL || uh[u][e] == SENTINEL;
+                        wants[u] = none;
+                        missing |= none;
+                    }
+                }
+                if (!__any(missing)) break;
+                if (polls >= POLLS_MAX) {
+                    sdead = 1;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
 #pragma unroll
             for (int u = 0; u < SP; ++u) {
                 const int s = tid + RT_T * u;
                 if (s >= c1 && s < M) {
-#pragma unroll
-                    for (int e = 0; e < WPC; ++e) {
-                        uz[u][e] = get(ex.at(0, s, e));
-                        uh[u][e] = get(ex.at(1, s, e));
+                    z[u] = value_of<R>(uz[u]);
+                    h[u] = value_of<R>(uh[u]);
+                    const cx<R> xs = x[s];
+                    qs = fma(xs.x, z[u].x, fma(xs.y, z[u].y, qs));
+                    if (s == c1) {
+                        sz1 = z[u];
+                        shoo = h[u].x;
                     }
                 }
             }
-#pragma unroll
-            for (int e = 0; e < WPC; ++e) {
-                u1[e] = get(ex.at(0, c1, e));
-                u1[WPC + e] = get(ex.at(1, c1, e));
-            }
-            uq = 0;
-            if (lane < G) uq = get(ex.at_q(lane));
-            if (!__any(missing)) break;
-            if (polls >= POLLS_MAX) {
-                sdead = 1;
-                break;
-            }
+            qs = dpp_wave_sum(qs);
         }
+        if (lane == 0) sq[w] = qs;
+        lds_barrier();
         // ---- B
-        R qq = q_of<R>(uq);        // zero where there is no member
-        qq = dpp_wave_sum(qq);
-        const cx<R> z1 = value_of<R>(u1), h1 = value_of<R>(u1 + WPC);
-        const R hoo = h1.x;
-        const cx<R> sz = cmul(scale, z1);
+        if (w == 0 && own < M) {
+            // every member has published column c, so every member has read
+            // column c - 1: clear its slots
+#pragma unroll
+            for (int e = 0; e < 2 * WPC; ++e)
+                if (e % PARTS == part) store_agent(old + e * ex.MP + own, SENTINEL);
+        }
+        // v is stored by the owners of the last eight tile columns in turn
+        const int Cv = nt - 1 - (c & 7) >= k1n ? nt - 1 - (c & 7) : nt - 1;
+        bool stores_v = false;
+#pragma unroll
+        for (int k = 0; k < KC; ++k) stores_v |= g + G * k == Cv;
+        const cx<R> tau = sref[0], scale = sref[1];
+        const R hoo = shoo;
+        const R qq = ((sq[0] + sq[1]) + (sq[2] + sq[3])) + ((sq[4] + sq[5]) + (sq[6] + sq[7]));
+        const cx<R> sz = cmul(scale, sz1);
         const R vav = hoo + (R)2 * sz.x + (scale.x * scale.x + scale.y * scale.y) * qq;
         const R a2 = (R)-0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
         const cx<R> w1 = cadd(cmul(tau, cadd(mk<R>(hoo, 0), sz)), mk<R>(a2, 0));
@@ -624,13 +692,12 @@ __global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G
             if (s < MPX) {
                 cx<R> vs = zero, wv = zero, xn = zero;
                 if (s >= c1 && s < M) {
-                    const cx<R> z = value_of<R>(uz[u]), h = value_of<R>(uh[u]);
                     vs = csel(s == c1, mk<R>(1, 0), cmul(scale, x[s]));
-                    wv = csel(s == c1, w1, cfma(tau, cfma(scale, z, h), cscale(vs, a2)));
+                    wv = csel(s == c1, w1, cfma(tau, cfma(scale, z[u], h[u]), cscale(vs, a2)));
                     // x'_s = h_s - (v_s conj(w_{c+1}) + w_s)
-                    xn = csub(h, cadd(cmulc(w1, vs), wv));
-                    if (c % G == g) V[(int64_t)(i0 + s) + (int64_t)i * n] = vs;
-                    if (s == c1 && g == 0) ws.d[b * n + i + 1] = hoo - (R)2 * w1.x;
+                    xn = csub(h[u], cadd(cmulc(w1, vs), wv));
+                    if (stores_v) V[(int64_t)(i0 + s) + (int64_t)i * n] = vs;
+                    if (s == c1 && last == nt - 1) ws.d[b * n + i + 1] = hoo - (R)2 * w1.x;
                     if (s == c1 + 1) salpha = xn;
                     xn = csel(s >= c1 + 2, xn, zero);
                     nrm += xn.x * xn.x + xn.y * xn.y;
@@ -641,10 +708,6 @@ __global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G
                 F[3][s] = wv.y;
                 x[s] = xn;
             }
-        }
-        if (tid == 0 && g == 0) {
-            ws.e[b * n + i] = beta;
-            ws.tau[b * n + i] = tau;
         }
         nrm = dpp_wave_sum(nrm);
         if (lane == 0) red[w] = nrm;
@@ -750,8 +813,8 @@ struct GroupShape {
     int M, KC;
     double us;
 };
-constexpr GroupShape GROUP_SHAPES[] = {{256, 4, 3.8}, {384, 3, 4.4},  {512, 2, 4.4},
-                                       {640, 2, 5.7}, {768, 1, 4.5}, {1024, 1, 5.2}};
+constexpr GroupShape GROUP_SHAPES[] = {{256, 4, 3.2}, {384, 3, 3.7},  {512, 2, 3.6},
+                                       {640, 2, 4.4}, {768, 1, 3.4}, {1024, 1, 3.9}};
 
 // How often the chip is filled with whole groups.  Where groups take turns and
 // do not divide the chip, the partly placed one holds compute units idle:
@@ -813,7 +876,11 @@ hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk)
         if (fits(2)) return launch_group<R, 2, 2>(st, ws, i0, nk);
         return launch_group<R, 2, 4>(st, ws, i0, nk);
     }
-    if (M <= 384) return fits(1) ? launch_group<R, 3, 1>(st, ws, i0, nk) : launch_group<R, 3, 3>(st, ws, i0, nk);
+    if (M <= 384) {
+        if (fits(1)) return launch_group<R, 3, 1>(st, ws, i0, nk);
+        if (fits(2)) return launch_group<R, 3, 2>(st, ws, i0, nk);
+        return launch_group<R, 3, 3>(st, ws, i0, nk);
+    }
     if (M <= 512) return fits(1) ? launch_group<R, 4, 1>(st, ws, i0, nk) : launch_group<R, 4, 2>(st, ws, i0, nk);
     if (M <= 640) return fits(1) ? launch_group<R, 5, 1>(st, ws, i0, nk) : launch_group<R, 5, 2>(st, ws, i0, nk);
     if (M <= 768) return launch_group<R, 6, 1>(st, ws, i0, nk);
