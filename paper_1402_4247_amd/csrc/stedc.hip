@@ -114,18 +114,31 @@ __device__ inline void wave_sync()
 // the leaf is held as a dense symmetric LEAF x LEAF matrix in LDS (rows past
 // the leaf are zero and never rotated), and each sweep takes LEAF - 1 rounds of
 // LEAF / 2 disjoint rotations (round-robin pairing with the last index fixed).
-// A rotation of the (p, q) plane with c = 1 / sqrt(1 + t^2), s = t c,
-// t = sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a_qq - a_pp) / (2 a_pq),
-// zeroes a_pq; each lane forms the rotation of pair lane mod 8 and applies it
+// A rotation of the (p, q) plane with s / c = sign(tau) / (|tau| +
+// sqrt(1 + tau^2)), tau = (a_qq - a_pp) / (2 a_pq), zeroes a_pq; each lane forms the rotation of pair lane mod 8 and applies it
 // to two rows (then two columns): the columns of A and of the accumulated V
 // together, then the rows of A.  An off-diagonal entry
 // at most eps * max_i(|d_i| + |e_i|) is left alone (the normwise deflation
 // threshold of implicit QL); a sweep that rotates nothing ends the iteration.
 // Eigenvalues go to D[0] ascending, the eigenvectors (columns of V) to the
-// leaf's diagonal block of Q[0] (the rest of Q[0] is the identity's zeros).
+// leaf's diagonal block of Q[0], with zeros in the rows of its parent segment
+// outside the leaf (the parent merge reads its whole diagonal block).
 // The rounds are short dependent chains of LDS traffic, where a QL sweep is a
 // chain of rotations, each with a square root and a reciprocal.
 constexpr int LEAF_SWEEPS = 30;
+
+// 1 / sqrt(x): the hardware's estimate and two Newton steps (a third of the
+// latency of a square root and a division, which a round's chain is made of)
+__device__ inline double rsqrt_nr(double x)
+{
+    double r = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const double e = fma(-x * r, r, 1.0);
+        r = fma(0.5 * r, e, r);
+    }
+    return r;
+}
 
 __device__ inline void leaf_pair(int r, int k, int& p, int& q)
 {
@@ -161,14 +174,21 @@ __global__ __launch_bounds__(64) void dc_leaf(DcWs ws, int tl)
     const double dr = lane < ns ? D[s + lane] : 0.0;
     const double er = lane + 1 < ns ? es[s + lane] : 0.0;
     // the deflation threshold from the leaf's norm (max over rows of |d| + |e|)
-    const double tol = 2.220446049250313e-16 * dpp_wave_max(fabs(dr) + fabs(er));
+    const double norm = dpp_wave_max(fabs(dr) + fabs(er));
+    // the leaf is taken at norm 0.5..1 (an exact power of two away), so that
+    // the squares of entries above the threshold stay in range
+    int ex = 0;
+    (void)frexp(norm, &ex);
+    ex = norm > 0.0 && isfinite(norm) ? max(ex, -1000) : 0;
+    const double up = ldexp(1.0, -ex), down = ldexp(1.0, ex);
+    const double tol = 2.220446049250313e-16 * (norm * up);
     for (int e = lane; e < LEAF * LEAF; e += 64) {
         const int i = e / LEAF, j = e % LEAF;
         double a = 0.0;
         if (i < ns && j < ns) {
-            if (i == j) a = D[s + i];
-            else if (j == i + 1) a = es[s + i];
-            else if (i == j + 1) a = es[s + j];
+            if (i == j) a = D[s + i] * up;
+            else if (j == i + 1) a = es[s + i] * up;
+            else if (i == j + 1) a = es[s + j] * up;
         }
         As[i][j] = a;
         Vs[i][j] = (i == j) ? 1.0 : 0.0;
@@ -185,10 +205,14 @@ __global__ __launch_bounds__(64) void dc_leaf(DcWs ws, int tl)
             const double apq = As[p][q];
             double c = 1.0, sn = 0.0;
             if (fabs(apq) > tol) {
-                const double tau = (As[q][q] - As[p][p]) / (2.0 * apq);
-                const double t = copysign(1.0, tau) / (fabs(tau) + sqrt(fma(tau, tau, 1.0)));
-                c = 1.0 / sqrt(fma(t, t, 1.0));
-                sn = t * c;
+                // |cot 2 theta| = |a| / |g|: c^2 = (1 + |a| / h) / 2 and
+                // c s = sign(a) g / (2 h), h = sqrt(a^2 + g^2)
+                const double a = As[q][q] - As[p][p], g = 2.0 * apq;
+                const double ih = rsqrt_nr(fma(a, a, g * g));
+                const double c2 = fma(0.5 * fabs(a), ih, 0.5);
+                const double ic = rsqrt_nr(c2);
+                c = c2 * ic;
+                sn = copysign(0.5, a) * g * ih * ic;
                 rotated = true;
             }
             // a round in which no pair rotates (all of the final sweep) leaves
@@ -226,7 +250,7 @@ __global__ __launch_bounds__(64) void dc_leaf(DcWs ws, int tl)
     }
     if (!conv && lane == 0 && ws.status) atomicOr(ws.status + b, ST_NOCONV);
     // ascending order: the rank of lane j's value (ties by index)
-    const double lam = lane < ns ? As[lane][lane] : 0.0;
+    const double lam = lane < ns ? As[lane][lane] * down : 0.0;
     int rank = 0;
     for (int k = 0; k < ns; ++k) {
         const double dk = rdl(lam, k);
@@ -234,29 +258,35 @@ __global__ __launch_bounds__(64) void dc_leaf(DcWs ws, int tl)
     }
     if (lane < ns) D[s + rank] = lam;
     double* Q = ws.Q[0] + b * ws.sQ;
+    const Seg pg = tl > 0 ? seg_of(blockIdx.x >> 1, n, tl - 1) : g;
     for (int j = 0; j < ns; ++j) {
         const int rj = __builtin_amdgcn_readlane(rank, j);
         if (lane < ns) Q[(int64_t)(s + lane) + (int64_t)(s + rj) * n] = Vs[lane][j];
+        const int64_t r = pg.s + lane;
+        if (r < pg.e && (r < g.s || r >= g.e)) Q[r + (int64_t)(s + j) * n] = 0.0;
     }
 }
 
-// Q = I for the leaves (buffer 0); grid (ceil(n*n/256), nk)
-__global__ __launch_bounds__(256) void dc_eye(DcWs ws)
-{
-    const int64_t b = blockIdx.y;
-    const int64_t nn = (int64_t)ws.n * ws.n;
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q >= nn) return;
-    const int64_t i = q % ws.n, j = q / ws.n;
-    ws.Q[0][b * ws.sQ + q] = (i == j) ? 1.0 : 0.0;
-}
-
 // ---------------------------------------------------------------------------
-// Deflation for one merge (one workgroup per segment and problem).
+// Deflation for one merge (one workgroup per segment and problem).  The lists
+// (sorted poles sd, components sz, columns perm, indices kidx) stay in LDS when
+// the segment fits: 24 bytes a row.
+//
+// Which candidates go: one with a negligible z_q alone, and of two neighbouring
+// others (pending p, then q) with |gap c s| <= tol, c = z_q / tau,
+// s = -z_p / tau, tau^2 = z_q^2 + z_p^2 (tested without the square root and the
+// divisions), the first, after a rotation that folds it into the second.
+// As long as no rotation has changed the pending candidate the test of a pair
+// reads that pair alone, so all pairs are tested at once, and one thread
+// follows only the chains that start where a test succeeds; the lists are
+// compacted by prefix counts in the order of a serial scan (the same results,
+// bit for bit).  One thread scanning all candidates took 0.17 us each: 25 us
+// at 128 rows, 64 us at 333, 333 us at 2000.
 __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int lds_cap)
 {
     __shared__ double sh[8];
-    extern __shared__ double dyn[];   // lds_cap doubles sd, lds_cap doubles sz, lds_cap ints perm
+    __shared__ int s_cnt[2][4], s_nrot;
+    extern __shared__ double dyn[];   // lds_cap doubles sd, lds_cap doubles sz, lds_cap ints perm, lds_cap ints kidx
     const int64_t b = blockIdx.y;
     const int64_t n = ws.n;
     const Seg g = seg_of(blockIdx.x, n, t);
@@ -267,12 +297,11 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
     double* Qr = ws.Q[rb] + b * ws.sQ;
     int* kc = ws.kcnt + b * n;
     int* ndc = ws.ndcnt + b * n;
-    // the serial deflation scan reads these at every step: keep them in LDS
-    // when the segment fits
-    const bool in_lds = (int)(g.e - g.s) <= lds_cap;
-    int* perm = in_lds ? reinterpret_cast<int*>(dyn + 2 * lds_cap) : ws.perm + b * n + s;
+    const bool in_lds = ns <= lds_cap;
     double* sd = in_lds ? dyn : ws.sd + b * n + s;
     double* sz = in_lds ? dyn + lds_cap : ws.sz + b * n + s;
+    int* perm = in_lds ? reinterpret_cast<int*>(dyn + 2 * lds_cap) : ws.perm + b * n + s;
+    int* kidx = in_lds ? reinterpret_cast<int*>(dyn + 2 * lds_cap) + lds_cap : ws.orgi + b * n + s;
     int* ndx = ws.ndx + b * n + s;
     double* ndd = ws.ndd + b * n + s;
     double* ndz = ws.ndz + b * n + s;
@@ -282,7 +311,11 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
     int* rotb = ws.rotb + b * n + s;
     double* rotc = ws.rotc + b * n + s;
     double* rots = ws.rots + b * n + s;
-    const int tid = threadIdx.x;
+    // scratch until the secular equation writes these
+    int* what = ws.cmap + b * n + s;      // 4 * column that goes here | 2: one goes here | 1: kept
+    double* goes = ws.lam + b * n + s;    // its value
+    int* starts = ws.ndx + b * n + s;     // pairs that rotate as they stand (kidx positions)
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 
     if (ns == 1) {
         if (tid == 0) {
@@ -301,26 +334,35 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
     const double sgn = (beta >= 0.0) ? 1.0 : -1.0;
     const double rs2 = 0.70710678118654752440;
 
-    // stable merge of the two sorted halves: perm[pos] = local column.  perm
-    // starts as the identity so it stays a valid index list even if the
-    // inputs hold NaNs (then positions may collide).
-    for (int c = tid; c < ns; c += 256) perm[c] = c;
+    // stable merge of the two sorted halves: perm[pos] = local column.  The
+    // poles are staged in sz for the binary searches.  perm starts as the
+    // identity so it stays a valid index list even if the inputs hold NaNs
+    // (then positions may collide).
+    for (int c = tid; c < ns; c += 256) {
+        perm[c] = c;
+        sz[c] = Dr[s + c];
+    }
+    __syncthreads();
+    for (int c = tid; c < ns; c += 256) {
+        const double dc = sz[c];
+        int pos;
+        if (c < n1) {
+            int lo = n1, hi = ns;      // count right-half entries strictly below dc
+            while (lo < hi) { int md = (lo + hi) >> 1; if (sz[md] < dc) lo = md + 1; else hi = md; }
+            pos = c + (lo - n1);
+        } else {
+            int lo = 0, hi = n1;       // count left-half entries <= dc
+            while (lo < hi) { int md = (lo + hi) >> 1; if (sz[md] <= dc) lo = md + 1; else hi = md; }
+            pos = (c - n1) + lo;
+        }
+        kidx[c] = min(max(pos, 0), ns - 1);
+    }
     __syncthreads();
     double dmx = 0.0, zmx = 0.0;
     for (int c = tid; c < ns; c += 256) {
         const double dc = Dr[s + c];
         const double zc = (c < n1) ? Qr[(g.mid - 1) + (s + c) * n] * rs2 : sgn * Qr[g.mid + (s + c) * n] * rs2;
-        int pos;
-        if (c < n1) {
-            int lo = n1, hi = ns;      // count right-half entries strictly below dc
-            while (lo < hi) { int md = (lo + hi) >> 1; if (Dr[s + md] < dc) lo = md + 1; else hi = md; }
-            pos = c + (lo - n1);
-        } else {
-            int lo = 0, hi = n1;       // count left-half entries <= dc
-            while (lo < hi) { int md = (lo + hi) >> 1; if (Dr[s + md] <= dc) lo = md + 1; else hi = md; }
-            pos = (c - n1) + lo;
-        }
-        pos = min(max(pos, 0), ns - 1);
+        const int pos = kidx[c];
         perm[pos] = c;
         sd[pos] = dc;
         sz[pos] = zc;
@@ -329,74 +371,117 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
     }
     dmx = dpp_wave_max(dmx);
     zmx = dpp_wave_max(zmx);
-    if ((tid & 63) == 0) { sh[tid >> 6] = dmx; sh[4 + (tid >> 6)] = zmx; }
+    if (lane == 0) { sh[wv] = dmx; sh[4 + wv] = zmx; }
     __syncthreads();
     dmx = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
     zmx = fmax(fmax(sh[4], sh[5]), fmax(sh[6], sh[7]));
     const double tol = 8.0 * EPS * fmax(dmx, zmx);
 
-    __shared__ int s_nrot;
-    if (tid == 0) {
-        int K = 0, nd = 0, nr = 0;
-        if (rho * zmx <= tol) {
-            for (int q = 0; q < ns; ++q) { dfx[nd] = perm[q]; dfd[nd] = sd[q]; ++nd; }
-        } else {
-            // the pending kept candidate (pole d_p, component z_p, column c_p)
-            // is carried in registers; a rotation folds it into the next one
-            bool have = false;
-            double zp = 0.0, dpv = 0.0;
-            int cp = 0;
-            // the candidates are read from LDS four at a time, ahead of the
-            // serial decisions that use them
-            constexpr int DQ = 4;
-            for (int q0 = 0; q0 < ns; q0 += DQ) {
-                double zq4[DQ], dq4[DQ];
-                int cq4[DQ];
-#pragma unroll
-                for (int u = 0; u < DQ; ++u) {
-                    const int q = q0 + u < ns ? q0 + u : q0;
-                    zq4[u] = sz[q];
-                    dq4[u] = sd[q];
-                    cq4[u] = perm[q];
-                }
-#pragma unroll
-                for (int u = 0; u < DQ; ++u) {
-                    if (q0 + u >= ns) break;
-                    const double zq = zq4[u], dq = dq4[u];
-                    const int cq = cq4[u];
-                    if (rho * fabs(zq) <= tol) {
-                        dfx[nd] = cq; dfd[nd] = dq; ++nd;
-                    } else if (!have) {
-                        have = true; zp = zq; dpv = dq; cp = cq;
-                    } else {
-                        // |gap c s| <= tol with c = z_q / tau, s = -z_p / tau,
-                        // tau^2 = z_q^2 + z_p^2, tested without the square
-                        // root and the divisions
-                        const double gap = dq - dpv;
-                        if (fabs(gap * zq * zp) <= tol * (zq * zq + zp * zp)) {
-                            const double tau = hypot(zq, zp);
-                            const double c = zq / tau, sn = -zp / tau;
-                            rota[nr] = cp; rotb[nr] = cq; rotc[nr] = c; rots[nr] = sn; ++nr;
-                            dfx[nd] = cp; dfd[nd] = dpv * c * c + dq * sn * sn; ++nd;
-                            zp = tau;
-                            dpv = dpv * sn * sn + dq * c * c;
-                            cp = cq;
-                        } else {
-                            ndx[K] = cp; ndd[K] = dpv; ndz[K] = zp; ++K;
-                            zp = zq; dpv = dq; cp = cq;
-                        }
-                    }
-                }
-            }
-            if (have) { ndx[K] = cp; ndd[K] = dpv; ndz[K] = zp; ++K; }
+    // this thread's place in the list of all flagged ones (thread order),
+    // which had `count` entries; two lists at a time
+    auto place2 = [&](bool f0, bool f1, int& count0, int& count1, int& at0, int& at1) {
+        const unsigned long long m0 = __builtin_amdgcn_ballot_w64(f0), m1 = __builtin_amdgcn_ballot_w64(f1);
+        if (lane == 0) {
+            s_cnt[0][wv] = __popcll(m0);
+            s_cnt[1][wv] = __popcll(m1);
         }
-        kc[s] = K;
-        ndc[s] = nd;
-        ws.nrot[b * n + s] = nr;
-        ws.rho[b * n + s] = rho;
-        s_nrot = nr;
+        __syncthreads();
+        const unsigned long long below = ((unsigned long long)1 << lane) - 1;
+        at0 = count0 + __popcll(m0 & below);
+        at1 = count1 + __popcll(m1 & below);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < wv) {
+                at0 += s_cnt[0][w];
+                at1 += s_cnt[1][w];
+            }
+            count0 += s_cnt[0][w];
+            count1 += s_cnt[1][w];
+        }
+        __syncthreads();
+    };
+    auto rotates = [&](double dp, double zp, double dq, double zq) {
+        return fabs((dq - dp) * zq * zp) <= tol * (zq * zq + zp * zp);
+    };
+    // the candidates with z not negligible (none if the whole update is)
+    const bool none = rho * zmx <= tol;
+    int K1 = 0, dummy = 0, at0, at1;
+    for (int q0 = 0; q0 < ns; q0 += 256) {
+        const int q = q0 + tid;
+        const bool keep = q < ns && !none && !(rho * fabs(sz[q < ns ? q : 0]) <= tol);
+        place2(keep, false, K1, dummy, at0, at1);
+        if (keep) kidx[at0] = q;
+        if (q < ns) {
+            what[q] = keep ? 1 : 4 * perm[q] + 2;
+            if (!keep) goes[q] = sd[q];
+        }
+    }
+    if (tid == 0) s_nrot = 0;
+    __syncthreads();
+    int nst = 0;
+    for (int r0 = 0; r0 + 1 < K1; r0 += 256) {
+        const int r = r0 + tid;
+        bool f = false;
+        if (r + 1 < K1) {
+            const int p = kidx[r], q = kidx[r + 1];
+            f = rotates(sd[p], sz[p], sd[q], sz[q]);
+        }
+        place2(f, false, nst, dummy, at0, at1);
+        if (f) starts[at0] = r;
     }
     __syncthreads();
+    if (nst > 0) {
+        if (tid == 0) {
+            int nr = 0, from = 0;
+            for (int u = 0; u < nst; ++u) {
+                int r = starts[u];
+                if (r < from) continue;          // part of the chain before
+                double dp = sd[kidx[r]], zp = sz[kidx[r]];
+                while (r + 1 < K1) {
+                    const int p = kidx[r], q = kidx[r + 1];
+                    const double dq = sd[q], zq = sz[q];
+                    if (!rotates(dp, zp, dq, zq)) break;
+                    const double tau = hypot(zq, zp);
+                    const double c = zq / tau, sn = -zp / tau;
+                    rota[nr] = perm[p]; rotb[nr] = perm[q]; rotc[nr] = c; rots[nr] = sn; ++nr;
+                    what[p] &= ~1;
+                    what[q] = 4 * perm[p] + 2 + 1;
+                    goes[q] = dp * c * c + dq * sn * sn;
+                    zp = tau;
+                    dp = dp * sn * sn + dq * c * c;
+                    ++r;
+                }
+                sd[kidx[r]] = dp;
+                sz[kidx[r]] = zp;
+                from = r + 1;
+            }
+            s_nrot = nr;
+        }
+        __syncthreads();
+    }
+    // the lists, in order of position
+    int K = 0, nd = 0;
+    for (int q0 = 0; q0 < ns; q0 += 256) {
+        const int q = q0 + tid;
+        const int f = q < ns ? what[q] : 0;
+        const bool keep = (f & 1) != 0, go = (f & 2) != 0;
+        place2(keep, go, K, nd, at0, at1);
+        if (keep) {
+            ndx[at0] = perm[q];
+            ndd[at0] = sd[q];
+            ndz[at0] = sz[q];
+        }
+        if (go) {
+            dfx[at1] = f >> 2;
+            dfd[at1] = goes[q];
+        }
+    }
+    if (tid == 0) {
+        kc[s] = K;
+        ndc[s] = nd;
+        ws.nrot[b * n + s] = s_nrot;
+        ws.rho[b * n + s] = rho;
+    }
     const int nr = s_nrot;
     // apply the deflation rotations, in order, to the columns of Q (rows s..e).
     // Consecutive rotations chain through their second column (the pending
@@ -427,50 +512,102 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
 // lanes (four roots per wave) gave the top merges enough waves to hide the
 // divide latency: 1.1% off the n = 2000 x 16 step against four lanes, with 32
 // lanes equal and 64 slower.
+//
+// A workgroup's sixteen roots share the poles and z^2 in LDS (segments of up
+// to SEC_CAP rows).  Small merges are bound by the slowest root's chain of
+// evaluations, so each root starts from the two-pole model through the midpoint
+// with its neighbours' own z^2, and the last root takes the two-pole model
+// too (its poles K-2 and K-1): at most 9 evaluations on the spectra of dense and
+// LCAO pencils where starting at the middle of the bracket and a one-pole
+// model for the last root took up to 28.
 constexpr int SEC_LANES = 16;
+constexpr int SEC_T = 256;
+constexpr int SEC_CAP = 4000;
 
 __device__ inline double root_sum(double v)
 {
     return dpp_sum<SEC_LANES>(v);
 }
 
-__device__ inline void secular_eval(int K, const double* dl, const double* zl, double rho, int j, double dorg,
-                                    double tau, int sub, double& f, double& psi, double& dpsi, double& phi,
-                                    double& dphi)
+struct SecularSums {
+    double f, psi, dpsi, phi, dphi;
+};
+
+// f and its two parts at tau (relative to the pole dorg): psi over q <= js,
+// phi over q > js
+__device__ inline SecularSums secular_eval(int K, const double* dl, const double* z2, double rho, int js, double dorg,
+                                           double tau, int sub)
 {
-    psi = 0.0; dpsi = 0.0; phi = 0.0; dphi = 0.0;
+    SecularSums v{0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
     for (int q = sub; q < K; q += SEC_LANES) {
         const double del = (dl[q] - dorg) - tau;
         const double r = 1.0 / del;
-        const double tq = zl[q] * zl[q] * r;
-        if (q <= j) { psi += tq; dpsi = fma(tq, r, dpsi); }
-        else { phi += tq; dphi = fma(tq, r, dphi); }
+        const double tq = z2[q] * r;
+        const bool left = q <= js;
+        v.psi += left ? tq : 0.0;
+        v.dpsi = left ? fma(tq, r, v.dpsi) : v.dpsi;
+        v.phi += left ? 0.0 : tq;
+        v.dphi = left ? v.dphi : fma(tq, r, v.dphi);
     }
-    psi = rho * root_sum(psi);
-    dpsi = rho * root_sum(dpsi);
-    phi = rho * root_sum(phi);
-    dphi = rho * root_sum(dphi);
-    f = 1.0 + psi + phi;
+    v.psi = rho * root_sum(v.psi);
+    v.dpsi = rho * root_sum(v.dpsi);
+    v.phi = rho * root_sum(v.phi);
+    v.dphi = rho * root_sum(v.dphi);
+    v.f = 1.0 + v.psi + v.phi;
+    return v;
 }
 
-__global__ __launch_bounds__(64) void dc_secular(DcWs ws, int t)
+// the root eta of c eta^2 - B eta + C = 0 with tau + eta inside (lo, hi), as
+// tau + eta; lo where there is none
+__device__ inline double model_root(double c, double B, double C, double tau, double lo, double hi)
 {
+    const double disc = B * B - 4.0 * c * C;
+    if (!(disc >= 0.0)) return lo;
+    const double sq = sqrt(disc);
+    const double den = B >= 0.0 ? B + sq : B - sq;
+    const double x1 = tau + 2.0 * C / den, x2 = tau + den / (2.0 * c);
+    if (x1 > lo && x1 < hi) return x1;
+    return x2 > lo && x2 < hi ? x2 : lo;
+}
+
+// z^2 of every kept pole, in zhat (which the next step overwrites), for the
+// segments that do not fit in LDS
+__global__ __launch_bounds__(256) void dc_square(DcWs ws)
+{
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q >= ws.n) return;
+    const double z = ws.ndz[blockIdx.y * (int64_t)ws.n + q];
+    ws.zhat[blockIdx.y * (int64_t)ws.n + q] = z * z;
+}
+
+__global__ __launch_bounds__(SEC_T) void dc_secular(DcWs ws, int t, int cap)
+{
+    extern __shared__ double dyn[];      // cap poles, cap z^2
     const int64_t b = blockIdx.z;
     const int64_t n = ws.n;
     const Seg g = seg_of(blockIdx.y, n, t);
     if (g.e - g.s < 2) return;
     const int64_t s = g.s;
     const int K = ws.kcnt[b * n + s];
-    const int gt = blockIdx.x * 64 + threadIdx.x;
+    if (blockIdx.x * (SEC_T / SEC_LANES) >= K) return;
+    const int gt = blockIdx.x * SEC_T + threadIdx.x;
     const int j = gt / SEC_LANES, sub = gt % SEC_LANES;
-    if (j >= K) return;          // the lanes of a root leave together
     const double* dl = ws.ndd + b * n + s;
     const double* zl = ws.ndz + b * n + s;
+    const double* z2 = ws.zhat + b * n + s;
     const double rho = ws.rho[b * n + s];
-
-    int org;
-    double lo, hi;
-    double f, psi, dpsi, phi, dphi;
+    if (K <= cap) {
+        for (int q = threadIdx.x; q < K; q += SEC_T) {
+            const double z = zl[q];
+            dyn[q] = dl[q];
+            dyn[cap + q] = z * z;
+        }
+        dl = dyn;
+        z2 = dyn + cap;
+    }
+    __syncthreads();
+    if (j >= K) return;          // the lanes of a root leave together
     if (K == 1) {
         // one pole: lambda = d + rho z^2 exactly
         const double tau1 = rho * zl[0] * zl[0];
@@ -481,66 +618,51 @@ __global__ __launch_bounds__(64) void dc_secular(DcWs ws, int t)
         }
         return;
     }
+    // the poles left and right of the model: j and j + 1, for the last root
+    // K - 2 and K - 1
+    const int js = j < K - 1 ? j : K - 2;
+    const double gap = dl[js + 1] - dl[js];
+    int org = j;
+    double lo, hi, at;
     if (j < K - 1) {
-        const double half = 0.5 * (dl[j + 1] - dl[j]);
-        secular_eval(K, dl, zl, rho, j, dl[j], half, sub, f, psi, dpsi, phi, dphi);
-        if (f >= 0.0) { org = j; lo = 0.0; hi = half; }
-        else { org = j + 1; lo = -half; hi = 0.0; }
+        at = 0.5 * gap;
     } else {
         double zz = 0.0;
-        for (int q = sub; q < K; q += SEC_LANES) zz = fma(zl[q], zl[q], zz);
-        zz = root_sum(zz);
-        org = j; lo = 0.0; hi = rho * zz;
-        for (int g2 = 0; g2 < 8; ++g2) {
-            secular_eval(K, dl, zl, rho, j, dl[org], hi, sub, f, psi, dpsi, phi, dphi);
-            if (f >= 0.0) break;
-            lo = hi; hi *= 2.0;
-        }
+        for (int q = sub; q < K; q += SEC_LANES) zz += z2[q];
+        hi = rho * root_sum(zz);
+        at = 0.5 * hi;
+    }
+    SecularSums v = secular_eval(K, dl, z2, rho, js, dl[j], at, sub);
+    // everything but the two poles' own terms, at the first point
+    const double s1o = rho * z2[js], s2o = rho * z2[js + 1];
+    const double rest = v.f - s1o / ((dl[js] - dl[j]) - at) - s2o / ((dl[js + 1] - dl[j]) - at);
+    double P1, P2;               // the two poles relative to the origin
+    if (j < K - 1) {
+        if (v.f >= 0.0) { lo = 0.0; hi = at; P1 = 0.0; P2 = gap; }
+        else { org = j + 1; lo = -at; hi = 0.0; P1 = -gap; P2 = 0.0; }
+    } else {
+        if (v.f >= 0.0) { lo = 0.0; hi = at; }
+        else { lo = at; hi *= 1.0 + 8.0 * EPS; }
+        P1 = -gap; P2 = 0.0;
     }
     const double dorg = dl[org];
-    const double P1 = dl[j] - dorg;
-    const double P2 = (j < K - 1) ? dl[j + 1] - dorg : 0.0;
-    double tau = 0.5 * (lo + hi);
+    double tau = model_root(rest, rest * (P1 + P2) + s1o + s2o, rest * P1 * P2 + s1o * P2 + s2o * P1, 0.0, lo, hi);
+    if (!(tau > lo && tau < hi)) tau = 0.5 * (lo + hi);
     bool conv = false;
     for (int it = 0; it < 400; ++it) {
-        secular_eval(K, dl, zl, rho, j, dorg, tau, sub, f, psi, dpsi, phi, dphi);
-        if (f == 0.0) { conv = true; break; }
-        if (f < 0.0) lo = tau; else hi = tau;
-        if (fabs(f) <= 8.0 * EPS * (1.0 + fabs(psi) + fabs(phi)) * (double)(K > 8 ? 8 : K)) { conv = true; break; }
+        v = secular_eval(K, dl, z2, rho, js, dorg, tau, sub);
+        if (v.f == 0.0) { conv = true; break; }
+        if (v.f < 0.0) lo = tau; else hi = tau;
+        if (fabs(v.f) <= 8.0 * EPS * (1.0 + fabs(v.psi) + fabs(v.phi)) * (double)(K > 8 ? 8 : K)) { conv = true; break; }
         if (hi - lo <= 4.0 * EPS * fmax(fabs(lo), fabs(hi))) { conv = true; break; }
         // two-pole rational model through (tau, f, f')
         double cand = 0.5 * (lo + hi);
-        const double d1 = P1 - tau;
         if ((it & 7) != 7) {
-            if (j < K - 1) {
-                const double d2 = P2 - tau;
-                const double s1 = dpsi * d1 * d1, s2 = dphi * d2 * d2;
-                const double c = 1.0 + (psi - dpsi * d1) + (phi - dphi * d2);
-                const double Bq = c * (d1 + d2) + s1 + s2;
-                const double Cq = d1 * d2 * f;
-                double eta;
-                bool okq = true;
-                if (c == 0.0) {
-                    eta = Cq / Bq;
-                } else {
-                    const double disc = Bq * Bq - 4.0 * c * Cq;
-                    if (disc < 0.0) okq = false;
-                    const double sq = sqrt(fmax(disc, 0.0));
-                    const double den = (Bq >= 0.0) ? (Bq + sq) : (Bq - sq);
-                    eta = (den != 0.0) ? 2.0 * Cq / den : 0.0;
-                    const double x2 = tau + eta;
-                    if (!(x2 > lo && x2 < hi)) eta = den / (2.0 * c);
-                }
-                const double x = tau + eta;
-                if (okq && x > lo && x < hi && isfinite(x)) cand = x;
-            } else {
-                const double s1 = dpsi * d1 * d1;
-                const double c = 1.0 + (psi - dpsi * d1) + phi;
-                if (c != 0.0) {
-                    const double x = tau + d1 + s1 / c;
-                    if (x > lo && x < hi && isfinite(x)) cand = x;
-                }
-            }
+            const double d1 = P1 - tau, d2 = P2 - tau;
+            const double s1 = v.dpsi * d1 * d1, s2 = v.dphi * d2 * d2;
+            const double c = 1.0 + (v.psi - v.dpsi * d1) + (v.phi - v.dphi * d2);
+            const double x = model_root(c, c * (d1 + d2) + s1 + s2, d1 * d2 * v.f, tau, lo, hi);
+            if (x > lo && x < hi) cand = x;
         }
         if (cand == tau) cand = 0.5 * (lo + hi);
         tau = cand;
@@ -552,19 +674,16 @@ __global__ __launch_bounds__(64) void dc_secular(DcWs ws, int t)
     if (!conv && ws.status) atomicOr(ws.status + b, ST_NOCONV);
 }
 
-// z recomputed from the roots (Loewner), one thread per pole.
-__global__ __launch_bounds__(64) void dc_zhat(DcWs ws, int t)
+// z recomputed from the roots (Loewner).
+__device__ inline void dc_zhat(const DcWs& ws, const Seg& g, int64_t b, int64_t n, int block)
 {
-    const int64_t b = blockIdx.z;
-    const int64_t n = ws.n;
-    const Seg g = seg_of(blockIdx.y, n, t);
     if (g.e - g.s < 2) return;
     const int64_t s = g.s;
     const int K = ws.kcnt[b * n + s];
     // SEC_LANES lanes per index i: lane `sub` multiplies the factors
     // q = sub mod SEC_LANES, a butterfly of products combines them (bitwise
     // equal in every lane of the group)
-    const int gt = blockIdx.x * 64 + threadIdx.x;
+    const int gt = block * 64 + threadIdx.x;
     const int i = gt / SEC_LANES, sub = gt % SEC_LANES;
     if (i >= K) return;          // the lanes of an index leave together
     const double* dl = ws.ndd + b * n + s;
@@ -584,15 +703,11 @@ __global__ __launch_bounds__(64) void dc_zhat(DcWs ws, int t)
 
 // Eigenvectors of D + rho z z^T: column j = zhat / (d - lambda_j), normalised.
 // One wave per column, the lanes over its rows (coalesced stores).
-__global__ __launch_bounds__(64) void dc_vectors(DcWs ws, int t)
+__device__ inline void dc_vectors(const DcWs& ws, const Seg& g, int64_t b, int64_t n, int j)
 {
-    const int64_t b = blockIdx.z;
-    const int64_t n = ws.n;
-    const Seg g = seg_of(blockIdx.y, n, t);
     if (g.e - g.s < 2) return;
     const int64_t s = g.s;
     const int K = ws.kcnt[b * n + s];
-    const int j = blockIdx.x;
     if (j >= K) return;
     const int lane = threadIdx.x;
     const double* dl = ws.ndd + b * n + s;
@@ -612,19 +727,16 @@ __global__ __launch_bounds__(64) void dc_vectors(DcWs ws, int t)
 }
 
 // Final ascending order of the merged eigenvalues (secular roots and deflated
-// poles): one thread per value counts the values that precede it.
-__global__ __launch_bounds__(64) void dc_order(DcWs ws, int t, int wb)
+// poles): each value counts the values that precede it.
+__device__ inline void dc_order(const DcWs& ws, const Seg& g, int64_t b, int64_t n, int block, int wb)
 {
-    const int64_t b = blockIdx.z;
-    const int64_t n = ws.n;
-    const Seg g = seg_of(blockIdx.y, n, t);
     const int ns = (int)(g.e - g.s);
     if (ns < 1) return;
     const int64_t s = g.s;
     const int K = ws.kcnt[b * n + s];
     const int nd = ws.ndcnt[b * n + s];
     // SEC_LANES lanes per value, each counting a strided share of the others
-    const int gt = blockIdx.x * 64 + threadIdx.x;
+    const int gt = block * 64 + threadIdx.x;
     const int q = gt / SEC_LANES, sub = gt % SEC_LANES;
     if (q >= K + nd) return;          // the lanes of a value leave together
     const double* lam = ws.lam + b * n + s;
@@ -645,20 +757,16 @@ __global__ __launch_bounds__(64) void dc_order(DcWs ws, int t, int wb)
 // Deflated columns move unchanged (after rotation) to their place, and every
 // column of the segment gets zeros in the rows of its parent segment that lie
 // outside it (the parent merge reads its whole diagonal block).
-__global__ __launch_bounds__(256) void dc_place(DcWs ws, int t, int rb, int wb)
+__device__ inline void dc_place(const DcWs& ws, const Seg& g, int64_t b, int64_t n, int q, int t, int rb, int wb)
 {
-    const int64_t b = blockIdx.z;
-    const int64_t n = ws.n;
-    const Seg g = seg_of(blockIdx.y, n, t);
     const int ns = (int)(g.e - g.s);
-    const int q = blockIdx.x;
     if (q >= ns) return;
     const int64_t s = g.s;
     double* Qw = ws.Q[wb] + b * ws.sQ;
     if (t > 0) {
         const Seg pg = seg_of(blockIdx.y >> 1, n, t - 1);
         double* col = Qw + (s + q) * n;
-        for (int64_t r = pg.s + threadIdx.x; r < pg.e; r += 256)
+        for (int64_t r = pg.s + threadIdx.x; r < pg.e; r += 64)
             if (r < g.s || r >= g.e) col[r] = 0.0;
     }
     const int K = ws.kcnt[b * n + s];
@@ -668,7 +776,25 @@ __global__ __launch_bounds__(256) void dc_place(DcWs ws, int t, int rb, int wb)
     const int dst = ws.cmap[b * n + s + K + q];
     const double* Qr = ws.Q[rb] + b * ws.sQ + (s + src) * n + s;
     double* Qd = Qw + (s + dst) * n + s;
-    for (int r = threadIdx.x; r < ns; r += 256) Qd[r] = Qr[r];
+    for (int r = threadIdx.x; r < ns; r += 64) Qd[r] = Qr[r];
+}
+
+// Two independent steps each in one launch (a launch of either costs 4.5 us at
+// least, whatever the size): the first nb workgroups of a row take the first,
+// the others the second.
+__global__ __launch_bounds__(64) void dc_zhat_order(DcWs ws, int t, int wb, int nb)
+{
+    const int64_t b = blockIdx.z, n = ws.n;
+    const Seg g = seg_of(blockIdx.y, n, t);
+    if ((int)blockIdx.x < nb) dc_zhat(ws, g, b, n, blockIdx.x);
+    else dc_order(ws, g, b, n, blockIdx.x - nb, wb);
+}
+__global__ __launch_bounds__(64) void dc_vectors_place(DcWs ws, int t, int rb, int wb, int nb)
+{
+    const int64_t b = blockIdx.z, n = ws.n;
+    const Seg g = seg_of(blockIdx.y, n, t);
+    if ((int)blockIdx.x < nb) dc_vectors(ws, g, b, n, blockIdx.x);
+    else dc_place(ws, g, b, n, blockIdx.x - nb, t, rb, wb);
 }
 
 // Q_new(s:e, s + cmap[j]) = sum_q Q(s:e, s + ndx[q]) V(q, j): real product on
@@ -797,21 +923,23 @@ hipError_t stedc(hipStream_t st, const DcWs& ws0, double* w, double* Z, double* 
     ws.Q[L & 1] = Z;
     ws.Q[(L & 1) ^ 1] = Qscratch;
     hipLaunchKernelGGL(dc_init, dim3((unsigned)nk), dim3(256), 0, st, ws, L);
-    hipLaunchKernelGGL(dc_eye, dim3((unsigned)((n * n + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws);
     hipLaunchKernelGGL(dc_leaf, dim3(1u << L, (unsigned)nk), dim3(64), 0, st, ws, L);
     for (int t = L - 1; t >= 0; --t) {
         const int rb = (L - t - 1) & 1, wb = (L - t) & 1;
         const unsigned segs = 1u << t;
         const int64_t nsmax = ((n + segs - 1) / segs) + 1;
-        const int cap = (int)std::min<int64_t>(nsmax, 3200);
-        const size_t dyn_bytes = (size_t)cap * (2 * sizeof(double) + sizeof(int));
+        const int cap = (int)std::min<int64_t>(nsmax, 2700);
+        const size_t dyn_bytes = (size_t)cap * (2 * sizeof(double) + 2 * sizeof(int));
         hipLaunchKernelGGL(dc_deflate, dim3(segs, (unsigned)nk), dim3(256), dyn_bytes, st, ws, t, rb, cap);
+        const int scap = (int)std::min<int64_t>(nsmax, SEC_CAP);
+        if (nsmax > SEC_CAP)
+            hipLaunchKernelGGL(dc_square, dim3((unsigned)((n + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws);
+        hipLaunchKernelGGL(dc_secular, dim3((unsigned)((nsmax * SEC_LANES + SEC_T - 1) / SEC_T), segs, (unsigned)nk),
+                           dim3(SEC_T), (size_t)scap * 2 * sizeof(double), st, ws, t, scap);
         const unsigned gxs = (unsigned)((nsmax * SEC_LANES + 63) / 64);
-        hipLaunchKernelGGL(dc_secular, dim3(gxs, segs, (unsigned)nk), dim3(64), 0, st, ws, t);
-        hipLaunchKernelGGL(dc_zhat, dim3(gxs, segs, (unsigned)nk), dim3(64), 0, st, ws, t);
-        hipLaunchKernelGGL(dc_vectors, dim3((unsigned)nsmax, segs, (unsigned)nk), dim3(64), 0, st, ws, t);
-        hipLaunchKernelGGL(dc_order, dim3(gxs, segs, (unsigned)nk), dim3(64), 0, st, ws, t, wb);
-        hipLaunchKernelGGL(dc_place, dim3((unsigned)nsmax, segs, (unsigned)nk), dim3(256), 0, st, ws, t, rb, wb);
+        hipLaunchKernelGGL(dc_zhat_order, dim3(2 * gxs, segs, (unsigned)nk), dim3(64), 0, st, ws, t, wb, (int)gxs);
+        hipLaunchKernelGGL(dc_vectors_place, dim3((unsigned)(2 * nsmax), segs, (unsigned)nk), dim3(64), 0, st, ws, t, rb,
+                           wb, (int)nsmax);
         const int tiles = (int)((nsmax + DB - 1) / DB);
         hipLaunchKernelGGL(dc_gemm, dim3((unsigned)(tiles * tiles), segs, (unsigned)nk), dim3(256), 0, st, ws, t, rb, wb,
                            tiles);

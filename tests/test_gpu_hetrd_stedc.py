@@ -271,3 +271,28 @@ def test_group_given_up_is_reduced_in_memory():
         spectrum_check(300, 5, 77)
     finally:
         lib.kgev_internal_group_wait(-1)
+
+
+# merges with chains of deflation rotations, long runs of negligible
+# components, tiny and graded blocks; the segment sizes about the deflation's
+# steps of 256 rows; tolerances as test_stedc_matches_oracle
+def merge_cases():
+    rng = np.random.default_rng(7)
+    out = []
+    for n in (15, 16, 17, 32, 255, 256, 257, 513):
+        out.append((f"edge{n}", rng.standard_normal(n), rng.standard_normal(n - 1)))
+    n = 200
+    out.append(("repeated", np.tile([1.0, 2.0, 2.0, 1.0], n // 4), np.where(np.arange(n - 1) % 4 == 3, 1e-9, 0.3)))
+    out.append(("nearly-diagonal", rng.standard_normal(n), 1e-13 * rng.standard_normal(n - 1)))
+    out.append(("graded", 10.0 ** -np.linspace(0, 40, n), 10.0 ** -np.linspace(0.5, 40.5, n - 1)))
+    d, e = rng.standard_normal(n), rng.standard_normal(n - 1)
+    d[100:120] *= 1e-180
+    e[99:120] *= 1e-180
+    out.append(("tiny-block", d, e))
+    out.append(("constant", np.full(300, 0.7), np.full(299, 0.25)))
+    return out
+
+
+@pytest.mark.parametrize("name,d,e", merge_cases(), ids=lambda x: x if isinstance(x, str) else "")
+def test_stedc_merges(name, d, e):
+    test_stedc_matches_oracle(name, d, e)
