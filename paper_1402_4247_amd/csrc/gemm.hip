@@ -11,6 +11,8 @@
 // im = (ar + ai)(br + bi) - ar br - ai bi, which saves a quarter of the MFMA
 // work at a normwise (not componentwise) error bound of the same order;
 // op(A) = A^H is folded into the global->LDS copy.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -150,6 +152,15 @@ __device__ inline void store_b(R (*sr)[BN + 1], R (*si)[BN + 1], int tid, const 
         sr[kk][c] = ok ? rb[q].x : (R)0;
         if constexpr (TB != 2) si[kk][c] = ok ? (TB ? -rb[q].y : rb[q].y) : (R)0;
     }
+}
+
+// alpha v, rounded the same way in every kernel
+template <typename C> __device__ inline C alpha_times(C alpha, C v)
+{
+    C z;
+    z.x = fma(alpha.x, v.x, -(alpha.y * v.y));
+    z.y = fma(alpha.x, v.y, alpha.y * v.x);
+    return z;
 }
 
 // BM x BN workgroup tile, four waves in a 2 x 2 arrangement, each owning a
@@ -299,11 +310,231 @@ __global__ __launch_bounds__(G_THREADS, 2) void cgemm_kernel(CGemmArgs<R> p)
                     } else {
                         v = mk<R>(accR[a][b][r], accI[a][b][r]);
                     }
-                    cx<R> out = cmul(p.alpha, v);
+                    cx<R> out = alpha_times(p.alpha, v);
                     if (rb0) out = cfma(p.beta, C[i + j * p.ldc], out);
                     C[i + j * p.ldc] = out;
                 }
             }
+}
+
+
+// ---------------------------------------------------------------------------
+// The same tile product for complex128 operands with the tiles loaded straight
+// from memory into LDS (global_load_lds, 16 bytes a lane: one element), the
+// product this library spends most of its time in.  Against the kernel above:
+// no staging registers, address arithmetic or masks per element (a pointer
+// advances by a constant per K step), so three waves fit a SIMD instead of
+// two, and NS - 1 steps of loads are in flight instead of one.
+//
+// A load writes 64 consecutive elements of LDS, lane by lane, so a tile's
+// layout is chosen through what each lane loads:
+//   rows contiguous in memory (A as it stands, B conjugate-transposed): element
+//     (k, r) at k * T + r; the 16 lanes of an operand read are contiguous.
+//   k contiguous (A conjugate-transposed, B as it stands): element (k, r) at
+//     r * GK + (k ^ swizzle(r)): the 16 rows of an operand read would share
+//     banks without the exclusive-or.
+// Rows and columns past the matrix are read at its last one (what they produce
+// is not stored); k past the inner dimension is read from a zero.  The order of
+// accumulation is that of the kernel above, for any T, GK, NS: the same bits.
+//
+// Bound by the FP64 MFMA rate (a 3M product's 6 m n k flops at 78.6 TF are 104.8
+// TF of algorithmic 8 m n k): 2000^3 x 16 67.7 -> 87.9 TF, X^H G (lower) 66.6 ->
+// 81.8, 1024^3 x 64 70.3 -> 91.7, 4096^3 x 2 71.2 -> 92.6, the rank-64 update of
+// 1936 rows x 16 (bound by reading and writing C) 322 -> 271 us.  K steps of 16
+// in two stages (two workgroups per CU) gave 60.0 TF on the first of these, of 4
+// in four stages 85.1, in six 82.2.  For 32 x 32 tiles every depth tried gave
+// the same times (128^3: one product 10.1 -> 8 us): K steps of 16 in four stages.
+template <int T, int GK> struct DmaTile {
+    static constexpr int ELEMS = T * GK;
+    static constexpr int LOADS = ELEMS / G_THREADS;        // per thread and K step
+    static_assert(ELEMS % G_THREADS == 0, "whole loads");
+    static __device__ __attribute__((always_inline)) inline int swizzle(int r)
+    {
+        // 16 elements are all the banks: GK rows apart by 16 / GK rows
+        return GK >= 16 ? (r & 15) : ((r >> 1) & 7);
+    }
+    // (k, r) of element e of a tile
+    template <bool KC> static __device__ __attribute__((always_inline)) inline void at(int e, int& k, int& r)
+    {
+        if constexpr (KC) {
+            r = e / GK;
+            k = (e % GK) ^ swizzle(r);
+        } else {
+            r = e % T;
+            k = e / T;
+        }
+    }
+    template <bool KC> static __device__ __attribute__((always_inline)) inline int index(int k, int r)
+    {
+        return KC ? r * GK + (k ^ swizzle(r)) : k * T + r;
+    }
+};
+
+// 64 lanes x 16 bytes from each lane's address to LDS at lds + 16 * lane
+// (written as assembly because the compiler would wait for all of them before
+// any LDS read; no register receives anything; m0 is not allocated and set
+// anew by whatever uses it)
+__device__ __attribute__((always_inline)) inline void load_to_lds(uint32_t lds, const double2* p)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(p) : "memory");
+}
+__device__ __attribute__((always_inline)) inline uint32_t lds_address(const void* p)
+{
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
+__device__ const double2 dma_zero = {0.0, 0.0};
+
+template <int T, int GK, int NS, int TA, int TB>
+__global__ __launch_bounds__(G_THREADS, T == 64 ? 3 : 2) void zgemm_dma(CGemmArgs<double> p)
+{
+    using M = Mfma<double>;
+    using Tile = DmaTile<T, GK>;
+    constexpr bool KCA = TA == 1, KCB = TB == 0;   // k contiguous in memory
+    constexpr int TM = T / 32;                     // MFMA tiles per wave in each direction
+    constexpr int NL = Tile::LOADS;
+    __shared__ double2 sA[NS][Tile::ELEMS], sB[NS][Tile::ELEMS];
+
+    const int64_t total = (p.tri ? (int64_t)p.tiles_m * (p.tiles_m + 1) / 2 : (int64_t)p.tiles_m * p.tiles_n) * p.batch;
+    int64_t bz;
+    int tm, tn;
+    tile_of(blockIdx.x, total, p.tiles_m, p.tiles_n, p.remap, p.tri, bz, tm, tn);
+    const int64_t bo = bz / p.batch2, bi = bz - bo * p.batch2;
+    const int64_t m = p.m, n = p.n;
+    const int K = (int)p.k;
+    const int64_t i0 = (int64_t)tm * T, j0 = (int64_t)tn * T;
+    if (p.lower && i0 + T <= j0) return;   // tile entirely above the diagonal
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = w & 1, wn = w >> 1;
+    const int li = lane & 15, lk = lane >> 4;
+
+    d4_t accR[TM][TM], accI[TM][TM], accT[TM][TM];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) accR[a][b][r] = accI[a][b][r] = accT[a][b][r] = 0;
+
+    // this thread's elements: load q of a step is element (w * NL + q) * 64 + lane
+    const double2 *pa[NL], *pb[NL];
+    int64_t da = 0, db = 0;                // the pointers' advance per K step
+    auto start = [&](int sg) {
+        const double2* A = p.A[sg] + bo * p.sA[sg] + bi * p.sA2[sg];
+        const double2* B = p.B[sg] + bo * p.sB[sg] + bi * p.sB2[sg];
+        const int64_t lda = p.lda[sg], ldb = p.ldb[sg];
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            int k, r;
+            Tile::template at<KCA>((w * NL + q) * 64 + lane, k, r);
+            const int64_t gi = i0 + r < m ? i0 + r : m - 1;
+            pa[q] = A + (KCA ? k + gi * lda : gi + k * lda);
+            Tile::template at<KCB>((w * NL + q) * 64 + lane, k, r);
+            const int64_t gj = j0 + r < n ? j0 + r : n - 1;
+            pb[q] = B + (KCB ? k + gj * ldb : gj + k * ldb);
+        }
+        da = KCA ? GK : GK * lda;
+        db = KCB ? GK : GK * ldb;
+    };
+    const int nkt = (K + GK - 1) / GK, total_k = nkt * p.nseg;
+    int lstep = 0, lkt = 0, lstage = 0;    // the next step to load: global, within its term, its stage
+    auto load_step = [&]() {
+        if (lkt == 0) start(lstep == 0 ? 0 : 1);
+        const uint32_t la = lds_address(&sA[lstage][w * NL * 64]), lb = lds_address(&sB[lstage][w * NL * 64]);
+        if ((lkt + 1) * GK <= K) {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) {
+                load_to_lds(la + q * 1024, pa[q]);
+                load_to_lds(lb + q * 1024, pb[q]);
+                pa[q] += da;
+                pb[q] += db;
+            }
+        } else {
+            // the last, partial step of a term (every lane loads, so that the
+            // count of outstanding loads is the same)
+#pragma unroll
+            for (int q = 0; q < NL; ++q) {
+                const int e = (w * NL + q) * 64 + lane;
+                int ka, kb, r;
+                Tile::template at<KCA>(e, ka, r);
+                Tile::template at<KCB>(e, kb, r);
+                load_to_lds(la + q * 1024, lkt * GK + ka < K ? pa[q] : &dma_zero);
+                load_to_lds(lb + q * 1024, lkt * GK + kb < K ? pb[q] : &dma_zero);
+            }
+        }
+        ++lstep;
+        lkt = lkt + 1 == nkt ? 0 : lkt + 1;
+        lstage = lstage + 1 == NS ? 0 : lstage + 1;
+    };
+    for (int q = 0; q < NS - 1 && q < total_k; ++q) load_step();
+    int stage = 0;
+    for (int it = 0; it < total_k; ++it) {
+        // this wave's loads of step `it` have arrived once only those of the
+        // steps after it are outstanding; after the barrier everybody's have,
+        // and everybody is done with the stage that is loaded next
+        if (it + NS - 1 <= total_k)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * 2 * NL) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (lstep < total_k) load_step();
+        const double2* cA = sA[stage];
+        const double2* cB = sB[stage];
+#pragma unroll
+        for (int ks = 0; ks < GK; ks += 4) {
+            double ar[TM], ai[TM], br[TM], bi_[TM], bs[TM];
+#pragma unroll
+            for (int t = 0; t < TM; ++t) {
+                const double2 av = cA[Tile::template index<KCA>(ks + lk, wm * (T / 2) + t * 16 + li)];
+                const double2 bv = cB[Tile::template index<KCB>(ks + lk, wn * (T / 2) + t * 16 + li)];
+                ar[t] = av.x;
+                ai[t] = TA ? -av.y : av.y;
+                br[t] = bv.x;
+                bi_[t] = TB ? -bv.y : bv.y;
+                bs[t] = br[t] + bi_[t];
+            }
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                const double as = ar[a] + ai[a];
+#pragma unroll
+                for (int b = 0; b < TM; ++b) {
+                    accR[a][b] = M::mma(ar[a], br[b], accR[a][b]);
+                    accI[a][b] = M::mma(as, bs[b], accI[a][b]);
+                    accT[a][b] = M::mma(ai[a], bi_[b], accT[a][b]);
+                }
+            }
+        }
+        stage = stage + 1 == NS ? 0 : stage + 1;
+    }
+
+    double2* C = p.C + bo * p.sC + bi * p.sC2;
+    const bool rb0 = (p.beta.x != 0 || p.beta.y != 0);
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t i = i0 + wm * (T / 2) + a * 16 + M::row(lk, r);
+                const int64_t j = j0 + wn * (T / 2) + b * 16 + li;
+                if (i < m && j < n && (!p.lower || i >= j)) {
+                    const double pr = accR[a][b][r], qi = accT[a][b][r];
+                    double2 out = alpha_times(p.alpha, mk<double>(pr - qi, accI[a][b][r] - pr - qi));
+                    if (rb0) out = cfma(p.beta, C[i + j * p.ldc], out);
+                    C[i + j * p.ldc] = out;
+                }
+            }
+}
+
+// Operands the 16-byte loads to LDS may read: elements on 16-byte boundaries
+// (any device allocation; a caller may still pass an 8-byte aligned address)
+// and an inner dimension to load.
+template <typename R> bool dma_operands(const CGemmArgs<R>& p)
+{
+    for (int s = 0; s < p.nseg; ++s)
+        if (reinterpret_cast<uintptr_t>(p.A[s]) % 16 != 0 || reinterpret_cast<uintptr_t>(p.B[s]) % 16 != 0) return false;
+    return p.k >= 1 && p.k < (1 << 30);
 }
 
 template <typename R, int BM, int BN, bool G3, int TA, int TB>
@@ -313,6 +544,15 @@ hipError_t launch_tiles(CGemmArgs<R> p, hipStream_t st, const ProfLaunch& pl)
     p.tiles_n = (int)((p.n + BN - 1) / BN);
     p.tri = (p.lower && BM == BN && p.tiles_m == p.tiles_n) ? 1 : 0;
     const int64_t total = (p.tri ? (int64_t)p.tiles_m * (p.tiles_m + 1) / 2 : (int64_t)p.tiles_m * p.tiles_n) * p.batch;
+    if constexpr (std::is_same_v<R, double> && TB != 2) {
+        if (dma_operands(p)) {
+            if constexpr (BM == 64)
+                launch_timed(pl, zgemm_dma<64, 8, 3, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
+            else
+                launch_timed(pl, zgemm_dma<32, 16, 4, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
+            return hipGetLastError();
+        }
+    }
     launch_timed(pl, cgemm_kernel<R, BM, BN, G3, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
     return hipGetLastError();
 }

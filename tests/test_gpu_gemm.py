@@ -71,3 +71,45 @@ def test_zgemm_beta_zero_ignores_nan_in_c():
         check(kg.zgemm_device(ctx, "N", "N", 20, 20, 20, 1.0, dA, 20, 0, dA, 20, 0, 0.0, dC, 20, 0, 1))
         torch.cuda.synchronize()
     assert np.allclose(dC.cpu().numpy().T, A @ A, atol=1e-12)
+
+
+# the loads straight to LDS at the edges of their steps (8 and 16 of the inner
+# dimension) and tiles, with 32 x 32 tiles (one product) and 64 x 64 tiles (a
+# batch that fills the chip); operands on 8-byte boundaries only take the
+# kernel without those loads and give the same bits
+@pytest.mark.parametrize("ta", ["N", "C"])
+@pytest.mark.parametrize("tb", ["N", "C"])
+@pytest.mark.parametrize("m,n,k,batch", [(1, 1, 1, 1), (33, 31, 7, 1), (64, 65, 8, 1), (40, 70, 17, 2), (65, 64, 9, 130),
+                                         (31, 63, 16, 260), (70, 5, 25, 130), (64, 64, 33, 256)])
+def test_zgemm_loads_to_lds(ta, tb, m, n, k, batch):
+    kg = K()
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m + 10 * n + 100 * k)
+
+    def ops(shift):
+        """Column-major operands, `shift` doubles off a 16-byte boundary."""
+        out = []
+        for x in (a, b, c):
+            buf = torch.empty(x.numel() * 2 + 2, dtype=torch.float64, device=DEV)
+            buf[shift:shift + x.numel() * 2] = torch.view_as_real(x).reshape(-1)
+            out.append(buf[shift:])
+        return out
+
+    a = torch.randn((batch, k, m) if ta == "N" else (batch, m, k), dtype=torch.complex128, device=DEV, generator=g)
+    b = torch.randn((batch, n, k) if tb == "N" else (batch, k, n), dtype=torch.complex128, device=DEV, generator=g)
+    c = torch.randn((batch, n, m), dtype=torch.complex128, device=DEV, generator=g)
+    got = []
+    with kg.Context(0) as ctx:
+        for shift in (0, 1):
+            da, db, dc = ops(shift)
+            check(kg.zgemm_device(ctx, ta, tb, m, n, k, 0.75 - 0.5j, da, a.shape[-1], m * k, db, b.shape[-1], n * k,
+                                  0.25 + 1.0j, dc, m, m * n, batch), "zgemm")
+            torch.cuda.synchronize()
+            got.append(torch.view_as_complex(dc[:2 * c.numel()].clone().reshape(batch, n, m, 2)))
+    assert torch.equal(torch.view_as_real(got[0]), torch.view_as_real(got[1]))
+    A, B, C = (x.cpu().numpy().swapaxes(-1, -2) for x in (a, b, c))
+    A = A if ta == "N" else A.conj().swapaxes(-1, -2)
+    B = B if tb == "N" else B.conj().swapaxes(-1, -2)
+    ref = (0.75 - 0.5j) * (A @ B) + (0.25 + 1.0j) * C
+    bound = 8 * k * EPS * (abs(0.75 - 0.5j) * (np.abs(A) @ np.abs(B)) + abs(0.25 + 1.0j) * np.abs(C))
+    assert np.all(np.abs(got[0].cpu().numpy().swapaxes(-1, -2) - ref) <= 2 * bound)
