@@ -1,9 +1,9 @@
 // Part 2 in Cholesky form (an option beside the paper's diagonalisation of S):
 // S = L L^H, X = L^{-H} J, which satisfies X^H S X = I, so Parts 3 and 4 run
 // unchanged with this X.  Blocked in 64-column steps, batched over k-points:
-//   diagonal block : one workgroup per k factors it in LDS (right-looking,
+//   diagonal block : one workgroup per k factors it in registers (right-looking,
 //                    pivots checked against s_tol * max_i S_ii) and inverts
-//                    the factor (forward substitution);
+//                    the factor (forward substitution) in the same steps;
 //   panel          : L21 = A21 L11^{-H}                 (MFMA product)
 //   trailing       : A22 -= L21 L21^H, lower half        (MFMA product)
 // then L^{-1} block row by block row,
@@ -19,6 +19,7 @@
 // unreversed form missed the first-order bound of a backward-stable solve by
 // 11x in the oracle's own Householder reduction; reversed it is within 1%.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "lanes.hpp"
@@ -46,74 +47,116 @@ __global__ __launch_bounds__(256) void k_smax(int64_t n, const double2* A, int64
 // factor into L (lower, ld n), its inverse into Linv (ld n) and into D
 // (ld CB, one CB x CB block per k).  A failing pivot sets ST_NOTPD and is
 // replaced by 1 so that the rest stays finite.
+//
+// Both triangles are in registers: thread (tr, tc) of a 16 x 16 arrangement
+// holds rows tr + 16 i and columns tc + 16 j of the block and of the right-hand
+// side I of L V = I.  Step c takes one barrier: the owners put column c of
+// the block and row c of the right-hand side into LDS (two buffers by the
+// parity of c), every thread forms the pivot's 1 / sqrt and applies both
+// rank-one updates,
+//   a(r, q) -= l(r, c) conj(l(q, c)),   rhs(r, q) -= l(r, c) v(c, q),
+// to the 16-blocks that still change (known at compile time within 16 steps).
+// Bound by the latency of a step, 0.67 us.  43 us a block of 64, against 114 us
+// for factoring and then inverting in LDS with four barriers a column.
+constexpr int CT = CB / 16;      // 16-blocks per dimension
+
 __global__ __launch_bounds__(256) void k_chol_diag(int n, int j0, const double2* A, int64_t lda, int64_t sA,
                                                    double2* L, double2* Linv, int64_t sN, double2* D, int64_t sD,
                                                    const double* smax, double s_tol, int* status)
 {
-    __shared__ double2 a[CB][CB + 1];   // a[col][row]
-    __shared__ double2 v[CB][CB + 1];   // inverse, v[col][row]
-    __shared__ int bad;
+    __shared__ double2 col[2][CB], row[2][CB];
     const int64_t b = blockIdx.x;
     const int bs = n - j0 < CB ? n - j0 : CB;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, tr = tid & 15, tc = tid >> 4;
     const double2* Ab = A + b * sA + (int64_t)j0 + (int64_t)j0 * lda;
-    for (int e = tid; e < CB * CB; e += 256) {
-        const int r = e % CB, c = e / CB;
-        double2 x = mk<double>(0, 0);
-        if (r < bs && c <= r) x = Ab[r + (int64_t)c * lda];
-        a[c][r] = x;
-        v[c][r] = mk<double>(0, 0);
-    }
-    if (tid == 0) bad = 0;
     const double thr = s_tol * smax[b];
-    __syncthreads();
-    for (int c = 0; c < bs; ++c) {
-        if (tid == 0) {
-            double d = a[c][c].x;
+    const double2 zero = mk<double>(0, 0);
+    double2 a[CT][CT], v[CT][CT];
+#pragma unroll
+    for (int i = 0; i < CT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int r = tr + 16 * i, q = tc + 16 * j;
+            const bool in = r < bs && q <= r;
+            a[i][j] = csel(in, Ab[in ? r + (int64_t)q * lda : 0], zero);
+            v[i][j] = mk<double>(r == q && r < bs ? 1.0 : 0.0, 0.0);
+        }
+    bool bad = false;
+    int c = 0;
+    auto steps = [&](auto k1c) __attribute__((always_inline)) {
+        constexpr int k1 = decltype(k1c)::value;     // the 16-block of column c
+#pragma unroll 1
+        for (; c < bs && c < 16 * (k1 + 1); ++c) {
+            double2* cb = col[c & 1];
+            double2* rb = row[c & 1];
+            if (tc == (c & 15)) {
+#pragma unroll
+                for (int i = k1; i < CT; ++i) cb[tr + 16 * i] = a[i][k1];
+            }
+            if (tr == (c & 15)) {
+#pragma unroll
+                for (int j = 0; j <= k1; ++j) rb[tc + 16 * j] = v[k1][j];
+            }
+            __syncthreads();
+            double d = cb[c].x;
             if (!(d > thr)) {
-                bad = 1;
+                bad = true;
                 d = 1.0;
             }
-            a[c][c] = mk<double>(sqrt(d), 0.0);
+            const double root = sqrt(d), inv = 1.0 / root;
+            double2 lr[CT], lq[CT], vq[CT];
+#pragma unroll
+            for (int i = k1; i < CT; ++i) {
+                lr[i] = cscale(cb[tr + 16 * i], inv);
+                lq[i] = cscale(cb[tc + 16 * i], inv);
+                // finished rows and columns, and what is above the diagonal,
+                // are left alone by the updates below
+                if (tr + 16 * i <= c) lr[i] = zero;
+                if (tc + 16 * i <= c) lq[i] = zero;
+            }
+#pragma unroll
+            for (int j = 0; j <= k1; ++j) vq[j] = cscale(rb[tc + 16 * j], inv);
+            if (tc == (c & 15)) {
+                // the finished column of L
+#pragma unroll
+                for (int i = k1; i < CT; ++i) {
+                    const int r = tr + 16 * i;
+                    if (r >= c) a[i][k1] = r == c ? mk<double>(root, 0.0) : lr[i];
+                }
+            }
+            if (tr == (c & 15)) {
+#pragma unroll
+                for (int j = 0; j <= k1; ++j) v[k1][j] = vq[j];
+            }
+#pragma unroll
+            for (int i = k1; i < CT; ++i) {
+#pragma unroll
+                for (int j = k1; j <= i; ++j) a[i][j] = csub(a[i][j], cmulc(lq[j], lr[i]));
+#pragma unroll
+                for (int j = 0; j <= k1; ++j) v[i][j] = csub(v[i][j], cmul(lr[i], vq[j]));
+            }
         }
-        __syncthreads();
-        const double inv = 1.0 / a[c][c].x;
-        for (int r = c + 1 + tid; r < bs; r += 256) a[c][r] = cscale(a[c][r], inv);
-        __syncthreads();
-        // trailing lower part: a[c2][r] -= a[c][r] conj(a[c][c2]), c < c2 <= r
-        const int t = bs - c - 1;
-        for (int e = tid; e < t * t; e += 256) {
-            const int r = c + 1 + e % t, c2 = c + 1 + e / t;
-            if (c2 <= r) a[c2][r] = csub(a[c2][r], cmulc(a[c][c2], a[c][r]));
-        }
-        __syncthreads();
-    }
-    // inverse by rows: v(r, cc) = (delta - sum_{k=cc}^{r-1} L(r, k) v(k, cc)) / L(r, r),
-    // the four threads of a column splitting the sum
-    const int cc = tid >> 2, part = tid & 3;
-    for (int r = 0; r < bs; ++r) {
-        double2 s = mk<double>(0, 0);
-        if (cc <= r && cc < bs)
-            for (int k = cc + part; k < r; k += 4) s = cfma(a[k][r], v[cc][k], s);
-        s.x = dpp_sum<4>(s.x);
-        s.y = dpp_sum<4>(s.y);
-        if (part == 0 && cc <= r && cc < bs) {
-            const double2 dl = mk<double>(r == cc ? 1.0 : 0.0, 0.0);
-            v[cc][r] = cscale(csub(dl, s), 1.0 / a[r][r].x);
-        }
-        __syncthreads();
-    }
+    };
+    steps(std::integral_constant<int, 0>{});
+    steps(std::integral_constant<int, 1>{});
+    steps(std::integral_constant<int, 2>{});
+    steps(std::integral_constant<int, 3>{});
+    static_assert(CT == 4, "one call per 16-block");
     double2* Lb = L + b * sN + (int64_t)j0 + (int64_t)j0 * n;
     double2* Vb = Linv + b * sN + (int64_t)j0 + (int64_t)j0 * n;
     double2* Db = D + b * sD;
-    for (int e = tid; e < CB * CB; e += 256) {
-        const int r = e % CB, c = e / CB;
-        if (r < bs && c < bs) {
-            Lb[r + (int64_t)c * n] = a[c][r];
-            Vb[r + (int64_t)c * n] = v[c][r];
+#pragma unroll
+    for (int i = 0; i < CT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int r = tr + 16 * i, q = tc + 16 * j;
+            const bool in = r < bs && q <= r;
+            if (r < bs && q < bs) {
+                Lb[r + (int64_t)q * n] = csel(in, a[i][j], zero);
+                Vb[r + (int64_t)q * n] = csel(in, v[i][j], zero);
+            }
+            Db[r + (int64_t)q * CB] = csel(in, v[i][j], zero);
         }
-        Db[r + (int64_t)c * CB] = v[c][r];
-    }
     if (tid == 0 && bad) atomicOr(status + b, ST_NOTPD);
 }
 

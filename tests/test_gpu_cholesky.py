@@ -97,3 +97,9 @@ def test_cholesky_x_matches_oracle_factor(n):
         Xo = Li.conj().T[:, ::-1]
         bound = 8 * n * np.finfo(np.float64).eps * (np.abs(Li) @ np.abs(L) @ np.abs(Li)).conj().T[:, ::-1]
         assert np.all(np.abs(X[k] - Xo) <= bound + 1e-300)
+
+
+# the diagonal block at the edges of its 16-blocks, alone and as the last one
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 48, 64, 79, 97, 112])
+def test_cholesky_block_edges(n):
+    test_cholesky_x_matches_oracle_factor(n)
