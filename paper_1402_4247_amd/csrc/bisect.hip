@@ -9,10 +9,10 @@
 // a pivot of magnitude below pivmin being replaced by -pivmin (so no division
 // by zero; the count stays that of a matrix within rounding of T).  T is first
 // scaled to max |entry| = 1, and every eigenvalue starts from the Gershgorin
-// interval of the scaled T.  Four lanes share eigenvalue j: each round they
-// count at the three quarter points of its interval [lo, hi] (count(lo) <= j <
-// count(hi)) and keep the quarter that still brackets it, so the interval
-// shrinks four-fold per round, until it holds no representable midpoint
+// interval of the scaled T.  LANES lanes share eigenvalue j: each round they
+// count at LANES equally spaced points inside its interval [lo, hi] (count(lo)
+// <= j < count(hi)) and keep the part that still brackets it, so the interval
+// shrinks LANES + 1 fold per round, until it holds no representable midpoint
 // besides its ends, is within 2 eps of its magnitude, or is narrower than
 // 2 eps in the scaled units (the absolute accuracy of any backward-stable
 // solve, eps ||T||, which is all there is near zero); an eigenvalue that ends
@@ -28,8 +28,8 @@ namespace {
 
 constexpr double EPS = 2.220446049250313e-16;
 constexpr double SAFMIN = 2.2250738585072014e-308;
-constexpr int LANES = 4;        // lanes per eigenvalue
-constexpr int MAX_ROUNDS = 40;  // 4^40 = 2^80 > the 2^64 steps between any two doubles
+constexpr int MAX_ROUNDS = 40;  // 5^40 = 2^92 > the 2^64 steps between any two doubles
+constexpr int LDS_ROWS = 4096;  // rows of T staged in LDS (16 bytes each)
 
 // per problem: scale, Gershgorin interval of the scaled T, pivmin
 struct BzPrep {
@@ -92,13 +92,24 @@ __global__ __launch_bounds__(256) void stebz_prep(const double* __restrict__ d, 
     }
 }
 
-// number of eigenvalues of the scaled T below x
-__device__ inline int sturm_count(const double* __restrict__ d, const double* __restrict__ e, int n, double inv,
-                                  double x, double pivmin)
+// number of eigenvalues of the scaled T below x; t holds {d_i, e_{i-1}^2}, or
+// (t null) they are formed from d, e
+__device__ inline int sturm_count(const double2* t, const double* __restrict__ d, const double* __restrict__ e, int n,
+                                  double inv, double x, double pivmin)
 {
     double q = d[0] * inv - x;
     if (fabs(q) < pivmin) q = -pivmin;
     int c = q < 0.0 ? 1 : 0;
+    if (t) {
+#pragma unroll 4
+        for (int i = 1; i < n; ++i) {
+            const double2 v = t[i];
+            q = (v.x - x) - v.y / q;
+            if (fabs(q) < pivmin) q = -pivmin;
+            c += q < 0.0 ? 1 : 0;
+        }
+        return c;
+    }
     for (int i = 1; i < n; ++i) {
         const double ei = e[i - 1] * inv;
         q = (d[i] * inv - x) - ei * ei / q;
@@ -108,12 +119,32 @@ __device__ inline int sturm_count(const double* __restrict__ d, const double* __
     return c;
 }
 
-// grid (ceil(n * LANES / 256), nk): lanes 4j..4j+3 of the grid row own
-// eigenvalue j of problem blockIdx.y
+// the largest (smallest) value of an aligned group of LANES lanes, in all of them
+template <int LANES> __device__ inline double group_max(double v)
+{
+    v = fmax(v, lane_xor<1>(v));
+    v = fmax(v, lane_xor<2>(v));
+    if constexpr (LANES >= 8) v = fmax(v, lane_xor<4>(v));
+    if constexpr (LANES >= 16) v = fmax(v, lane_xor<8>(v));
+    if constexpr (LANES >= 64) {
+        v = fmax(v, lane_xor<16>(v));
+        v = fmax(v, lane_xor<32>(v));
+    }
+    return v;
+}
+
+// grid (ceil(n * LANES / 256), nk): lanes LANES * j .. of the grid row own
+// eigenvalue j of problem blockIdx.y.  A round is a chain of n divisions, so
+// its time is their latency as long as few waves share a SIMD.  Three of four
+// lanes counting at the quarter points, T read from memory at every step: n =
+// 128 346 us, 616 x 8 2.1 ms, 1040 x 16 4.2 ms, 2000 x 16 8.4 ms; now 87 us, 0.71,
+// 2.4 and 4.7 ms.
+template <int LANES>
 __global__ __launch_bounds__(256) void stebz_bisect(const double* __restrict__ d, const double* __restrict__ e,
                                                     int64_t sde, int n, const BzPrep* __restrict__ prep,
-                                                    double* __restrict__ w, int64_t sw)
+                                                    double* __restrict__ w, int64_t sw, int staged)
 {
+    extern __shared__ double2 rows[];
     const int64_t b = blockIdx.y;
     const int t = blockIdx.x * 256 + threadIdx.x;
     const int j = t / LANES, q = t % LANES;
@@ -123,6 +154,13 @@ __global__ __launch_bounds__(256) void stebz_bisect(const double* __restrict__ d
     const double* eb = e + b * sde;
     const BzPrep p = prep[b];
     const double inv = 1.0 / p.scale;
+    if (staged) {
+        for (int i = threadIdx.x; i < n; i += 256) {
+            const double ei = i > 0 ? eb[i - 1] * inv : 0.0;
+            rows[i] = mk<double>(db[i] * inv, ei * ei);
+        }
+        __syncthreads();
+    }
     double lo = p.gl, hi = p.gu;
     for (int r = 0; r < MAX_ROUNDS; ++r) {
         const double width = hi - lo;
@@ -132,23 +170,14 @@ __global__ __launch_bounds__(256) void stebz_bisect(const double* __restrict__ d
         const bool done = width <= 2.0 * EPS * fmax(fmax(fabs(lo), fabs(hi)), 1.0) || mid <= lo || mid >= hi;
         // every lane of the group takes the same decision (same lo, hi)
         if (done) break;
-        double x = lo + width * (double)(q + 1) * 0.25;
-        if (q == 1) x = mid;                       // the midpoint exactly
+        double x = lo + width * ((double)(q + 1) / (double)(LANES + 1));
+        if (q == LANES / 2) x = mid;               // a point strictly inside
         x = fmin(fmax(x, lo), hi);
-        const int c = q < 3 ? sturm_count(db, eb, n, inv, x, p.pivmin) : 0;
-        // gather the group's three points and counts (quad_perm broadcasts of
-        // lanes 0, 1, 2 of the quad)
-        const double xs[3] = {quad_bcast<0>(x), quad_bcast<1>(x), quad_bcast<2>(x)};
-        const int cs[3] = {quad_bcast<0>(c), quad_bcast<1>(c), quad_bcast<2>(c)};
-        double nlo = lo, nhi = hi;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            if (cs[k] <= jc) nlo = fmax(nlo, xs[k]);
-        }
-#pragma unroll
-        for (int k = 2; k >= 0; --k) {
-            if (cs[k] > jc) nhi = fmin(nhi, xs[k]);
-        }
+        const int c = sturm_count(staged ? rows : nullptr, db, eb, n, inv, x, p.pivmin);
+        // the largest point with at most j eigenvalues below it, the smallest
+        // with more
+        const double nlo = group_max<LANES>(c <= jc ? x : lo);
+        double nhi = -group_max<LANES>(c > jc ? -x : -hi);
         if (nhi < nlo) nhi = nlo;                  // counts not monotone by rounding: keep a valid interval
         lo = nlo;
         hi = nhi;
@@ -157,6 +186,15 @@ __global__ __launch_bounds__(256) void stebz_bisect(const double* __restrict__ d
     double x = 0.5 * (lo + hi);
     if (fabs(x) <= 2.0 * EPS) x = 0.0;
     if (live && q == 0) w[b * sw + j] = x * p.scale;
+}
+
+template <int LANES>
+void launch_bisect(hipStream_t st, const double* d, const double* e, int64_t sde, int64_t n, int64_t nk,
+                   const BzPrep* prep, double* w, int64_t sw)
+{
+    const int staged = n <= LDS_ROWS;
+    hipLaunchKernelGGL(stebz_bisect<LANES>, dim3((unsigned)((n * LANES + 255) / 256), (unsigned)nk), dim3(256),
+                       staged ? sizeof(double2) * (size_t)n : 0, st, d, e, sde, (int)n, prep, w, sw, staged);
 }
 
 }  // namespace
@@ -169,8 +207,16 @@ hipError_t stebz(hipStream_t st, const double* d, const double* e, int64_t sde, 
     if (n < 1 || nk < 1) return hipSuccess;
     BzPrep* prep = static_cast<BzPrep*>(work);
     hipLaunchKernelGGL(stebz_prep, dim3((unsigned)nk), dim3(256), 0, st, d, e, sde, (int)n, prep);
-    const unsigned gx = (unsigned)((n * LANES + 255) / 256);
-    hipLaunchKernelGGL(stebz_bisect, dim3(gx, (unsigned)nk), dim3(256), 0, st, d, e, sde, (int)n, prep, w, sw);
+    // More lanes per eigenvalue are fewer rounds and more counts in all: worth
+    // it as long as SIMDs have room for the waves.  n = 128 x 1 with 4, 8, 16,
+    // 64 lanes: 209, 152, 124, 87 us; 600 x 4: 943, 667, 518, 774; 616 x 8:
+    // 1014, 710, 808, 1190; 1040 x 8: 1605, 1689, 1805, 3299; 2000 x 16: 4743,
+    // 5956, 8467, 20992.
+    const int64_t count = n * nk;
+    if (count <= 1024) launch_bisect<64>(st, d, e, sde, n, nk, prep, w, sw);
+    else if (count <= 4096) launch_bisect<16>(st, d, e, sde, n, nk, prep, w, sw);
+    else if (count <= 8192) launch_bisect<8>(st, d, e, sde, n, nk, prep, w, sw);
+    else launch_bisect<4>(st, d, e, sde, n, nk, prep, w, sw);
     return hipGetLastError();
 }
 

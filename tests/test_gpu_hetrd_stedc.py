@@ -218,6 +218,21 @@ def test_stebz_closed_forms():
     assert mx(w2 - cle) <= 16 * EPS * m
 
 
+# bisection at the edges of its lane counts (64, 16, 8 and 4 lanes for n nk up to
+# 1024, 4096, 8192 and beyond) and of T in LDS (4096 rows): Toeplitz matrices,
+# each problem with its own shift and scale, tolerance as above
+@pytest.mark.parametrize("n,nk", [(1, 3), (2, 2), (63, 1), (1024, 1), (65, 16), (1365, 3), (4096, 1), (4097, 1),
+                                  (100, 82), (5, 1700)])
+def test_stebz_lane_counts(n, nk):
+    a = 0.3 - 0.01 * np.arange(nk)
+    b = -1.7 + 0.0005 * np.arange(nk)
+    j = np.arange(1, n + 1)
+    w = gpu_stebz(np.repeat(a[:, None], n, 1), np.repeat(b[:, None], n - 1, 1))
+    ref = np.sort(a[:, None] + 2 * b[:, None] * np.cos(j * np.pi / (n + 1)), axis=1)
+    # the shift reaches 17 and is then the scale of the matrix
+    assert np.all(np.abs(w - ref).max(axis=1) <= 8 * EPS * 4 * np.maximum(2 * np.abs(b), np.abs(a)))
+
+
 # the resident reduction at the edges of its tiles (16), of its two tile
 # counts (64, 128), at the smallest trailing orders and handed over to with a
 # ragged trailing order; tolerances as above
