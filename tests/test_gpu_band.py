@@ -62,6 +62,26 @@ def test_fermi_matches_oracle(nk, n, kT, fill):
     assert np.abs(occ - occ0).max() <= dmu / (4 * kT) + 64 * U
 
 
+# where Newton steps start badly: nearly empty and nearly full bands, levels far
+# apart on the scale of kT, one that is wide against the spectrum
+@pytest.mark.parametrize("nk,n,kT,fill", [(1, 1, 1e-3, 0.01), (2, 64, 0.05, 1e-6), (2, 1025, 3.0, 0.999),
+                                          (4, 300, 1e-4, 0.5), (5, 90, 0.01, 0.995)])
+def test_fermi_newton_edges(nk, n, kT, fill):
+    test_fermi_matches_oracle(nk, n, kT, fill)
+
+
+def test_fermi_in_a_gap():
+    # the count is flat there: mu is anywhere inside, the occupations are 0 or 1
+    # to the rounding of the count (n terms of one)
+    rng = np.random.default_rng(77)
+    nk, n = 3, 130
+    w = np.sort(np.where(np.arange(n) < n // 2, -1.0, 1.0) + rng.uniform(-0.1, 0.1, (nk, n)), axis=1)
+    res, occ, st = gpu_fermi(w, np.full(nk, 1.0 / nk), float(n), 0.01, 2.0)
+    assert st == 0 and -0.9 < res[0] < 0.9
+    assert abs(res[2] - n) <= 1e-12 * n
+    assert np.abs(occ - (w < 0)).max() <= 1e-12 * n
+
+
 def test_fermi_out_of_range_status():
     w = np.array([[-1.0, 0.0, 1.0]])
     for nelec in (0.0, 6.0, 7.5, -1.0):
