@@ -85,11 +85,11 @@ struct SolvePlan {
     int nb, kb;
     int slots1;                // Hermitian-product tile grouping threshold (HetrdWs::slots1)
     int groups;                // HetrdWs::groups
-    int NBmax, CHmax, PN;
+    int NBmax, CHmax;
     // complex128 arrays
-    size_t Aw, Vs, X, G, Wp, tau, ypart, ypartT, pvw, qpart, uwork, cwork, ppart, ndrop;
+    size_t Aw, Vs, X, G, Wp, tau, ypart, ypartT, pdot, qpart, uwork, cwork, ppart, ndrop;
     // real / int arrays
-    size_t d, e, sS, wA, pnorm, Zr, Qs, Vsec;
+    size_t d, e, sS, wA, unorm, Zr, Qs, Vsec;
     size_t dc_es, dc_onrm, dc_D0, dc_D1, dc_sd, dc_sz, dc_ndd, dc_ndz, dc_dfd, dc_rotc, dc_rots, dc_rho, dc_tauv,
         dc_lam, dc_zhat;
     size_t dc_kcnt, dc_ndcnt, dc_nrot, dc_perm, dc_ndx, dc_dfx, dc_rota, dc_rotb, dc_orgi, dc_cmap;
@@ -97,7 +97,7 @@ struct SolvePlan {
     // mixed precision: complex64 tridiagonalisation / back-transformation
     // buffers and the FP64 refinement scratch (size 0 in the FP64 form)
     bool mixed;
-    size_t f_A, f_V, f_Y, f_W, f_tau, f_ypart, f_ypartT, f_pvw, f_qpart, f_uwork, f_d, f_e, f_pnorm;
+    size_t f_A, f_V, f_Y, f_W, f_tau, f_ypart, f_ypartT, f_pdot, f_qpart, f_uwork, f_d, f_e, f_unorm;
     size_t r_Ynext, r_G, r_S, r_F, r_pS, r_pR, r_delta, r_cid;
     size_t total;
 };
@@ -114,7 +114,6 @@ SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots
     p.kb = UNMTR_KB;
     p.NBmax = hetrd_nbmax(n);
     p.CHmax = hetrd_chmax(n);
-    p.PN = hetrd_pn(n);
     Layout L;
     const size_t z = sizeof(double2), r = sizeof(double), i4 = sizeof(int);
     const size_t nn = (size_t)n * n;
@@ -129,7 +128,7 @@ SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots
     p.tau = L.add(z * n * nk);
     p.ypart = L.add(z * (size_t)p.NBmax * p.NBmax * 64 * nk);
     p.ypartT = L.add(z * (size_t)p.NBmax * p.CHmax * 64 * nk);
-    p.pvw = L.add(z * 4 * (size_t)p.NBmax * nbA * nk);      // W and V parts interleaved by block
+    p.pdot = L.add(z * 2 * nbA * nk);
     p.qpart = L.add(r * (size_t)p.NBmax * p.CHmax * nk);
     p.uwork = L.add(z * (size_t)unmtr_work_elems(n, p.kb) * nk);
     p.cwork = L.add(z * (size_t)chol_work_elems(n) * nk);
@@ -139,7 +138,7 @@ SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots
     p.e = L.add(r * n * nk);
     p.sS = L.add(r * n * nk);
     p.wA = L.add(r * n * nk);
-    p.pnorm = L.add(r * 2 * p.PN * nk);
+    p.unorm = L.add(r * nk);
     p.Zr = L.add(r * nn * nk);
     p.Qs = L.add(r * nn * nk);
     p.Vsec = L.add(r * nn * nk);
@@ -161,12 +160,12 @@ SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots
     p.f_tau = L.add(m * c * n * nk);
     p.f_ypart = L.add(m * c * (size_t)p.NBmax * p.NBmax * 64 * nk);
     p.f_ypartT = L.add(m * c * (size_t)p.NBmax * p.CHmax * 64 * nk);
-    p.f_pvw = L.add(m * c * 4 * (size_t)p.NBmax * nbA * nk);
+    p.f_pdot = L.add(m * c * 2 * nbA * nk);
     p.f_qpart = L.add(m * f * (size_t)p.NBmax * p.CHmax * nk);
     p.f_uwork = L.add(m * c * (size_t)unmtr_work_elems(n, p.kb) * nk);
     p.f_d = L.add(m * f * n * nk);
     p.f_e = L.add(m * f * n * nk);
-    p.f_pnorm = L.add(m * f * 2 * p.PN * nk);
+    p.f_unorm = L.add(m * f * nk);
     p.r_Ynext = L.add(m * z * nn * nk);
     p.r_G = L.add(m * z * nn * nk);
     p.r_S = L.add(m * z * nn * nk);
@@ -194,12 +193,10 @@ HetrdWs<float> hetrd_ws32(const SolvePlan& p, void* w)
     h.d = reinterpret_cast<float*>(static_cast<char*>(w) + p.f_d);
     h.e = reinterpret_cast<float*>(static_cast<char*>(w) + p.f_e);
     h.tau = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_tau);
-    h.pnorm = reinterpret_cast<float*>(static_cast<char*>(w) + p.f_pnorm); h.s_pnorm = 2 * p.PN;
+    h.unorm = reinterpret_cast<float*>(static_cast<char*>(w) + p.f_unorm);
     h.ypart = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_ypart); h.s_ypart = (int64_t)p.NBmax * p.NBmax * 64;
     h.ypartT = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_ypartT); h.s_ypartT = (int64_t)p.NBmax * p.CHmax * 64;
-    h.pvw = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_pvw);
-    h.pvv = h.pvw + p.nb;
-    h.s_pdot = 4 * (int64_t)p.NBmax * p.nb;
+    h.pdot = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_pdot); h.s_pdot = 2 * (int64_t)p.nb;
     h.qpart = reinterpret_cast<float*>(static_cast<char*>(w) + p.f_qpart); h.s_qpart = (int64_t)p.NBmax * p.CHmax;
     return h;
 }
@@ -220,10 +217,10 @@ HetrdWs<double> hetrd_ws(const SolvePlan& p, void* w, double2* A, int64_t lda, i
     h.V = V; h.sV = p.n * p.n;
     h.W = at<double2>(w, p.Wp); h.sW = p.n * p.nb;
     h.d = d; h.e = e; h.tau = tau;
-    h.pnorm = at<double>(w, p.pnorm); h.s_pnorm = 2 * p.PN;
+    h.unorm = at<double>(w, p.unorm);
     h.ypart = at<double2>(w, p.ypart); h.s_ypart = (int64_t)p.NBmax * p.NBmax * 64;
     h.ypartT = at<double2>(w, p.ypartT); h.s_ypartT = (int64_t)p.NBmax * p.CHmax * 64;
-    h.pvw = at<double2>(w, p.pvw); h.pvv = h.pvw + p.nb; h.s_pdot = 4 * (int64_t)p.NBmax * p.nb;
+    h.pdot = at<double2>(w, p.pdot); h.s_pdot = 2 * (int64_t)p.nb;
     h.qpart = at<double>(w, p.qpart); h.s_qpart = (int64_t)p.NBmax * p.CHmax;
     return h;
 }

@@ -7,22 +7,19 @@
 //       the lower triangle only, with u the column below the sub-diagonal as
 //       it stands (u_o = 0, u_r = A(r, i)), plus the chunk's share of
 //       q = Re(u^H z).  It needs nothing derived in this step, so the
-//       workgroups only stream their tiles.
-//   update : every workgroup derives the reflector (Procedure 2, stable sign,
-//       real beta) from the partial norms, v = (1, scale * A(o+1:n, i)), and
-//       forms for its rows y = tau (A22(:, o) + scale z - V (W^H v) - W (V^H v))
+//       workgroups only stream their tiles.  A few more workgroups form the
+//       panel products W^H u and V^H u and ||u||^2 meanwhile.
+//   update : every wave derives the reflector (Procedure 2, stable sign, real
+//       beta), v = (1, scale * A(o+1:n, i)), and forms for its rows
+//       y = tau (A22(:, o) + scale z - V (W^H v) - W (V^H v))
 //       (A22 v = A22(:, o) + scale A22 u by linearity) and
 //       w = y - (tau/2)(y^H v) v (Procedure 5).  y^H v needs no reduction over
 //       y: with h = A22(:, o), v^H A22 v = h_o + 2 Re(scale z_o) + |scale|^2 q
 //       and y^H v = conj(tau) (v^H A22 v - 2 Re((V^H v)^H (W^H v))), so
 //       alpha2 = -(tau/2) y^H v = -|tau|^2 / 2 (...) is real and every
-//       workgroup computes it, and row o of w, from the same partials.
+//       wave computes it, and row o of w, from the same partials.
 //       Then the next column of the panel is brought up to date,
-//       A(o:n, o) -= V(o:n, 0:j) conj(W(o, 0:j))^T + W(o:n, 0:j) conj(V(o, 0:j))^T,
-//       and its squared norm below the sub-diagonal and its products with
-//       the panel columns (the pieces of W^H v and V^H v for the next
-//       reflector, taken on the unscaled column) are reduced in per-block
-//       partials.
+//       A(o:n, o) -= V(o:n, 0:j) conj(W(o, 0:j))^T + W(o:n, 0:j) conj(V(o, 0:j))^T.
 // After the panel the trailing matrix takes the rank-2nb update
 // A22 -= V W^H + W V^H (Procedure 6, on MFMA).
 // Once a panel's trailing matrix is small enough, the rest of the reduction
@@ -45,36 +42,11 @@ namespace {
 
 constexpr int ZT = 64;          // ZHEMV tile edge
 constexpr int ZCH = 4;          // tiles per ZHEMV chunk: one per wave of the workgroup
-constexpr int RB = 64;          // rows per workgroup in the column kernels
 
 // chunks of block column C in the four-tile form, and in the form a
 // reduction uses (ws.zch: 4 tiles per chunk, or 1 for the one-tile form)
 __device__ __host__ inline int nchunks(int NB, int C) { return (NB - C + ZCH - 1) / ZCH; }
 __device__ __host__ inline int nchunks_z(int NB, int C, int zch) { return zch == 1 ? NB - C : (NB - C + 3) >> 2; }
-
-// Partial norms of column i: lane q takes the per-block partials q, q + 64,
-// ... (pn_first: the first of them, requested with the kernel's first batch
-// of loads; pn_rest: the sum, in that order).
-template <typename R>
-__device__ inline const R* pnorm_base(const HetrdWs<R>& ws, int64_t b, int i)
-{
-    return ws.pnorm + b * ws.s_pnorm + (i & 1) * ((ws.n + RB - 1) / RB);
-}
-template <typename R>
-__device__ inline R pn_first(const HetrdWs<R>& ws, int64_t b, int i, int lane)
-{
-    const int np = (ws.n - i + RB - 1) / RB;
-    return pnorm_base(ws, b, i)[lane < np ? lane : 0];
-}
-template <typename R>
-__device__ inline R pn_rest(const HetrdWs<R>& ws, int64_t b, int i, int lane, R first)
-{
-    const int np = (ws.n - i + RB - 1) / RB;
-    const R* pn = pnorm_base(ws, b, i);
-    R part = lane < np ? first : (R)0;
-    for (int q = lane + 64; q < np; q += 64) part += pn[q];
-    return part;
-}
 
 // One halving step of the transposing reduction: lanes with the MASK bit set
 // keep values HALF..2HALF-1 (moved down to 0..HALF-1), the others keep
@@ -129,20 +101,52 @@ __device__ __attribute__((always_inline)) inline cx<R> transpose_sum8(cx<R> (&t)
 }
 
 // ---------------------------------------------------------------------------
-// First column of a panel: d_c and partial norms of rows c+2..n-1.
+// The panel products with column i, W^H u and V^H u (u below the sub-diagonal),
+// and ||u||^2: workgroup `unit` of a problem takes DV of the 2 j vectors
+// W(:, 0..j-1), V(:, p..p+j-1), one row per thread and step.
+constexpr int DV = 8;
+__host__ __device__ inline int dot_units(int j) { return j == 0 ? 1 : (2 * j + DV - 1) / DV; }
+
 template <typename R>
-__global__ __launch_bounds__(RB) void hetrd_colstart(HetrdWs<R> ws, int c)
+__device__ __attribute__((always_inline)) inline void panel_dots(const HetrdWs<R>& ws, int i, int p, int unit, int64_t b)
 {
-    const int64_t b = blockIdx.y;
-    const int64_t r = (int64_t)c + (int64_t)blockIdx.x * RB + threadIdx.x;
-    R acc = 0;
-    if (r < ws.n) {
-        const cx<R> a = ws.A[b * ws.sA + r + (int64_t)c * ws.lda];
-        if (r == c) ws.d[b * ws.n + c] = a.x;
-        if (r >= c + 2) acc = a.x * a.x + a.y * a.y;
+    __shared__ cx<R> sd[4][DV];
+    __shared__ R sn[4];
+    const int n = ws.n, j = i - p;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const cx<R>* Ai = ws.A + b * ws.sA + (int64_t)i * ws.lda;
+    const cx<R>* Wp = ws.W + b * ws.sW;
+    const cx<R>* Vp = ws.V + b * ws.sV + (int64_t)p * n;
+    const cx<R>* P[DV];
+#pragma unroll
+    for (int k = 0; k < DV; ++k) {
+        const int idx = unit * DV + k;
+        P[k] = idx < j ? Wp + (int64_t)idx * n : Vp + (int64_t)(idx < 2 * j ? idx - j : 0) * n;
     }
-    acc = dpp_wave_sum(acc);
-    if (threadIdx.x == 0) ws.pnorm[b * ws.s_pnorm + (c & 1) * ((ws.n + RB - 1) / RB) + blockIdx.x] = acc;
+    cx<R> acc[DV];
+#pragma unroll
+    for (int k = 0; k < DV; ++k) acc[k] = czero<cx<R>>();
+    R nrm = 0;
+#pragma unroll 2
+    for (int r = i + 2 + tid; r < n; r += 256) {
+        const cx<R> u = Ai[r];
+#pragma unroll
+        for (int k = 0; k < DV; ++k) acc[k] = cfmac(P[k][r], u, acc[k]);
+        nrm = fma(u.x, u.x, fma(u.y, u.y, nrm));
+    }
+    const cx<R> s = transpose_sum8<R>(acc, lane);
+    nrm = dpp_wave_sum(nrm);
+    if ((lane & 7) == 0) sd[w][lane >> 3] = s;
+    if (lane == 0) sn[w] = nrm;
+    __syncthreads();
+    const int idx = unit * DV + tid;
+    if (tid < DV && idx < 2 * j)
+        ws.pdot[b * ws.s_pdot + (idx < j ? idx : ws.nb + idx - j)] =
+            cadd(cadd(sd[0][tid], sd[1][tid]), cadd(sd[2][tid], sd[3][tid]));
+    if (unit == 0 && tid == 0) {
+        ws.unorm[b] = (sn[0] + sn[1]) + (sn[2] + sn[3]);
+        if (j == 0) ws.d[b * n + i] = Ai[i].x;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -153,9 +157,9 @@ __global__ __launch_bounds__(RB) void hetrd_colstart(HetrdWs<R> ws, int c)
 // products go to the wave's LDS block, the next group is requested into the
 // same registers, and the column sums are taken from LDS while it is in
 // flight; the four waves' column sums are added once.  Three workgroups per
-// CU.
+// CU.  The first `units` workgroups of a problem form the panel products.
 template <typename R, bool BUF>
-__global__ __launch_bounds__(256, 3) void hetrd_zhemv(HetrdWs<R> ws, int i, int rev)
+__global__ __launch_bounds__(256, 3) void hetrd_zhemv(HetrdWs<R> ws, int i, int p, int units, int rev)
 {
     __shared__ cx<R> svC[ZCH][ZT];
     __shared__ cx<R> sT[ZCH][ZT];
@@ -164,7 +168,11 @@ __global__ __launch_bounds__(256, 3) void hetrd_zhemv(HetrdWs<R> ws, int i, int 
     // last chunk first), so that a launch after a forward one starts on the
     // tiles its predecessor read last
     const int64_t b = rev ? (int64_t)(gridDim.y - 1 - blockIdx.y) : (int64_t)blockIdx.y;
-    const int lid = rev ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    if ((int)blockIdx.x < units) {
+        panel_dots(ws, i, p, blockIdx.x, b);
+        return;
+    }
+    const int lid = rev ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x - units;
     const int n = ws.n;
     const int o = i + 1;
     const int m = n - o;
@@ -292,13 +300,17 @@ __global__ __launch_bounds__(256, 3) void hetrd_zhemv(HetrdWs<R> ws, int i, int 
 // direct parts are added in LDS, and each column's sum comes from the one
 // wave that owns it.  Same partial-sum layout with one chunk per tile.
 template <typename R, bool BUF>
-__global__ __launch_bounds__(256, 3) void hetrd_zhemv_tile(HetrdWs<R> ws, int i, int rev)
+__global__ __launch_bounds__(256, 3) void hetrd_zhemv_tile(HetrdWs<R> ws, int i, int p, int units, int rev)
 {
     __shared__ cx<R> svC[ZCH][ZT];
     __shared__ cx<R> sT[ZCH][ZT];
     __shared__ cx<R> sP[ZCH][8][ZT + 1];
     const int64_t b = rev ? (int64_t)(gridDim.y - 1 - blockIdx.y) : (int64_t)blockIdx.y;
-    const int lid = rev ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    if ((int)blockIdx.x < units) {
+        panel_dots(ws, i, p, blockIdx.x, b);
+        return;
+    }
+    const int lid = rev ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x - units;
     const int n = ws.n;
     const int o = i + 1;
     const int m = n - o;
@@ -405,9 +417,8 @@ __global__ __launch_bounds__(256, 3) void hetrd_zhemv_tile(HetrdWs<R> ws, int i,
 
 // ---------------------------------------------------------------------------
 // Partial sums read as buffer loads: an offset at or beyond the buffer's size
-// returns 0, so a term that does not exist is read at OOB and added as 0, and
+// returns 0, so a term that does not exist is read past the end and added as 0, and
 // every batch is loaded and added whole, without selects.
-constexpr int OOB = 0x20000000;
 
 // A descriptor built from workgroup-uniform values, pinned to scalar
 // registers (64-bit offset arithmetic can leave it in vector registers, and a
@@ -440,82 +451,9 @@ __device__ inline cx<R> bload(i4_t rsrc, int voff)
         return __builtin_bit_cast(cx<R>, raw_buffer_load_v2i32(rsrc, voff, 0, 0));
 }
 
-// z at one row: the partial sums over the block columns and chunks that
-// touch it, split over the four waves (wave w takes the terms with index =
-// w mod 4) and combined as (w0 + w1) + (w2 + w3).  A wave's terms are the
-// block columns C = w, w + 4, ... <= Rb (per-block partials) and the chunks
-// ch = w, w + 4, ... < nc (per-chunk partials); term t of each list goes to
-// the first of two running sums if t is even, to the second if odd.  The
-// first ZB terms of both lists are requested together (one memory round trip
-// at n = 2000), longer lists load the rest as they are summed.
-constexpr int ZB = 8;
-
-template <typename R>
-struct ZTerms {
-    i4_t rp, rq;          // block row Rb's per-block and per-chunk partials
-    int w, tp, tq, roff;  // wave (uniform), term counts, row offset in bytes
-    __device__ ZTerms(const HetrdWs<R>& ws, int64_t b, int Rb, int NB, int r, int w_) : w(w_)
-    {
-        rp = uniform_rsrc(ws.ypart + b * ws.s_ypart + (int64_t)Rb * ws.NBmax * ZT,
-                         (uint32_t)((int64_t)ws.NBmax * ZT * (int64_t)sizeof(cx<R>)));
-        rq = uniform_rsrc(ws.ypartT + b * ws.s_ypartT + (int64_t)Rb * ws.CHmax * ZT,
-                         (uint32_t)((int64_t)ws.CHmax * ZT * (int64_t)sizeof(cx<R>)));
-        const int nc = nchunks_z(NB, Rb, ws.zch);
-        tp = Rb >= w ? (Rb - w) / 4 + 1 : 0;
-        tq = nc > w ? (nc - 1 - w) / 4 + 1 : 0;
-        roff = r * (int)sizeof(cx<R>);
-    }
-    __device__ int off(int t, int tn) const
-    {
-        return (t < tn ? (w + 4 * t) * ZT * (int)sizeof(cx<R>) : OOB) + roff;
-    }
-    __device__ void load(int t0, cx<R> (&vp)[ZB], cx<R> (&vq)[ZB]) const
-    {
-#pragma unroll
-        for (int t = 0; t < ZB; ++t) {
-            vp[t] = bload<R>(rp, off(t0 + t, tp));
-            vq[t] = bload<R>(rq, off(t0 + t, tq));
-        }
-    }
-    // the whole sum, given the first batches (overwritten)
-    __device__ cx<R> sum(cx<R> (&vp)[ZB], cx<R> (&vq)[ZB]) const
-    {
-        cx<R> y0 = czero<cx<R>>(), y1 = czero<cx<R>>();
-#pragma unroll
-        for (int t = 0; t < ZB; t += 2) {
-            y0 = cadd(y0, vp[t]);
-            y1 = cadd(y1, vp[t + 1]);
-        }
-        for (int t0 = ZB; t0 < tp; t0 += ZB) {
-#pragma unroll
-            for (int t = 0; t < ZB; ++t) vp[t] = bload<R>(rp, off(t0 + t, tp));
-#pragma unroll
-            for (int t = 0; t < ZB; t += 2) {
-                y0 = cadd(y0, vp[t]);
-                y1 = cadd(y1, vp[t + 1]);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < ZB; t += 2) {
-            y0 = cadd(y0, vq[t]);
-            y1 = cadd(y1, vq[t + 1]);
-        }
-        for (int t0 = ZB; t0 < tq; t0 += ZB) {
-#pragma unroll
-            for (int t = 0; t < ZB; ++t) vq[t] = bload<R>(rq, off(t0 + t, tq));
-#pragma unroll
-            for (int t = 0; t < ZB; t += 2) {
-                y0 = cadd(y0, vq[t]);
-                y1 = cadd(y1, vq[t + 1]);
-            }
-        }
-        return cadd(y0, y1);
-    }
-};
-
-// z at row o (row 0 of block 0), needed by every workgroup: the 1 + nc terms
+// z at row o (row 0 of block 0), needed by every wave: the 1 + nc terms
 // (block column 0, then the chunks of block row 0) spread over the lanes of
-// one wave and summed by a fixed lane tree, so every workgroup holds the same
+// the wave and summed by a fixed lane tree, so every wave holds the same
 // bits.  z0_first is the lane's first term, requested with the kernel's first
 // batch of loads; z0_rest adds the others (lane + 64, ...).
 template <typename R>
@@ -534,29 +472,28 @@ __device__ inline cx<R> z0_rest(const HetrdWs<R>& ws, int64_t b, int NB, int lan
     return acc;
 }
 
-template <typename C>
-__device__ inline C sum4(const C (&s)[4][64], int l)
-{
-    return cadd(cadd(s[0][l], s[1][l]), cadd(s[2][l], s[3][l]));
-}
+// Column i: reflector, v and w, then (update_next) column o brought up to
+// date.  A workgroup has the 64 rows of a row block, a wave 16 of them with
+// four lanes per row: lane (r, k) takes every fourth panel column and every
+// fourth partial sum of z, k first, and two lane exchanges add the four.  The
+// waves share nothing, so the launch has no barrier; each forms the scalars of
+// the column (reflector, W^H v, V^H v, row o) from the same loads.
+//
+// Bound by the instructions of a wave (few problems: one wave a SIMD, 64: all of
+// them): one pass over the panel columns serves the corrections and the next
+// column, and the panel products come finished from the launch before.  Against
+// four waves sharing 64 rows by panel columns, with the panel products of the
+// next column formed here in per-block partials: one problem at m = 1500 6.6 ->
+// 5.6 us, 16 at m = 780 7.2 -> 5.7 us, 64 at m = 780 17 -> 12 us (and 0.4, 0.7, 1.9 us
+// more in the launch of the product, which has the panel products now).
+constexpr int PC = 4;           // panel columns of V and W per lane and batch
 
-// Column i: reflector, v and w for one 64-row block (rows o + 64 Rb ...),
-// then (update_next) column o brought up to date for these rows with its
-// partial norm and partial panel dots.  Every global value the block needs
-// is requested in one first phase, including this thread's rows of the panel
-// columns V(:, p + jj), W(:, jj) (the four waves take jj = w, w+4, ...; panels
-// up to 32 wide are held in registers, wider ones reload the rest), which
-// then serve the corrections, the column update and the panel dots.  Every
-// wave forms the panel dots, the row-o scalars and v, w of the block itself,
-// so the launch has three workgroup barriers: after the loads, after the
-// corrections and after the column update.
-template <typename R>
-__global__ __launch_bounds__(256) void hetrd_update(HetrdWs<R> ws, int i, int p, int update_next, int nch)
+template <typename R, int ZB>
+__global__ __launch_bounds__(256, 2) void hetrd_update(HetrdWs<R> ws, int i, int p, int update_next, int nch)
 {
-    __shared__ cx<R> s1[4][64], s2[4][64], sy[4][64], sco[4][64];
-    __shared__ cx<R> swv[4][64], svv[4][64];  // W^H v, V^H v (zero beyond j), one copy per wave
-    __shared__ cx<R> sWo[64], sVo[64];        // row o of W(:, 0:j) and V(:, p:p+j) (zero beyond j)
-    __shared__ R sqq[4];
+    // per wave: W^H v, V^H v, row o of W and of V over the panel's columns
+    // (zero beyond j)
+    __shared__ cx<R> sc[4][4][64];
     const int64_t b = blockIdx.y;
     const int n = ws.n, o = i + 1, m = n - o;
     const int NB = (m + ZT - 1) / ZT;
@@ -564,279 +501,162 @@ __global__ __launch_bounds__(256) void hetrd_update(HetrdWs<R> ws, int i, int p,
     const int j = i - p;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform (scalar) wave index
-    const int64_t gr = (int64_t)o + (int64_t)Rb * ZT + lane;
+    const int k = lane >> 4, row = 16 * w + (lane & 15);
+    const int64_t gr = (int64_t)o + (int64_t)Rb * ZT + row;
+    if ((int64_t)o + (int64_t)Rb * ZT + 16 * w >= n) return;
     const int64_t grc = gr < n ? gr : (int64_t)n - 1;     // clamped row for unconditional loads
-    const cx<R>* A = ws.A + b * ws.sA;
+    cx<R>* A = ws.A + b * ws.sA;
     cx<R>* V = ws.V + b * ws.sV;
     cx<R>* W = ws.W + b * ws.sW;
-    const int npn = (n + RB - 1) / RB;
     const cx<R> zero = czero<cx<R>>();
 
-    // ---- phase 1: every load that depends on nothing computed here, issued
-    // whole before any of it is waited for (lists longer than their first
-    // batch load the rest as they are summed)
-    // V(gr, p + jj), W(gr, jj) for jj = w + 4q < j, else 0 (read past the
-    // panel's buffers)
-    const uint32_t panel_bytes = (uint32_t)((int64_t)n * ws.nb * (int64_t)sizeof(cx<R>));
-    const i4_t rV = uniform_rsrc(V + (int64_t)p * n, panel_bytes), rW = uniform_rsrc(W, panel_bytes);
-    const int roff = (int)grc * (int)sizeof(cx<R>);
-    cx<R> pv[8], pw[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int jj = w + 4 * q;
-        const int off = (jj < j ? jj * n * (int)sizeof(cx<R>) : OOB) + roff;
-        pv[q] = bload<R>(rV, off);
-        pw[q] = bload<R>(rW, off);
-    }
-    const cx<R> ai = A[grc + (int64_t)i * ws.lda];
-    cx<R> h = A[grc + (int64_t)o * ws.lda];
-    const cx<R> alpha = A[(int64_t)(i + 1) + (int64_t)i * ws.lda];
+    // ---- every load that depends on nothing computed here, issued whole
+    // before any of it is waited for (longer lists load the rest as they go):
+    // what the scalars need first
+    const cx<R> alpha = A[(int64_t)o + (int64_t)i * ws.lda];
     const R hoo = A[(int64_t)o + (int64_t)o * ws.lda].x;
-    const R npf = pn_first(ws, b, i, lane);
-    const cx<R> z0f = z0_first(ws, b, NB, lane);
-    // row o of the panel (stored to LDS by wave 1 once every load is issued)
+    const R un = ws.unorm[b];
     const int lc = lane < j ? lane : 0;
+    const cx<R> wd = ws.pdot[b * ws.s_pdot + lc];
+    const cx<R> vd = ws.pdot[b * ws.s_pdot + ws.nb + lc];
     const cx<R> wo_l = W[(int64_t)o + (int64_t)lc * n];
     const cx<R> vo_l = V[(int64_t)o + (int64_t)(p + lc) * n];
-    // this row's z partials and the chunk shares of q = Re(u^H A22 u)
-    const ZTerms<R> zt(ws, b, Rb, NB, lane, w);
-    cx<R> zp[ZB], zq[ZB];
-    zt.load(0, zp, zq);
+    const cx<R> z0f = z0_first(ws, b, NB, lane);
     constexpr int QL = 4;
     const i4_t rq = uniform_rsrc(ws.qpart + b * ws.s_qpart, (uint32_t)((int64_t)nch * (int64_t)sizeof(R)));
     R qt[QL];
 #pragma unroll
-    for (int u = 0; u < QL; ++u) qt[u] = bload_r<R>(rq, (tid + 256 * u) * (int)sizeof(R));
-
-    // the unscaled panel-dot partials of column i, blocks q = w, w + 4, ...
-    // (added in that order); lanes 0-31 take the W parts of panel columns
-    // 0-31, lanes 32-63 their V parts (columns 32 and up, for panels wider
-    // than 32, in a second pass)
-    constexpr int PL = 8;
-    const int npd = (n - i + RB - 1) / RB;
-    const int nb2 = 2 * ws.nb;
-    const i4_t rpd = uniform_rsrc(ws.pvw + b * ws.s_pdot + (int64_t)(i & 1) * ws.NBmax * nb2,
-                                 (uint32_t)((int64_t)ws.NBmax * nb2 * (int64_t)sizeof(cx<R>)));
-    const int pd_half = lane >> 5, pd_c = lane & 31;
-    auto pd_off = [&](int c0, int q) {
-        const int loff = c0 + pd_c < j ? (pd_half * ws.nb + c0 + pd_c) * (int)sizeof(cx<R>) : OOB;
-        return (q < npd ? q * nb2 * (int)sizeof(cx<R>) : OOB) + loff;
+    for (int u = 0; u < QL; ++u) qt[u] = bload_r<R>(rq, (lane + 64 * u) * (int)sizeof(R));
+    const cx<R> ai = A[grc + (int64_t)i * ws.lda];
+    cx<R> h = A[grc + (int64_t)o * ws.lda];
+    if (gr == o) h.y = 0;
+    // the row's z terms: block columns C = k, k + 4, ... <= Rb and the chunks
+    // k, k + 4, ... < nc of block column Rb
+    const int nc = nchunks_z(NB, Rb, ws.zch);
+    const i4_t rp = uniform_rsrc(ws.ypart + b * ws.s_ypart + (int64_t)Rb * ws.NBmax * ZT,
+                                 (uint32_t)((Rb + 1) * ZT * (int)sizeof(cx<R>)));
+    const i4_t rt = uniform_rsrc(ws.ypartT + b * ws.s_ypartT + (int64_t)Rb * ws.CHmax * ZT,
+                                 (uint32_t)(nc * ZT * (int)sizeof(cx<R>)));
+    constexpr int ZSTEP = 4 * ZT * (int)sizeof(cx<R>);
+    const int zoff = (k * ZT + row) * (int)sizeof(cx<R>);
+    cx<R> zp[ZB], zq[ZB];
+#pragma unroll
+    for (int t = 0; t < ZB; ++t) {
+        zp[t] = bload<R>(rp, zoff + t * ZSTEP);
+        zq[t] = bload<R>(rt, zoff + t * ZSTEP);
+    }
+    // this row of the panel columns k, k + 4, ... < j (0 beyond), in batches
+    const i4_t rV = uniform_rsrc(V + (int64_t)p * n, (uint32_t)((int64_t)n * j * (int64_t)sizeof(cx<R>)));
+    const i4_t rW = uniform_rsrc(W, (uint32_t)((int64_t)n * j * (int64_t)sizeof(cx<R>)));
+    const int pstep = 4 * n * (int)sizeof(cx<R>);
+    int poff = (k * n + (int)grc) * (int)sizeof(cx<R>);
+    cx<R> pv[PC], pw[PC];
+    auto load_panel = [&]() {
+#pragma unroll
+        for (int q = 0; q < PC; ++q) {
+            pv[q] = bload<R>(rV, poff);
+            pw[q] = bload<R>(rW, poff);
+            poff += pstep;
+        }
     };
-    cx<R> pt[PL];
-#pragma unroll
-    for (int u = 0; u < PL; ++u) pt[u] = bload<R>(rpd, pd_off(0, w + 4 * u));
+    load_panel();
 
-    // ---- sums of the partials (the remainders of long lists load here)
-    if (w == 1) {
-        sWo[lane] = csel(lane < j, wo_l, zero);
-        sVo[lane] = csel(lane < j, vo_l, zero);
-    }
-    sy[w][lane] = zt.sum(zp, zq);
-    {
-        R qa = 0;
-        for (int c0 = tid;; c0 += 256 * QL) {
-#pragma unroll
-            for (int u = 0; u < QL; ++u) qa += qt[u];
-            if (c0 + 256 * QL >= nch) break;
-#pragma unroll
-            for (int u = 0; u < QL; ++u) qt[u] = bload_r<R>(rq, (c0 + 256 * QL + 256 * u) * (int)sizeof(R));
-        }
-        qa = dpp_wave_sum(qa);
-        if (lane == 0) sqq[w] = qa;
-    }
-    cx<R> z0 = z0_rest(ws, b, NB, lane, z0f);
-    // panel-dot sums (the first pass's loads were issued with the others)
-    for (int c0 = 0; c0 < j; c0 += 32) {
-        if (c0 > 0) {
-#pragma unroll
-            for (int u = 0; u < PL; ++u) pt[u] = bload<R>(rpd, pd_off(c0, w + 4 * u));
-        }
-        cx<R> a = zero;
-        for (int q0 = w;; q0 += 4 * PL) {
-#pragma unroll
-            for (int u = 0; u < PL; ++u) a = cadd(a, pt[u]);
-            if (q0 + 4 * PL >= npd) break;
-#pragma unroll
-            for (int u = 0; u < PL; ++u) pt[u] = bload<R>(rpd, pd_off(c0, q0 + 4 * PL + 4 * u));
-        }
-        if (pd_half == 0)
-            s1[w][c0 + pd_c] = a;
-        else
-            s2[w][c0 + pd_c] = a;
-    }
+    // ---- scalars of the column, the same bits in every wave: reflector, panel
+    // products with v (lane = panel column), y_o, alpha2 and w_o
     cx<R> tau, scale;
     R beta;
-    reflector_core(alpha, dpp_wave_sum(pn_rest(ws, b, i, lane, npf)), tau, scale, beta);
-    if (gr == o) h.y = 0;
-    __syncthreads();
-
-    // ---- panel dots W^H v = conj(W(o, :)) + scale * partials (likewise V),
-    // lane = panel column.  Every wave forms them (the same bits in each) and
-    // keeps them in its own LDS row for the corrections, so no barrier is
-    // needed before those.
-    cx<R> wvl = zero, vvl = zero;
+    reflector_core(alpha, un, tau, scale, beta);
+    cx<R> wvl = zero, vvl = zero, wol = zero, vol = zero;
     if (lane < j) {
-        wvl = cfma(scale, sum4(s1, lane), cconj(sWo[lane]));
-        vvl = cfma(scale, sum4(s2, lane), cconj(sVo[lane]));
+        wvl = cfma(scale, wd, cconj(wo_l));
+        vvl = cfma(scale, vd, cconj(vo_l));
+        wol = wo_l;
+        vol = vo_l;
     }
-    swv[w][lane] = wvl;
-    svv[w][lane] = vvl;
-
-    // ---- row o: y_o, alpha2 and w_o from fixed-order wave sums over the
-    // panel columns, identical in every wave and every workgroup
-    cx<R> co = cfma(sVo[lane], wvl, cmul(sWo[lane], vvl));
+    sc[w][0][lane] = wvl;
+    sc[w][1][lane] = vvl;
+    sc[w][2][lane] = cconj(wol);
+    sc[w][3][lane] = cconj(vol);
+    R qq = 0;
+    for (int c0 = lane;; c0 += 64 * QL) {
+#pragma unroll
+        for (int u = 0; u < QL; ++u) qq += qt[u];
+        if (c0 - lane + 64 * QL >= nch) break;
+#pragma unroll
+        for (int u = 0; u < QL; ++u) qt[u] = bload_r<R>(rq, (c0 + 64 * (QL + u)) * (int)sizeof(R));
+    }
+    cx<R> z0 = z0_rest(ws, b, NB, lane, z0f);
+    cx<R> co = cfma(vol, wvl, cmul(wol, vvl));
     R cross = vvl.x * wvl.x + vvl.y * wvl.y;   // Re(conj(V^H v) W^H v)
     co.x = dpp_wave_sum(co.x);
     co.y = dpp_wave_sum(co.y);
     cross = dpp_wave_sum(cross);
     z0.x = dpp_wave_sum(z0.x);
     z0.y = dpp_wave_sum(z0.y);
-    const R qq = (sqq[0] + sqq[1]) + (sqq[2] + sqq[3]);
+    qq = dpp_wave_sum(qq);
     const cx<R> sz = cmul(scale, z0);
     const R vav = hoo + (R)2 * sz.x + (scale.x * scale.x + scale.y * scale.y) * qq;
     const R a2 = (R)-0.5 * (tau.x * tau.x + tau.y * tau.y) * (vav - (R)2 * cross);
     const cx<R> wo = cadd(cmul(tau, csub(cadd(mk<R>(hoo, 0), sz), co)), mk<R>(a2, 0));
     wave_sync();
 
-    // ---- this block's corrections V (W^H v) + W (V^H v), partial per wave
-    cx<R> corr = zero;
+    // ---- the lane's shares of z, of the corrections V (W^H v) + W (V^H v) and
+    // of the next column's
+    cx<R> z = zero, acc = zero;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int jj = w + 4 * q;
-        corr = cfma(pv[q], swv[w][jj], corr);
-        corr = cfma(pw[q], svv[w][jj], corr);
+    for (int t = 0; t < ZB; ++t) z = cadd(z, cadd(zp[t], zq[t]));
+    const int tmax = max(Rb + 1, nc);
+    for (int t = 4 * ZB; t < tmax; t += 4 * ZB) {
+        const int off = zoff + t * (ZSTEP / 4);
+#pragma unroll
+        for (int u = 0; u < ZB; ++u) {
+            zp[u] = bload<R>(rp, off + u * ZSTEP);
+            zq[u] = bload<R>(rt, off + u * ZSTEP);
+        }
+#pragma unroll
+        for (int u = 0; u < ZB; ++u) z = cadd(z, cadd(zp[u], zq[u]));
     }
-    for (int jj = w + 32; jj < j; jj += 4) {
-        corr = cfma(V[grc + (int64_t)(p + jj) * n], swv[w][jj], corr);
-        corr = cfma(W[grc + (int64_t)jj * n], svv[w][jj], corr);
+    z = cmul(scale, z);
+#pragma unroll 1
+    for (int c = k; c - k < j; c += 4 * PC) {
+#pragma unroll
+        for (int q = 0; q < PC; ++q) {
+            const int jj = min(c + 4 * q, 63);
+            z = csub(z, cmul(pv[q], sc[w][0][jj]));
+            z = csub(z, cmul(pw[q], sc[w][1][jj]));
+            acc = cfma(pv[q], sc[w][2][jj], acc);
+            acc = cfma(pw[q], sc[w][3][jj], acc);
+        }
+        load_panel();
     }
-    sco[w][lane] = corr;
-    __syncthreads();
+    z = xor_add_v<16, R>(z);
+    z = xor_add_v<32, R>(z);
+    acc = xor_add_v<16, R>(acc);
+    acc = xor_add_v<32, R>(acc);
 
-    // ---- v and w of this block's rows (every wave forms them, wave 0 stores)
-    cx<R> myv = zero, myw = zero;
+    const cx<R> myv = csel(gr == o, mk<R>(1, 0), cmul(ai, scale));
+    cx<R> myw = cfma(mk<R>(a2, 0), myv, cmul(tau, cadd(h, z)));
+    myw = csel(gr == o, wo, myw);
     if (gr < n) {
-        myv = csel(gr == o, mk<R>(1, 0), cmul(ai, scale));
-        if (gr == o) {
-            myw = wo;
-        } else {
-            const cx<R> z = sum4(sy, lane);
-            const cx<R> y = cmul(tau, csub(cfma(scale, z, h), sum4(sco, lane)));
-            myw = cfma(mk<R>(a2, 0), myv, y);
+        if (k == 0) V[gr + (int64_t)i * n] = myv;
+        if (k == 1) W[gr + (int64_t)j * n] = myw;
+        if (k == 2 && update_next) {
+            const cx<R> a = csub(csub(csub(h, acc), cmul(myv, cconj(wo))), myw);
+            if (gr == o)
+                // the diagonal goes to d only: A(o, o) is read as it stood by
+                // every wave of this launch and is not needed afterwards
+                ws.d[b * n + o] = a.x;
+            else
+                A[gr + (int64_t)o * ws.lda] = a;
         }
-        if (w == 0) {
-            V[gr + (int64_t)i * n] = myv;
-            W[gr + (int64_t)j * n] = myw;
-        }
-    }
-    if (w == 0 && Rb == 0 && lane == 0) {
-        ws.e[b * n + i] = beta;
-        ws.tau[b * n + i] = tau;
-    }
-    if (!update_next) return;
-
-    // ---- column o -= V(:, 0:j) conj(W(o, 0:j))^T + W(:, 0:j) conj(V(o, 0:j))^T
-    // (sWo, sVo hold row o of columns 0..j-1 and zero beyond; column j is
-    // this block's v, w with row o = (1, w_o), added last by its wave)
-    cx<R> acc = zero;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int jj = w + 4 * q;
-        acc = cfma(pv[q], cconj(sWo[jj]), acc);
-        acc = cfma(pw[q], cconj(sVo[jj]), acc);
-    }
-    if (j < 32 && ((j - w) & 3) == 0) {
-        acc = cfma(myv, cconj(wo), acc);
-        acc = cfma(myw, cconj(mk<R>(1, 0)), acc);
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (w + 4 * q == j) {
-                pv[q] = myv;
-                pw[q] = myw;
-            }
-    }
-    for (int jj = w + 32; jj <= j; jj += 4) {
-        const bool old = jj < j;
-        const int jc = old ? jj : 0;
-        const cx<R> vr = csel(old, V[grc + (int64_t)(p + jc) * n], myv);
-        const cx<R> wr = csel(old, W[grc + (int64_t)jc * n], myw);
-        acc = cfma(vr, cconj(csel(old, sWo[jj], wo)), acc);
-        acc = cfma(wr, cconj(csel(old, sVo[jj], mk<R>(1, 0))), acc);
-    }
-    s2[w][lane] = acc;
-    __syncthreads();
-    // the updated column (every wave; wave 0 stores it, its diagonal and the
-    // partial norm of rows o + 2 and below)
-    cx<R> an = zero;
-    {
-        R nrm = 0;
-        if (gr < n) {
-            const cx<R> a = csub(h, sum4(s2, lane));
-            if (w == 0) {
-                if (gr == o) {
-                    // the diagonal goes to d only: A(o, o) is read as it stood by
-                    // every workgroup of this launch and is not needed afterwards
-                    ws.d[b * n + o] = a.x;
-                } else {
-                    ws.A[b * ws.sA + gr + (int64_t)o * ws.lda] = a;
-                }
-            }
-            if (gr >= o + 2) {
-                nrm = a.x * a.x + a.y * a.y;
-                an = a;
-            }
-        }
-        if (w == 0) {
-            nrm = dpp_wave_sum(nrm);
-            if (lane == 0) ws.pnorm[b * ws.s_pnorm + (o & 1) * npn + Rb] = nrm;
-        }
-    }
-    // products of the panel columns 0..j with the updated column below its
-    // sub-diagonal: this block's share of the next reflector's panel dots,
-    // eight columns per wave per transposing reduction
-    const int64_t base = b * ws.s_pdot + ((int64_t)(o & 1) * ws.NBmax + Rb) * 2 * ws.nb;
-    {
-        cx<R> t1[8], t2[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            t1[q] = cmulc(pw[q], an);
-            t2[q] = cmulc(pv[q], an);
-        }
-        const cx<R> r1 = transpose_sum8<R>(t1, lane);
-        const cx<R> r2 = transpose_sum8<R>(t2, lane);
-        const int jj = w + 4 * (lane >> 3);
-        if ((lane & 7) == 0 && jj <= j) {
-            ws.pvw[base + jj] = r1;
-            ws.pvv[base + jj] = r2;
-        }
-    }
-    if (j >= 32) {
-        cx<R> t1[8], t2[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int jj = w + 32 + 4 * q;
-            const bool old = jj < j;
-            const int jc = old ? jj : 0;
-            cx<R> vr = V[grc + (int64_t)(p + jc) * n];
-            cx<R> wr = W[grc + (int64_t)jc * n];
-            vr = csel(old, vr, csel(jj == j, myv, zero));
-            wr = csel(old, wr, csel(jj == j, myw, zero));
-            t1[q] = cmulc(wr, an);
-            t2[q] = cmulc(vr, an);
-        }
-        const cx<R> r1 = transpose_sum8<R>(t1, lane);
-        const cx<R> r2 = transpose_sum8<R>(t2, lane);
-        const int jj = w + 32 + 4 * (lane >> 3);
-        if ((lane & 7) == 0 && jj <= j) {
-            ws.pvw[base + jj] = r1;
-            ws.pvv[base + jj] = r2;
+        if (k == 3 && gr == o) {
+            ws.e[b * n + i] = beta;
+            ws.tau[b * n + i] = tau;
         }
     }
 }
 
 }  // namespace
-
-int hetrd_pn(int64_t n) { return (int)((n + RB - 1) / RB); }
 
 template <typename R>
 hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
@@ -854,8 +674,8 @@ hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
             if (e != hipSuccess) return e;
             break;
         }
-        dim3 g1((unsigned)((n - p + RB - 1) / RB), (unsigned)nk);
-        hipLaunchKernelGGL(hetrd_colstart<R>, g1, dim3(RB), 0, st, ws, p);
+        if (p == n - 1)      // order 1: its diagonal, from the panel products' workgroup
+            hipLaunchKernelGGL((hetrd_zhemv<R, false>), dim3(1, (unsigned)nk), dim3(256), 0, st, ws, p, p, 1, 0);
         const int iend = min(p + nb, n - 1);
         for (int i = p; i < iend; ++i) {
             const int o = i + 1, m = n - o;
@@ -878,22 +698,27 @@ hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
             // k-points exceed it (n = 2000 x 16: 9% faster at m = 1500..1750).
             const int rev = i & 1;
             const ProfLaunch pl = prof_launch_begin(PH_HEMV, st);
-            const dim3 gz((unsigned)nch, (unsigned)nk);
+            const int units = dot_units(i - p);
+            const dim3 gz((unsigned)(units + nch), (unsigned)nk);
             if (ws.zch == 1) {
                 if (buf)
-                    launch_timed(pl, hetrd_zhemv_tile<R, true>, gz, dim3(256), st, ws, i, rev);
+                    launch_timed(pl, hetrd_zhemv_tile<R, true>, gz, dim3(256), st, ws, i, p, units, rev);
                 else
-                    launch_timed(pl, hetrd_zhemv_tile<R, false>, gz, dim3(256), st, ws, i, rev);
+                    launch_timed(pl, hetrd_zhemv_tile<R, false>, gz, dim3(256), st, ws, i, p, units, rev);
             } else {
                 if (buf)
-                    launch_timed(pl, hetrd_zhemv<R, true>, gz, dim3(256), st, ws, i, rev);
+                    launch_timed(pl, hetrd_zhemv<R, true>, gz, dim3(256), st, ws, i, p, units, rev);
                 else
-                    launch_timed(pl, hetrd_zhemv<R, false>, gz, dim3(256), st, ws, i, rev);
+                    launch_timed(pl, hetrd_zhemv<R, false>, gz, dim3(256), st, ws, i, p, units, rev);
             }
             prof_launch_end(PH_HEMV, st, pl,
                             (double)sizeof(cx<R>) * 0.5 * (double)m * (double)(m + 1) * (double)nk, 0.0);
             const int upd = (i + 1 < p + nb) && (o <= n - 1);
-            hipLaunchKernelGGL(hetrd_update<R>, dim3((unsigned)NB, (unsigned)nk), dim3(256), 0, st, ws, i, p, upd, nch);
+            // up to 16 row blocks a wave's share of the partial sums is four
+            // terms of each list at most: half the loads of the wider form
+            // (64 reductions of order 1024: 50.8 ms against 51.5)
+            hipLaunchKernelGGL((NB <= 16 ? hetrd_update<R, 4> : hetrd_update<R, 8>), dim3((unsigned)NB, (unsigned)nk),
+                               dim3(256), 0, st, ws, i, p, upd, nch);
         }
         if (p + nb <= n - 1) {
             const int t0 = p + nb;

@@ -74,21 +74,16 @@ struct HetrdWs {
     cx<R>* V; int64_t sV;      // reflectors, n x n, ld n (zero outside the reflector rows)
     cx<R>* W; int64_t sW;      // panel W, n x nb, ld n; the buffer holds 64 n values per problem
     R* d; R* e; cx<R>* tau;    // stride n per problem
-    // The per-column partials below come in two buffers selected by the
-    // parity of the column they describe: the kernel that consumes column
-    // i's partials writes column i+1's in the same launch.
-    R* pnorm; int64_t s_pnorm; // partial squared norms, 2 x hetrd_pn(n)
+    // what the product of a column leaves for its update
+    R* unorm;                        // ||u||^2, one per problem
     cx<R>* ypart; int64_t s_ypart;   // NBmax x NBmax x 64
     cx<R>* ypartT; int64_t s_ypartT; // NBmax x CHmax x 64
-    // panel-dot partials W^H u and V^H u: per problem 2 x NBmax blocks of
-    // [W part (nb), V part (nb)], so pvv = pvw + nb and the block stride is 2 nb
-    cx<R>* pvw; cx<R>* pvv; int64_t s_pdot;
+    cx<R>* pdot; int64_t s_pdot;     // W^H u (nb), V^H u (nb)
     R* qpart; int64_t s_qpart;       // NBmax x CHmax: per-chunk shares of Re(u^H A22 u)
 };
 
 inline int hetrd_nbmax(int64_t n) { return (int)((n - 1 + 63) / 64) > 0 ? (int)((n - 1 + 63) / 64) : 1; }
 inline int hetrd_chmax(int64_t n) { return hetrd_nbmax(n); }   // room for one-tile chunks
-int hetrd_pn(int64_t n);   // partial norms per column (one per 64-row block)
 
 template <typename R>
 hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws, int64_t nk);

@@ -274,6 +274,13 @@ def test_group_reduction_spectrum(n, nk):
     spectrum_check(n, nk, 31 * n + nk)
 
 
+# blocked columns at the edges of the update's batches (16 panel columns, 32
+# and 64 per panel) and of its row blocks, down to the resident reduction
+@pytest.mark.parametrize("n,nb", [(193, 1), (150, 5), (257, 16), (258, 17), (322, 33), (200, 64)])
+def test_blocked_column_edges(n, nb):
+    test_hetrd_matches_oracle(n, nb)
+
+
 def test_group_given_up_is_reduced_in_memory():
     """No member waits for the others: every group is given up and the
     problems are reduced with the matrix in memory, with the same results."""
