@@ -370,14 +370,15 @@ __global__ __launch_bounds__(256, 3) void hetrd_zhemv_tile(HetrdWs<R> ws, int i,
     __shared__ R sq[ZCH];
     const bool diag_tile = (Rb == C);
     cx<R> yd = czero<cx<R>>();
-    auto group = [&](int g, auto next) {
-        constexpr bool NEXT = decltype(next)::value;
+    // WHOLE: an entry of every row and column (most tiles): no masks
+    auto group = [&](int g, auto next, auto whole) {
+        constexpr bool NEXT = decltype(next)::value, WHOLE = decltype(whole)::value;
         const int64_t gc0 = gcb + g * 8;
 #pragma unroll
         for (int cc = 0; cc < 8; ++cc) {
             const int64_t gc = gc0 + cc;
-            const bool ok = row_ok && gc < n && (!diag_tile || gr >= gc);
-            const bool diag = diag_tile && (gr == gc);
+            const bool ok = WHOLE || (row_ok && gc < n && (!diag_tile || gr >= gc));
+            const bool diag = !WHOLE && diag_tile && (gr == gc);
             cx<R> x;
             x.x = ok ? a[cc].x : (R)0;
             x.y = (ok && !diag) ? a[cc].y : (R)0;
@@ -396,8 +397,13 @@ __global__ __launch_bounds__(256, 3) void hetrd_zhemv_tile(HetrdWs<R> ws, int i,
         if (lane < 8) sT[w][g * 8 + lane] = cs;
         __builtin_amdgcn_wave_barrier();
     };
-    group(g0, std::true_type{});
-    group(g0 + 1, std::false_type{});
+    if (!diag_tile && o + (Rb + 1) * ZT <= n) {
+        group(g0, std::true_type{}, std::true_type{});
+        group(g0 + 1, std::false_type{}, std::true_type{});
+    } else {
+        group(g0, std::true_type{}, std::false_type{});
+        group(g0 + 1, std::false_type{}, std::false_type{});
+    }
     // the four waves' shares of the tile's direct part
     sP[w][0][lane] = yd;
     R qd = uR.x * yd.x + uR.y * yd.y;
