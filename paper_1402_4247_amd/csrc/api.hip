@@ -92,7 +92,7 @@ struct SolvePlan {
     size_t d, e, sS, wA, unorm, Zr, Qs, Vsec;
     size_t dc_es, dc_onrm, dc_D0, dc_D1, dc_sd, dc_sz, dc_ndd, dc_ndz, dc_dfd, dc_rotc, dc_rots, dc_rho, dc_tauv,
         dc_lam, dc_zhat;
-    size_t dc_kcnt, dc_ndcnt, dc_nrot, dc_perm, dc_ndx, dc_dfx, dc_rota, dc_rotb, dc_orgi, dc_cmap;
+    size_t dc_kcnt, dc_ndcnt, dc_ksplit, dc_perm, dc_ndx, dc_dfx, dc_rota, dc_rotb, dc_orgi, dc_cmap;
     size_t status, bz;
     // mixed precision: complex64 tridiagonalisation / back-transformation
     // buffers and the FP64 refinement scratch (size 0 in the FP64 form)
@@ -146,7 +146,7 @@ SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots
                     &p.dc_rotc, &p.dc_rots, &p.dc_rho, &p.dc_tauv, &p.dc_lam, &p.dc_zhat};
     for (size_t* q : dv) *q = L.add(r * n * nk);
     p.dc_onrm = L.add(r * nk);
-    size_t* iv[] = {&p.dc_kcnt, &p.dc_ndcnt, &p.dc_nrot, &p.dc_perm, &p.dc_ndx, &p.dc_dfx, &p.dc_rota, &p.dc_rotb,
+    size_t* iv[] = {&p.dc_kcnt, &p.dc_ndcnt, &p.dc_ksplit, &p.dc_perm, &p.dc_ndx, &p.dc_dfx, &p.dc_rota, &p.dc_rotb,
                     &p.dc_orgi, &p.dc_cmap};
     for (size_t* q : iv) *q = L.add(i4 * n * nk);
     p.status = L.add(i4 * nk);
@@ -237,7 +237,7 @@ DcWs dc_ws(const SolvePlan& p, void* w, const double* d, const double* e, int* s
     c.D[1] = at<double>(w, p.dc_D1);
     c.sQ = p.n * p.n;
     c.Vsec = at<double>(w, p.Vsec);
-    c.kcnt = at<int>(w, p.dc_kcnt); c.ndcnt = at<int>(w, p.dc_ndcnt); c.nrot = at<int>(w, p.dc_nrot);
+    c.kcnt = at<int>(w, p.dc_kcnt); c.ndcnt = at<int>(w, p.dc_ndcnt); c.ksplit = at<int>(w, p.dc_ksplit);
     c.rho = at<double>(w, p.dc_rho);
     c.perm = at<int>(w, p.dc_perm); c.sd = at<double>(w, p.dc_sd); c.sz = at<double>(w, p.dc_sz);
     c.ndx = at<int>(w, p.dc_ndx); c.ndd = at<double>(w, p.dc_ndd); c.ndz = at<double>(w, p.dc_ndz);

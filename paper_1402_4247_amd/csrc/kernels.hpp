@@ -107,11 +107,12 @@ struct DcWs {
     double* D[2];        // n per problem
     double* Q[2]; int64_t sQ;  // n x n per problem; set by stedc()
     double* Vsec;        // n x n per problem
-    int* kcnt; int* ndcnt; int* nrot; double* rho;   // per segment, stored at its first index
+    int* kcnt; int* ndcnt; double* rho;   // per segment, stored at its first index
+    int* ksplit;         // per segment, at its first two: poles of the first half alone, these and the mixed ones
     int* perm; double* sd; double* sz;
     int* ndx; double* ndd; double* ndz;
     int* dfx; double* dfd;
-    int* rota; int* rotb; double* rotc; double* rots;
+    int* rota; int* rotb; double* rotc; double* rots;   // deflation rotations; then rota: the poles' places, rotb: their columns
     int* orgi; double* tauv; double* lam; double* zhat; int* cmap;
     int64_t s_w;         // stride of the eigenvalue output
     int* status;         // per problem (may be null)

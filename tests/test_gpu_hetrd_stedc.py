@@ -318,3 +318,14 @@ def merge_cases():
 @pytest.mark.parametrize("name,d,e", merge_cases(), ids=lambda x: x if isinstance(x, str) else "")
 def test_stedc_merges(name, d, e):
     test_stedc_matches_oracle(name, d, e)
+
+
+# the product of a merge takes one half's columns and the mixed ones for rows of
+# that half: halves at and off the edges of its 64-row tiles, with deflation
+# rotations inside each half and across them
+@pytest.mark.parametrize("n", [66, 127, 128, 129, 191, 260, 400])
+@pytest.mark.parametrize("coupling", [1.0, 1e-6, 1e-15])
+def test_stedc_halves(n, coupling):
+    rng = np.random.default_rng(n)
+    d = np.tile([1.0, 2.0, 3.0, 3.0], (n + 3) // 4)[:n] + 1e-3 * rng.integers(0, 3, n)
+    test_stedc_matches_oracle("halves", d, coupling * rng.uniform(0.1, 0.4, n - 1))
