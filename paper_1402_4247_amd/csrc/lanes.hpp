@@ -101,20 +101,6 @@ __device__ inline double lane_read(double v, int l)
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                             __builtin_amdgcn_readlane(__double2loint(v), l));
 }
-// broadcast of lane Q of each quad
-template <int Q, typename T> __device__ inline T quad_bcast(T v)
-{
-    static_assert(Q >= 0 && Q < 4, "lane of a quad");
-    constexpr int C = Q | (Q << 2) | (Q << 4) | (Q << 6);
-    if constexpr (sizeof(T) == 8) {
-        const double d = v;
-        return __hiloint2double(dpp<C>(__double2hiint(d)), dpp<C>(__double2loint(d)));
-    } else if constexpr (sizeof(T) == 4 && __is_same(T, float)) {
-        return __int_as_float(dpp<C>(__float_as_int(v)));
-    } else {
-        return dpp<C>(v);
-    }
-}
 
 // sum (product) over aligned groups of G = 2..16 lanes, butterfly in
 // ascending order: every lane of a group ends with the same bits

@@ -3,11 +3,10 @@
 // eigenvector normalisation (Eigen_HH's last step) fused with Part 2's
 // rearrangement of S (x_j = u_j / sqrt(s_j)) and its definiteness check, and
 // the triangular factor of a block of reflectors (compact WY).
-#include <utility>
-
 #include "common.hpp"
 #include "lanes.hpp"
 #include "kernels.hpp"
+#include "reflector.hpp"
 
 namespace kgev {
 
@@ -133,66 +132,105 @@ __global__ __launch_bounds__(256) void k_normalize_cols_real(int64_t n, double* 
 
 // T (kk x kk, upper) for reflectors c0..c0+kk-1 (compact WY):
 // T(j, j) = tau_j, T(0:j, j) = -tau_j T(0:j, 0:j) G(0:j, j), G = V_b^H V_b.
+// One workgroup per (block, k-point) makes T_b from G_b (ld kb) where the pair's
+// factor T_B wants it (block blk & 1 on the diagonal of pair blk / 2, ld 2 kb),
+// and the first of a pair clears the block below it.
+//
+// The recurrence runs in the four diagonal 16-blocks, one wave each, four lanes
+// a row; then halves of 16 and of 32 columns are joined,
+//   T_12 = -T_1 (G_12 T_2),
+// on MFMA.  G (strictly upper) and T (upper) share one LDS array, G(r, c) at
+// [c][r] and T(r, c) at [r][c].  Bound by instruction fetch and LDS latency: the
+// recurrence over all 64 columns from registers was 31 KB of code that ran once:
+// 24.5 us and a launch of 10.6 us to put T_b in its place, now 19 us (two blocks).
 constexpr int KBMAX = 64;
-// Step q of the T recurrence below, for one lane of row r's quad: acc[m]
-// holds the running sum of column part + 4m.  q is a template argument so
-// that acc stays in registers (every index into it is a constant).
-template <int Q, typename R>
-__device__ inline void larft_step(cx<R> (&acc)[KBMAX / 4], const cx<R> (*gl)[KBMAX + 1], const cx<R>* tl, int r,
-                                  int part, bool store, cx<R>* Tb, int kb)
-{
-    const cx<R> tq = tl[Q];
-    // in the lane with part == Q % 4, acc[Q / 4] is column Q's full sum
-    cx<R> t = csel(r < Q, cscale(cmul(tq, acc[Q >> 2]), (R)-1), csel(r == Q, tq, czero<cx<R>>()));
-    t.x = quad_bcast<Q & 3>(t.x);
-    t.y = quad_bcast<Q & 3>(t.y);
-    if (store) Tb[r + (int64_t)Q * kb] = t;
-    // the columns j > Q (a column j <= Q of a lane's set is finished and no
-    // longer read, so the first group holding a j > Q is the bound)
-#pragma unroll
-    for (int m = (Q < 3 ? 0 : (Q - 3) / 4 + 1); m < KBMAX / 4; ++m)
-        acc[m] = cfma(t, gl[part + 4 * m][Q], acc[m]);
-}
-template <typename R, int... Q>
-__device__ inline void larft_steps(std::integer_sequence<int, Q...>, int kk, cx<R> (&acc)[KBMAX / 4],
-                                   const cx<R> (*gl)[KBMAX + 1], const cx<R>* tl, int r, int part, bool store,
-                                   cx<R>* Tb, int kb)
-{
-    ((Q < kk ? (larft_step<Q, R>(acc, gl, tl, r, part, store, Tb, kb), 0) : 0), ...);
-}
-// T factors of every reflector block at once, one workgroup per (block,
-// k-point): T_b (kk x kk, ld kb) from G_b = V_b^H V_b (ld kb).  Row r of T
-// (T(r, j) = -tau_j sum_{q<j} T(r, q) G(q, j), T(r, r) = tau_r, zero below
-// the diagonal) depends on row r alone; it is taken by the quad of lanes
-// 4r .. 4r+3, lane p of which keeps the running sums of the columns
-// j = p + 4m in registers.  Step q finishes T(r, q) in the lane that owns
-// column q, broadcasts it over the quad and adds its term to every later
-// column's sum (right-looking), so the serial chain per step is one complex
-// product, one broadcast and one fused multiply-add, and no step waits for
-// memory written by another.
 template <typename R>
-__global__ __launch_bounds__(256) void k_larft_all(int kb, int nref, const cx<R>* G, int64_t sG,
-                                                   const cx<R>* tau, int64_t stau, cx<R>* T, int64_t strT)
+__global__ __launch_bounds__(256) void k_larft_all(int kb, int nref, const cx<R>* G, int64_t sG, const cx<R>* tau,
+                                                   int64_t stau, cx<R>* TB, int64_t sTB)
 {
-    __shared__ cx<R> gl[KBMAX][KBMAX + 1];   // gl[col][row] = G(row, col)
+    using M_ = Mfma<R>;
+    __shared__ cx<R> S[KBMAX][KBMAX + 1];
+    __shared__ cx<R> X[KBMAX / 2][KBMAX / 2 + 1];
     __shared__ cx<R> tl[KBMAX];
     const int blk = blockIdx.x;
     const int64_t b = blockIdx.y;
     const int c0 = blk * kb;
     const int kk = nref - c0 < kb ? nref - c0 : kb;
-    const int tid = threadIdx.x, r = tid >> 2, part = tid & 3;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const cx<R> zero = czero<cx<R>>();
     const cx<R>* g = G + b * sG + (int64_t)blk * kb * kb;
-    for (int e = tid; e < kk * kk; e += 256) {
-        const int rr = e % kk, cc = e / kk;
-        gl[cc][rr] = g[rr + (int64_t)cc * kb];
+    // columns and rows beyond kk are zero, which leaves the others alone
+#pragma unroll 8
+    for (int c = w; c < KBMAX; c += 4) {
+        const bool in = lane < c && c < kk;
+        const cx<R> v = g[in ? lane + (int64_t)c * kb : 0];
+        if (lane < c) S[c][lane] = csel(in, v, zero);
     }
-    if (tid < kk) tl[tid] = tau[b * stau + c0 + tid];
+    if (tid < KBMAX) tl[tid] = csel(tid < kk, tau[b * stau + c0 + (tid < kk ? tid : 0)], zero);
     __syncthreads();
-    cx<R> acc[KBMAX / 4];
+    {
+        const int base = 16 * w, r = base + (lane >> 2), part = lane & 3;
+#pragma unroll 1
+        for (int c = base; c < base + 16; ++c) {
+            cx<R> acc = zero;
 #pragma unroll
-    for (int m = 0; m < KBMAX / 4; ++m) acc[m] = czero<cx<R>>();
-    cx<R>* Tb = T + b * strT + (int64_t)blk * kb * kb;
-    larft_steps<R>(std::make_integer_sequence<int, KBMAX>{}, kk, acc, gl, tl, r, part, part == 0 && r < kk, Tb, kb);
+            for (int m = 0; m < 4; ++m) {
+                const int q = base + part + 4 * m;
+                if (q >= r && q < c) acc = cfma(S[r][q], S[c][q], acc);
+            }
+            acc.x = xor_sum<2>(xor_sum<1>(acc.x));
+            acc.y = xor_sum<2>(xor_sum<1>(acc.y));
+            const cx<R> t = tl[c];
+            if (part == 0 && r <= c) S[r][c] = csel(r == c, t, cscale(cmul(t, acc), (R)-1));
+            wave_sync();
+        }
+    }
+    __syncthreads();
+    const int li = lane & 15, lk = lane >> 4;
+#pragma unroll 1
+    for (int h = 16; h < KBMAX; h *= 2) {
+        // this wave's 16 x 16 tile of a pair's product, if there is one
+        const int per = (h / 16) * (h / 16), pair = w / per, ti = w % per % (h / 16), tj = w % per / (h / 16);
+        const int b1 = pair * 2 * h, b2 = b1 + h;
+        const bool mine = b2 < KBMAX;
+        const int r = 16 * ti + li, c = 16 * tj + li;
+        typename M_::acc_t re, im;
+        auto product = [&](auto fa, auto fb) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) re[q] = im[q] = (R)0;
+#pragma unroll 1
+            for (int k = lk; k < h; k += 4) {
+                const cx<R> x = fa(k), y = fb(k);
+                re = M_::mma(x.x, y.x, re);
+                im = M_::mma(x.x, y.y, im);
+                re = M_::mma(-x.y, y.y, re);
+                im = M_::mma(x.y, y.x, im);
+            }
+        };
+        if (mine) {
+            product([&](int k) { return S[b2 + k][b1 + r]; },
+                    [&](int k) { return csel(k <= c, S[b2 + k][b2 + c], zero); });
+#pragma unroll
+            for (int q = 0; q < 4; ++q) X[pair * h + 16 * ti + M_::row(lk, q)][c] = mk<R>(re[q], im[q]);
+        }
+        __syncthreads();
+        if (mine) {
+            product([&](int k) { return csel(r <= k, S[b1 + r][b1 + k], zero); },
+                    [&](int k) { return X[pair * h + k][c]; });
+#pragma unroll
+            for (int q = 0; q < 4; ++q) S[b1 + 16 * ti + M_::row(lk, q)][b2 + c] = mk<R>(-re[q], -im[q]);
+        }
+        __syncthreads();
+    }
+    const int64_t ld = 2 * kb;
+    cx<R>* t = TB + b * sTB + (int64_t)(blk >> 1) * 4 * kb * kb + (blk & 1) * (kb + kb * ld);
+#pragma unroll 4
+    for (int c = w; c < kk; c += 4)
+        if (lane < kk) t[lane + c * ld] = csel(lane <= c, S[lane][c], zero);
+    if ((blk & 1) == 0)
+        for (int c = w; c < kb; c += 4)
+            if (lane < kb) t[kb + lane + c * ld] = zero;
 }
 
 }  // namespace
@@ -400,33 +438,10 @@ int64_t unmtr_work_elems(int64_t n, int kb)
     const int64_t nblk = (n - 1 + kb - 1) / kb, npair = (nblk + 1) / 2;
     const int64_t kb2 = (int64_t)kb * kb;
     return nblk * kb2                 // G of the kb-blocks
-           + nblk * kb2               // T of the kb-blocks
            + npair * 4 * kb2          // T of the 2kb-blocks
            + 2 * npair * kb2          // V_1^H V_2 and (V_1^H V_2) T_2 per pair
            + 2 * 2 * (int64_t)kb * n; // W1, W2 (2kb x n)
 }
-
-namespace {
-// T_B of every pair: diagonal blocks copied from the kb-block factors, the
-// lower-left block zeroed (the upper-right block is written by products)
-template <typename R>
-__global__ __launch_bounds__(256) void k_pair_t(int kb, int nblk, const cx<R>* T, int64_t sT, cx<R>* TB, int64_t sTB)
-{
-    const int q = blockIdx.x;
-    const int64_t b = blockIdx.y;
-    const int b1 = 2 * q, b2 = 2 * q + 1;
-    const int64_t kb2 = (int64_t)kb * kb, ld = 2 * kb;
-    cx<R>* t = TB + b * sTB + (int64_t)q * 4 * kb2;
-    const cx<R>* t1 = T + b * sT + (int64_t)b1 * kb2;
-    const cx<R>* t2 = T + b * sT + (int64_t)b2 * kb2;
-    for (int e = threadIdx.x; e < kb * kb; e += 256) {
-        const int r = e % kb, c = e / kb;
-        t[r + (int64_t)c * ld] = t1[r + (int64_t)c * kb];
-        t[(kb + r) + (int64_t)c * ld] = czero<cx<R>>();
-        if (b2 < nblk) t[(kb + r) + (int64_t)(kb + c) * ld] = t2[r + (int64_t)c * kb];
-    }
-}
-}  // namespace
 
 template <typename R>
 hipError_t unmtr(hipStream_t st, int64_t n, const cx<R>* V, int64_t sV, const cx<R>* tau, int64_t stau, cx<R>* U,
@@ -439,8 +454,7 @@ hipError_t unmtr(hipStream_t st, int64_t n, const cx<R>* V, int64_t sV, const cx
     const int64_t nblk = (nref + kb - 1) / kb, nfull = nref / kb, npair = (nblk + 1) / 2;
     const int64_t kb2 = (int64_t)kb * kb, ld2 = 2 * kb;
     cx<R>* G = work;
-    cx<R>* T = G + nblk * kb2;
-    cx<R>* TB = T + nblk * kb2;
+    cx<R>* TB = G + nblk * kb2;
     cx<R>* G12 = TB + npair * 4 * kb2;
     cx<R>* X12 = G12 + npair * kb2;
     cx<R>* W1 = X12 + npair * kb2;
@@ -462,23 +476,19 @@ hipError_t unmtr(hipStream_t st, int64_t n, const cx<R>* V, int64_t sV, const cx
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_larft_all<R>, dim3((unsigned)nblk, (unsigned)nk), dim3(256), 0, st, kb, (int)nref, G, sw,
-                       tau, stau, T, sw);
+                       tau, stau, TB, sw);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // T of the 2kb-blocks: diagonal blocks, then T12 = -T_1 (V_1^H V_2) T_2
-    hipLaunchKernelGGL(k_pair_t<R>, dim3((unsigned)npair, (unsigned)nk), dim3(256), 0, st, kb, (int)nblk, T, sw, TB,
-                       sw);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    // T12 = -T_1 (V_1^H V_2) T_2 of the 2kb-blocks
     const int64_t nfp = nfull / 2;               // pairs of two full kb-blocks
     if (nfp > 0) {
         e = cgemm_batch2<R>(st, 'C', 'N', kb, kb, n - 1, one, V + 1, n, sV, 2 * kb * n, V + 1 + kb * n, n, sV,
                             2 * kb * n, zero, G12, kb, sw, kb2, nk, nfp);
         if (e != hipSuccess) return e;
-        e = cgemm_batch2<R>(st, 'N', 'N', kb, kb, kb, one, G12, kb, sw, kb2, T + kb2, kb, sw, 2 * kb2, zero, X12, kb,
-                            sw, kb2, nk, nfp);
+        e = cgemm_batch2<R>(st, 'N', 'N', kb, kb, kb, one, G12, kb, sw, kb2, TB + kb + kb * ld2, ld2, sw, 4 * kb2,
+                            zero, X12, kb, sw, kb2, nk, nfp);
         if (e != hipSuccess) return e;
-        e = cgemm_batch2<R>(st, 'N', 'N', kb, kb, kb, mone, T, kb, sw, 2 * kb2, X12, kb, sw, kb2, zero, TB + kb * ld2,
+        e = cgemm_batch2<R>(st, 'N', 'N', kb, kb, kb, mone, TB, ld2, sw, 4 * kb2, X12, kb, sw, kb2, zero, TB + kb * ld2,
                             ld2, sw, 4 * kb2, nk, nfp);
         if (e != hipSuccess) return e;
     }
@@ -489,10 +499,10 @@ hipError_t unmtr(hipStream_t st, int64_t n, const cx<R>* V, int64_t sV, const cx
         e = cgemm<R>(st, 'C', 'N', kb, kk2, n - 1, one, V + 1 + c1 * n, n, sV, V + 1 + c2 * n, n, sV, zero,
                      G12 + q * kb2, kb, sw, nk, false);
         if (e != hipSuccess) return e;
-        e = cgemm<R>(st, 'N', 'N', kb, kk2, kk2, one, G12 + q * kb2, kb, sw, T + (2 * q + 1) * kb2, kb, sw, zero,
+        e = cgemm<R>(st, 'N', 'N', kb, kk2, kk2, one, G12 + q * kb2, kb, sw, TB + q * 4 * kb2 + kb + kb * ld2, ld2, sw, zero,
                      X12 + q * kb2, kb, sw, nk, false);
         if (e != hipSuccess) return e;
-        e = cgemm<R>(st, 'N', 'N', kb, kk2, kb, mone, T + 2 * q * kb2, kb, sw, X12 + q * kb2, kb, sw, zero,
+        e = cgemm<R>(st, 'N', 'N', kb, kk2, kb, mone, TB + q * 4 * kb2, ld2, sw, X12 + q * kb2, kb, sw, zero,
                      TB + q * 4 * kb2 + kb * ld2, ld2, sw, nk, false);
         if (e != hipSuccess) return e;
     }

@@ -169,6 +169,13 @@ def test_eigen_hh_matches_oracle(n):
         assert np.abs(Y[q].conj().T @ Y[q] - np.eye(n)).max() <= 32 * n * EPS
 
 
+# the triangular factors at the edges of their 16- and 32-column halves and of
+# the 64-column blocks, alone, in pairs and left over
+@pytest.mark.parametrize("n", [3, 17, 18, 33, 34, 50, 65, 66, 82, 129, 146, 193, 194])
+def test_back_transform_block_edges(n):
+    test_back_transform_matches_oracle(n)
+
+
 def gpu_stebz(ds, es):
     kg = K()
     nk, n = ds.shape
