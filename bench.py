@@ -166,13 +166,13 @@ def roofline_object(prof, phase, elapsed, note, traffic, K):
     # four 64 x 64 tiles per workgroup (hetrd_zhemv) or one (hetrd_zhemv_tile),
     # chosen per column by the workgroup count: the phase covers both
     base = {"bound": "hbm" if hemv else "mfma",
-            "kernel": "hetrd_zhemv + hetrd_zhemv_tile" if hemv else "cgemm_kernel",
+            "kernel": "hetrd_zhemv + hetrd_zhemv_tile" if hemv else "zgemm_dma + cgemm_kernel",
             "peak": PEAK_HBM_GBS if hemv else PEAK_FP64_TFLOPS, "unit": "GB/s" if hemv else "TFLOP/s"}
     if prof is None:
         return {**base, "achieved": None, "frac": None, "traffic": None,
                 "measured_on": "not measured (kernel timing off)"}
     if prof["launches"] == 0:
-        # at orders up to 128 the LDS-resident tail kernel reduces the whole
+        # at small orders one launch with the matrix in registers reduces the whole
         # matrix, so there is no Hermitian-product launch
         return {**base, "achieved": None, "frac": None, "traffic": None, "launches": 0, "timed_launches": 0,
                 "measured_on": "no launch of the kernel at this order", "share_of_step": 0.0}
