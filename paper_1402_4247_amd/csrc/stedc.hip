@@ -828,22 +828,24 @@ __global__ __launch_bounds__(64) void dc_vectors_place(DcWs ws, int t, int rb, i
 // FP64 MFMA with a column gather on A and a column scatter on C.  The columns
 // are ordered by the half of the rows they live in and a tile has rows of one
 // half, so it takes only that half's columns and the mixed ones: half the work
-// (top merge of n = 2000: 343 -> 192 us, of 16 of them 4.07 -> 2.48 ms).  Column
-// tiles go first in the grid: workgroups go round the dice and shader engines,
-// which would each get the same few row tiles otherwise.
+// (top merge of n = 2000: 343 -> 192 us, of 16 of them 4.07 -> 2.48 ms).
+// Workgroups go round the dice and shader engines: problems go first in the
+// grid, so that a die reads few of them (2.55 -> 2.33 ms), then column tiles, as
+// each engine would get the same few row tiles otherwise.  Loads two K steps
+// ahead took 118 registers and were slower (2.63 ms).
 constexpr int DB = 64, DK = 16;
 __global__ __launch_bounds__(256) void dc_gemm(DcWs ws, int t, int rb, int wb, int tiles, int half_tiles)
 {
     __shared__ double sA[2][DK][DB + 1];
     __shared__ double sB[2][DK][DB + 1];
-    const int64_t b = blockIdx.z;
+    const int64_t b = blockIdx.x % (unsigned)ws.nk;
     const int64_t n = ws.n;
     const Seg g = seg_of(blockIdx.y, n, t);
     const int ns = (int)(g.e - g.s);
     if (ns < 2) return;
     const int64_t s = g.s;
     const int K = ws.kcnt[b * n + s];
-    const int tm = blockIdx.x / tiles, tn = blockIdx.x % tiles;
+    const int tile = (int)(blockIdx.x / (unsigned)ws.nk), tm = tile / tiles, tn = tile % tiles;
     // row tiles of the first half, then of the second; rows i0..ie-1
     const bool second = tm >= half_tiles;
     const int n1 = (int)(g.mid - g.s), ie = second ? ns : n1;
@@ -967,6 +969,7 @@ __global__ __launch_bounds__(256) void dc_finish(DcWs ws, int fb, double* w)
 hipError_t stedc(hipStream_t st, const DcWs& ws0, double* w, double* Z, double* Qscratch, int64_t nk)
 {
     DcWs ws = ws0;
+    ws.nk = nk;
     const int64_t n = ws.n;
     if (n < 1 || nk < 1) return hipSuccess;
     const int L = dc_leaf_depth(n);
@@ -994,8 +997,8 @@ hipError_t stedc(hipStream_t st, const DcWs& ws0, double* w, double* Z, double* 
                            wb, (int)nsmax);
         const int tiles = (int)((nsmax + DB - 1) / DB);
         const int half_tiles = (int)((n + 2 * segs - 1) / (2 * segs) + DB - 1) / DB;
-        hipLaunchKernelGGL(dc_gemm, dim3((unsigned)(2 * half_tiles * tiles), segs, (unsigned)nk), dim3(256), 0, st, ws, t,
-                           rb, wb, tiles, half_tiles);
+        hipLaunchKernelGGL(dc_gemm, dim3((unsigned)(nk * (2 * half_tiles * tiles)), segs), dim3(256), 0, st, ws, t, rb, wb,
+                           tiles, half_tiles);
     }
     hipLaunchKernelGGL(dc_finish, dim3((unsigned)((n + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws, L & 1, w);
     return hipGetLastError();
