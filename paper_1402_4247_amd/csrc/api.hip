@@ -139,8 +139,8 @@ SolvePlan make_plan(int64_t n, int64_t nk, int nb, bool mixed = false, int slots
     p.sS = L.add(r * n * nk);
     p.wA = L.add(r * n * nk);
     p.unorm = L.add(r * nk);
-    p.Zr = L.add(r * nn * nk);
-    p.Qs = L.add(r * nn * nk);
+    p.Zr = L.add(r * nn * nk);                 // (Zr and Qs also hold the matrix of a reduction whose
+    p.Qs = L.add(r * nn * nk);                 // group was given up, before the tridiagonal eigensolve)
     p.Vsec = L.add(r * nn * nk);
     size_t* dv[] = {&p.dc_es, &p.dc_D0, &p.dc_D1, &p.dc_sd, &p.dc_sz, &p.dc_ndd, &p.dc_ndz, &p.dc_dfd,
                     &p.dc_rotc, &p.dc_rots, &p.dc_rho, &p.dc_tauv, &p.dc_lam, &p.dc_zhat};
@@ -198,6 +198,9 @@ HetrdWs<float> hetrd_ws32(const SolvePlan& p, void* w)
     h.ypartT = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_ypartT); h.s_ypartT = (int64_t)p.NBmax * p.CHmax * 64;
     h.pdot = reinterpret_cast<float2*>(static_cast<char*>(w) + p.f_pdot); h.s_pdot = 2 * (int64_t)p.nb;
     h.qpart = reinterpret_cast<float*>(static_cast<char*>(w) + p.f_qpart); h.s_qpart = (int64_t)p.NBmax * p.CHmax;
+    h.Fr = reinterpret_cast<float*>(static_cast<char*>(w) + p.Zr);
+    h.Fi = reinterpret_cast<float*>(static_cast<char*>(w) + p.Qs);
+    h.sF = p.n * p.n;
     return h;
 }
 
@@ -222,6 +225,7 @@ HetrdWs<double> hetrd_ws(const SolvePlan& p, void* w, double2* A, int64_t lda, i
     h.ypartT = at<double2>(w, p.ypartT); h.s_ypartT = (int64_t)p.NBmax * p.CHmax * 64;
     h.pdot = at<double2>(w, p.pdot); h.s_pdot = 2 * (int64_t)p.nb;
     h.qpart = at<double>(w, p.qpart); h.s_qpart = (int64_t)p.NBmax * p.CHmax;
+    h.Fr = at<double>(w, p.Zr); h.Fi = at<double>(w, p.Qs); h.sF = p.n * p.n;
     return h;
 }
 

@@ -24,8 +24,8 @@
 // A22 -= V W^H + W V^H (Procedure 6, on MFMA).
 // Once a panel's trailing matrix is small enough, the rest of the reduction
 // runs in one launch, unblocked, with the matrix in registers (hetrd_res.hip).
-// No atomics: every sum is taken in a fixed order, so results are bitwise
-// reproducible run to run.
+// Every sum is taken in a fixed order (no atomic adds to a value; a group's
+// members meet through atomics), so results are bitwise reproducible run to run.
 #include <type_traits>
 
 #include "common.hpp"

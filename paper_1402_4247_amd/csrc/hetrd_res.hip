@@ -28,7 +28,8 @@
 // five barriers a column.  Four threads per row in B (every wave taking part)
 // measured 269 us, __syncthreads() for both barriers (which waits for the
 // stores of v) with run-time tile bounds 359 us.
-// Sums are taken in a fixed order: results are bitwise reproducible.
+// Sums are taken in a fixed order, here and in the groups below, also where a
+// group is given up: results are bitwise reproducible.
 #include <stdint.h>
 
 #include <type_traits>
@@ -46,7 +47,13 @@ namespace {
 // how long a workgroup of a group waits for the others to start, in ticks of
 // the 100 MHz wall clock: 200 ms
 constexpr int64_t GROUP_WAIT_TICKS = 20000000;
+// how often a member looks again for the others' columns before it gives up
+// (a constant: as an argument it cost 45 to 70 ns a column)
+constexpr int POLLS_MAX = 1 << 21;
+// set by tests: 0 gives every group up before it starts
 thread_local int64_t tl_group_wait_ticks = GROUP_WAIT_TICKS;
+// set by tests: a launch lacks its last member
+thread_local bool tl_group_lacks_one = false;
 
 constexpr int RT_T = 512;           // threads of a workgroup
 constexpr int RT_W = RT_T / WAVE;   // waves: tile row R belongs to wave R mod RT_W
@@ -313,8 +320,8 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
 // one group of a launch is partly placed; a member waits for the others to
 // start for a bounded time, after which the group is given up (the last one to
 // arrive and the one that gives up decide by an atomic on the same word) and
-// hetrd_memory reduces that problem instead.  Once all have started, every
-// wait ends; the poll is bounded all the same.  A group has at most 64 members
+// hetrd_memory reduces that problem instead, to the same bits.  Once all have
+// started, every wait ends; the poll is bounded all the same.  A group has at most 64 members
 // of the 256 compute units, so four launches on different streams (the
 // hardware queues of a process) cannot hold each other's partly placed groups.
 //
@@ -327,7 +334,6 @@ constexpr uint64_t SENTINEL = 0xFFF4DEADFFF4BEEFull;   // two NaNs as well for a
 constexpr uint32_t GIVEN_UP = 0x80000000u;
 constexpr int GROUP_MAX = 64;             // members of a group at most
 constexpr int GROUP_MIN = 160;            // orders up to this stay with panels and one workgroup
-constexpr int POLLS_MAX = 1 << 21;
 
 template <typename T> __device__ __attribute__((always_inline)) inline T load_agent(const T* p)
 {
@@ -377,12 +383,12 @@ template <typename R> __device__ inline cx<R> value_of(const uint64_t* u)
 }
 
 template <typename R>
-__global__ __launch_bounds__(256) void k_exchange_init(HetrdWs<R> ws, int M)
+__global__ __launch_bounds__(256) void k_exchange_init(HetrdWs<R> ws, int M, uint32_t started, uint32_t started_last)
 {
     const Exchange<R> ex(ws, blockIdx.y, M);
     const int words = 2 + 3 * ex.slot_words();
     const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q < words) ex.base[q] = q < 2 ? 0 : SENTINEL;
+    if (q < words) ex.base[q] = q > 1 ? SENTINEL : q == 1 ? 0 : blockIdx.y + 1 < gridDim.y ? started : started_last;
 }
 
 template <typename R, int RT, int KC>
@@ -720,71 +726,255 @@ __global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G
     }
 }
 
-// The problems whose group was given up: one workgroup each, with the
-// trailing matrix (lower triangle) in memory.  Reached only when other work
-// holds the GPU's compute units for longer than the members' wait, so it is
-// written for being right, not for speed.
+// The problems whose group was given up: one workgroup each, with the same
+// operations on the same values in the same order as a group's members, so
+// the results have the same bits whether a group ran or not.  The trailing
+// matrix (both triangles, as a group holds it) lies in the buffers of the
+// tridiagonal eigensolver, which has not run yet: real parts in Fr, imaginary
+// parts in Fi, tile by tile down each tile column, a tile in the order of its
+// lanes.  Sixteen waves: wave w takes the tile rows w mod 8, w mod 8 + 8, ... of two
+// of four tile columns at a time, whose sums are joined through LDS.  The rows of
+// phase B belong to the threads of a member's workgroup (s, s + 512).
+//
+// Reached only when other work holds the GPU's compute units for longer than
+// the members' wait.  Bound by one compute unit's traffic to memory, which the
+// matrix crosses twice a column: 2.8 ms at order 200, 23 ms at 512 and 172 ms at
+// 1024, after the wait.  (In place on the lower triangle, one thread per row and
+// other bits than a group's: 6.4, 39 and 297 ms.)
+__device__ unsigned int groups_given_up;     // for tests
+
 template <typename R>
-__global__ __launch_bounds__(1024) void hetrd_memory(HetrdWs<R> ws, int i0, int G)
+__global__ __launch_bounds__(2 * RT_T) void hetrd_memory(HetrdWs<R> ws, int i0, int G)
 {
-    constexpr int T = 1024, W = T / WAVE;
-    __shared__ cx<R> sv[HETRD_GROUP_M], sw[HETRD_GROUP_M];
-    __shared__ R red[2][W];
+    using M_ = Mfma<R>;
+    constexpr int MPX = HETRD_GROUP_M, SP = MPX / RT_T, FS = MPX + 16;
+    constexpr int CC = 4;                    // tile columns per pass: 64 columns
+    static_assert(CC * 16 == WAVE && SP == 2, "a wave's rows are a pass's columns");
+    __shared__ R F[4][FS];
+    __shared__ cx<R> x[MPX];
+    __shared__ cx<R> zp[RT_W][CC * 16];
+    __shared__ cx<R> hrow[CC * 16];
+    __shared__ R red[RT_W], sq[RT_W];
+    __shared__ cx<R> salpha, sref[2], sz1;
+    __shared__ R shoo;
+
     const int64_t b = blockIdx.x;
-    const int n = ws.n, M = n - i0, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int n = ws.n, M = n - i0, nt = (M + 15) >> 4;
     if (*Exchange<R>(ws, b, M).started() == (uint32_t)G) return;
-    cx<R>* A = ws.A + b * ws.sA + (int64_t)i0 + (int64_t)i0 * ws.lda;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wr = w & (RT_W - 1), wc = w / RT_W;
+    const bool rows = w < RT_W;              // this thread has rows of phase B
+    const cx<R>* A = ws.A + b * ws.sA + (int64_t)i0 + (int64_t)i0 * ws.lda;
     const int64_t lda = ws.lda;
     cx<R>* V = ws.V + b * ws.sV;
-    auto block_sum = [&](R v, R* sh) {
-        v = dpp_wave_sum(v);
-        if (lane == 0) sh[w] = v;
-        __syncthreads();
-        R t = 0;
-        for (int q = 0; q < W; ++q) t += sh[q];
-        return t;
+    R* Fr = ws.Fr + b * ws.sF;
+    R* Fi = ws.Fi + b * ws.sF;
+    const cx<R> zero = czero<cx<R>>();
+    if (tid == 0) atomicAdd(&groups_given_up, 1u);
+
+    // Register r of this lane in tile (Rt, C): its place in Fr and Fi, and
+    // whether the entry exists (0 and false past the matrix).  The last tile row and
+    // column hold the entries that exist only, so the M x M entries fill M x M places.
+    auto place = [&](int Rt, int C, int r, bool& in) -> int {
+        const int mr = min(16, M - Rt * 16), mc = min(16, M - C * 16);
+        const int base = C * 16 * M + Rt * 16 * mc;
+        in = true;
+        if (mr == 16 && mc == 16) return base + r * WAVE + lane;
+        const int row = M_::row(lk, r);
+        in = row < mr && li < mc;
+        return in ? base + li * mr + row : 0;
     };
-    if (tid == 0) ws.d[b * n + i0] = A[0].x;
+    // the full matrix from the lower triangle, by the lanes that update it below
+    for (int C = 0; C < nt; ++C) {
+        if (((C & (CC - 1)) >> 1) != wc) continue;
+        for (int Rt = wr; Rt < nt; Rt += RT_W)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = Rt * 16 + M_::row(lk, r), col = C * 16 + li;
+                bool in;
+                const int at = place(Rt, C, r, in);
+                if (in) {
+                    const bool low = row >= col;
+                    const cx<R> a = A[low ? (int64_t)row + (int64_t)col * lda : (int64_t)col + (int64_t)row * lda];
+                    Fr[at] = a.x;
+                    Fi[at] = row == col ? (R)0 : (low ? a.y : -a.y);
+                }
+            }
+    }
+    R nrm = 0;
+    for (int e = tid; e < 4 * FS; e += 2 * RT_T) (&F[0][0])[e] = (R)0;
+    if (rows) {
+#pragma unroll
+        for (int u = 0; u < SP; ++u) {
+            const int s = tid + RT_T * u;
+            const cx<R> a = csel(s < M, A[s < M ? s : 0], zero);
+            const cx<R> a2 = csel(s >= 2, a, zero);
+            x[s] = a2;
+            nrm += a2.x * a2.x + a2.y * a2.y;
+            if (s == 0) ws.d[b * n + i0] = a.x;
+            if (s == 1) salpha = a;
+        }
+        nrm = dpp_wave_sum(nrm);
+        if (lane == 0) red[w] = nrm;
+    }
+    __syncthreads();
+
     for (int c = 0; c + 1 < M; ++c) {
-        const int c1 = c + 1, i = i0 + c;
-        R part = 0;
-        for (int s = c1 + 1 + tid; s < M; s += T) {
-            const cx<R> a = A[s + c * lda];
-            part += a.x * a.x + a.y * a.y;
+        const int c1 = c + 1, i = i0 + c, k1 = c1 >> 4;
+        cx<R> z[SP], h[SP];
+#pragma unroll
+        for (int u = 0; u < SP; ++u) z[u] = h[u] = zero;
+        // ---- A: pending update, column sums, row c + 1
+        for (int C0 = k1 & ~(CC - 1); C0 < nt; C0 += CC) {
+#pragma unroll 1
+            for (int C = max(C0 + 2 * wc, k1); C < min(C0 + 2 * wc + 2, nt); ++C) {
+                const R opB = F[lk ^ 2][C * 16 + li];
+                cx<R> za[1] = {zero};
+                auto multiply = [&](int Rt, acc4<R>& tr, acc4<R>& ti) __attribute__((always_inline)) {
+                    const R nre = -F[lk][Rt * 16 + li], nim = -F[lk ^ 1][Rt * 16 + li];
+                    tr = M_::mma(nre, opB, tr);
+                    ti = M_::mma(nim, (lk & 1) ? -opB : opB, ti);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        za[0] = cfmac(mk<R>(tr[r], ti[r]), x[Rt * 16 + M_::row(lk, r)], za[0]);
+                    if (Rt == k1) {
+                        // row c + 1: A(:, c+1) is its conjugate
+                        const int rr = row_r<R>(c1 & 15);
+                        const R hr = rr < 2 ? (rr < 1 ? tr[0] : tr[1]) : (rr < 3 ? tr[2] : tr[3]);
+                        const R hi = rr < 2 ? (rr < 1 ? ti[0] : ti[1]) : (rr < 3 ? ti[2] : ti[3]);
+                        if (lk == row_lk<R>(c1 & 15)) hrow[(C - C0) * 16 + li] = mk<R>(hr, -hi);
+                    }
+                };
+                const int whole = C < (M >> 4) ? M >> 4 : 0;     // whole tiles of the column
+                int Rt = k1 + ((wr - k1) & (RT_W - 1));
+                // whole tiles: the next one is requested before this one is multiplied
+                R* const pr = Fr + C * 16 * M + lane;
+                R* const pi = Fi + C * 16 * M + lane;
+                acc4<R> nr, ni;
+                auto request = [&](int T) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        nr[r] = pr[T * 256 + r * WAVE];
+                        ni[r] = pi[T * 256 + r * WAVE];
+                    }
+                };
+                if (Rt < whole) request(Rt);
+#pragma unroll 1
+                for (; Rt < whole; Rt += RT_W) {
+                    acc4<R> tr = nr, ti = ni;
+                    if (Rt + RT_W < whole) request(Rt + RT_W);
+                    multiply(Rt, tr, ti);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        pr[Rt * 256 + r * WAVE] = tr[r];
+                        pi[Rt * 256 + r * WAVE] = ti[r];
+                    }
+                }
+#pragma unroll 1
+                for (; Rt < nt; Rt += RT_W) {
+                    acc4<R> tr, ti;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        bool in;
+                        const int at = place(Rt, C, r, in);
+                        tr[r] = in ? Fr[at] : (R)0;
+                        ti[r] = in ? Fi[at] : (R)0;
+                    }
+                    multiply(Rt, tr, ti);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        bool in;
+                        const int at = place(Rt, C, r, in);
+                        if (in) {
+                            Fr[at] = tr[r];
+                            Fi[at] = ti[r];
+                        }
+                    }
+                }
+                sum_lane_groups<R, 1>(za, lk, [&](int, cx<R> v) { zp[wr][(C - C0) * 16 + li] = v; });
+            }
+            __syncthreads();
+            // the thread whose row a column's sum is takes it
+            if (rows && w == ((C0 / CC) & (RT_W - 1))) {
+                cx<R> v[RT_W];
+#pragma unroll
+                for (int q = 0; q < RT_W; ++q) v[q] = zp[q][lane];
+                const cx<R> zs = cadd(cadd(cadd(v[0], v[1]), cadd(v[2], v[3])), cadd(cadd(v[4], v[5]), cadd(v[6], v[7])));
+                const bool second = C0 / CC >= RT_W;
+                z[0] = csel(second, z[0], zs);
+                h[0] = csel(second, h[0], hrow[lane]);
+                z[1] = csel(second, zs, z[1]);
+                h[1] = csel(second, hrow[lane], h[1]);
+            }
+            __syncthreads();
         }
-        const R sig2 = block_sum(part, red[0]);
-        cx<R> tau, scale;
-        R beta;
-        reflector_core(A[c1 + c * lda], sig2, tau, scale, beta);
-        for (int s = c1 + tid; s < M; s += T) {
-            const cx<R> v = csel(s == c1, mk<R>(1, 0), cmul(scale, A[s + c * lda]));
-            sv[s] = v;
-            V[(int64_t)(i0 + s) + (int64_t)i * n] = v;
+        // ---- Procedure 2
+        if (w == RT_W - 1) {
+            const R sig2 = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+            cx<R> tau, scale;
+            R beta;
+            reflector_core(salpha, sig2, tau, scale, beta);
+            if (lane == 0) {
+                sref[0] = tau;
+                sref[1] = scale;
+                ws.e[b * n + i] = beta;
+                ws.tau[b * n + i] = tau;
+            }
+        }
+        if (rows) {
+            R qs = 0;
+#pragma unroll
+            for (int u = 0; u < SP; ++u) {
+                const int s = tid + RT_T * u;
+                if (s >= c1 && s < M) {
+                    const cx<R> xs = x[s];
+                    qs = fma(xs.x, z[u].x, fma(xs.y, z[u].y, qs));
+                    if (s == c1) {
+                        sz1 = z[u];
+                        shoo = h[u].x;
+                    }
+                }
+            }
+            qs = dpp_wave_sum(qs);
+            if (lane == 0) sq[w] = qs;
         }
         __syncthreads();
-        // y = tau A22 v and v^H A22 v
-        part = 0;
-        for (int r = c1 + tid; r < M; r += T) {
-            cx<R> y = czero<cx<R>>();
-            for (int s = c1; s < r; ++s) y = cfma(A[r + s * lda], sv[s], y);
-            y = cfma(mk<R>(A[r + r * lda].x, 0), sv[r], y);
-            for (int s = r + 1; s < M; ++s) y = cfmac(A[s + r * lda], sv[s], y);
-            part += sv[r].x * y.x + sv[r].y * y.y;
-            sw[r] = cmul(tau, y);
+        // ---- B
+        if (rows) {
+            // (tau and scale come from LDS and the expressions are a member's, so
+            // that products and sums are fused alike)
+            const cx<R> tau = sref[0], scale = sref[1];
+            const R hoo = shoo;
+            const R qq = ((sq[0] + sq[1]) + (sq[2] + sq[3])) + ((sq[4] + sq[5]) + (sq[6] + sq[7]));
+            const cx<R> sz = cmul(scale, sz1);
+            const R vav = hoo + (R)2 * sz.x + (scale.x * scale.x + scale.y * scale.y) * qq;
+            const R a2 = (R)-0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
+            const cx<R> w1 = cadd(cmul(tau, cadd(mk<R>(hoo, 0), sz)), mk<R>(a2, 0));
+            nrm = 0;
+#pragma unroll
+            for (int u = 0; u < SP; ++u) {
+                const int s = tid + RT_T * u;
+                cx<R> vs = zero, wv = zero, xn = zero;
+                if (s >= c1 && s < M) {
+                    vs = csel(s == c1, mk<R>(1, 0), cmul(scale, x[s]));
+                    wv = csel(s == c1, w1, cfma(tau, cfma(scale, z[u], h[u]), cscale(vs, a2)));
+                    xn = csub(h[u], cadd(cmulc(w1, vs), wv));
+                    V[(int64_t)(i0 + s) + (int64_t)i * n] = vs;
+                    if (s == c1) ws.d[b * n + i + 1] = hoo - (R)2 * w1.x;
+                    if (s == c1 + 1) salpha = xn;
+                    xn = csel(s >= c1 + 2, xn, zero);
+                    nrm += xn.x * xn.x + xn.y * xn.y;
+                }
+                F[0][s] = vs.x;
+                F[1][s] = vs.y;
+                F[2][s] = wv.x;
+                F[3][s] = wv.y;
+                x[s] = xn;
+            }
+            nrm = dpp_wave_sum(nrm);
+            if (lane == 0) red[w] = nrm;
         }
-        const R vav = block_sum(part, red[1]);
-        const R a2 = (R)-0.5 * (tau.x * tau.x + tau.y * tau.y) * vav;
-        for (int r = c1 + tid; r < M; r += T) sw[r] = cadd(sw[r], cscale(sv[r], a2));
         __syncthreads();
-        for (int r = c1 + tid; r < M; r += T)
-            for (int s = c1; s <= r; ++s)
-                A[r + s * lda] = csub(A[r + s * lda], cadd(cmulc(sw[s], sv[r]), cmulc(sv[s], sw[r])));
-        __syncthreads();
-        if (tid == 0) {
-            ws.e[b * n + i] = beta;
-            ws.tau[b * n + i] = tau;
-            ws.d[b * n + i + 1] = A[c1 + c1 * lda].x;
-        }
     }
 }
 
@@ -796,10 +986,12 @@ hipError_t launch_group(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk
     if (nt > RT * RT_W || G > GROUP_MAX) return hipErrorInvalidValue;
     const Exchange<R> ex(ws, 0, M);
     const int words = 2 + 3 * ex.slot_words();
-    hipLaunchKernelGGL(k_exchange_init<R>, dim3((unsigned)((words + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws, M);
-    hipLaunchKernelGGL((hetrd_group<R, RT, KC>), dim3((unsigned)(nk * G)), dim3(RT_T), 0, st, ws, i0, G,
-                       tl_group_wait_ticks);
-    hipLaunchKernelGGL(hetrd_memory<R>, dim3((unsigned)nk), dim3(1024), 0, st, ws, i0, G);
+    hipLaunchKernelGGL(k_exchange_init<R>, dim3((unsigned)((words + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws, M,
+                       tl_group_wait_ticks == 0 ? GIVEN_UP : 0u,
+                       tl_group_wait_ticks == 0 ? GIVEN_UP : tl_group_lacks_one ? 1u : 0u);
+    hipLaunchKernelGGL((hetrd_group<R, RT, KC>), dim3((unsigned)(nk * G - (tl_group_lacks_one ? 1 : 0))), dim3(RT_T), 0,
+                       st, ws, i0, G, tl_group_wait_ticks);
+    hipLaunchKernelGGL(hetrd_memory<R>, dim3((unsigned)nk), dim3(2 * RT_T), 0, st, ws, i0, G);
     return hipGetLastError();
 }
 
@@ -892,9 +1084,21 @@ template hipError_t hetrd_res<float>(hipStream_t, const HetrdWs<float>&, int, in
 
 }  // namespace kgev
 
-// For tests: the wait for a group's members to start, in 100 MHz ticks, for the
-// calling thread (0 gives every group up at once; negative: the default).
+// For tests, for the calling thread: the wait for a group's members to start, in
+// 100 MHz ticks (0 gives every group up before it starts; negative: the
+// default), and launches whose last problem lacks a member that counts as
+// started, so that the others wait for its columns in vain.
 extern "C" void kgev_internal_group_wait(int64_t ticks)
 {
     kgev::tl_group_wait_ticks = ticks < 0 ? kgev::GROUP_WAIT_TICKS : ticks;
+}
+extern "C" void kgev_internal_group_lacks_one(int32_t on) { kgev::tl_group_lacks_one = on != 0; }
+// the problems of the current device that hetrd_memory has reduced so far
+// (waits for the device); -1 if they can't be read
+extern "C" int64_t kgev_internal_groups_given_up()
+{
+    unsigned int count = 0;
+    if (hipDeviceSynchronize() != hipSuccess) return -1;
+    if (hipMemcpyFromSymbol(&count, HIP_SYMBOL(kgev::groups_given_up), sizeof(count)) != hipSuccess) return -1;
+    return count;
 }

@@ -80,6 +80,7 @@ struct HetrdWs {
     cx<R>* ypartT; int64_t s_ypartT; // NBmax x CHmax x 64
     cx<R>* pdot; int64_t s_pdot;     // W^H u (nb), V^H u (nb)
     R* qpart; int64_t s_qpart;       // NBmax x CHmax: per-chunk shares of Re(u^H A22 u)
+    R* Fr; R* Fi; int64_t sF;        // n x n each: the trailing matrix of a group that was given up
 };
 
 inline int hetrd_nbmax(int64_t n) { return (int)((n - 1 + 63) / 64) > 0 ? (int)((n - 1 + 63) / 64) : 1; }

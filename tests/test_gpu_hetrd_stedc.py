@@ -302,6 +302,76 @@ def test_group_given_up_is_reduced_in_memory():
         lib.kgev_internal_group_wait(-1)
 
 
+class GroupHooks:
+    """The library's switches for groups that are given up, at their defaults
+    afterwards: at once (before they start), or late (the last problem's lacks a
+    member, whose columns the others wait for until their looks run out).
+    given_up(): the problems reduced in memory so far."""
+
+    def __enter__(self):
+        import ctypes
+        self.lib = K().lib
+        self.lib.kgev_internal_group_wait.argtypes = [ctypes.c_int64]
+        self.lib.kgev_internal_group_lacks_one.argtypes = [ctypes.c_int32]
+        self.lib.kgev_internal_groups_given_up.restype = ctypes.c_int64
+        return self
+
+    def __exit__(self, *exc):
+        self.set(None)
+
+    def set(self, how):
+        self.lib.kgev_internal_group_lacks_one(1 if how == "late" else 0)
+        self.lib.kgev_internal_group_wait(0 if how == "at once" else -1)
+
+    def given_up(self):
+        return self.lib.kgev_internal_groups_given_up()
+
+
+# one and two rows a thread, edges of the tiles, one and several problems, a
+# hand-over after blocked columns
+@pytest.mark.parametrize("n,nk,how", [(161, 2, "at once"), (200, 3, "at once"), (257, 1, "at once"),
+                                      (333, 3, "at once"), (512, 2, "at once"), (513, 1, "at once"),
+                                      (640, 2, "at once"), (777, 1, "at once"), (1024, 1, "at once"),
+                                      (1090, 2, "at once"), (200, 3, "late"), (600, 1, "late")])
+def test_given_up_group_has_the_same_bits(n, nk, how):
+    rng = np.random.default_rng(n)
+    As = np.stack([rand_herm(rng, n) for _ in range(nk)])
+    with GroupHooks() as hooks:
+        counts = [hooks.given_up()]
+        ref = gpu_hetrd(As)
+        counts.append(hooks.given_up())
+        hooks.set(how)
+        got = gpu_hetrd(As)
+        hooks.set(None)
+        counts.append(hooks.given_up())
+    assert np.diff(counts).tolist() == [0, nk if how == "at once" else 1]
+    for name, a, b in zip(("d", "e", "tau", "V"), ref, got):
+        assert np.array_equal(a, b), name
+
+
+@pytest.mark.parametrize("n,nk", [(200, 2), (520, 1)])
+def test_given_up_group_has_the_same_bits_mixed(n, nk):
+    # the complex64 reduction, through the mixed-precision solve
+    kg = K()
+    rng = np.random.default_rng(n)
+    dH = dev(np.stack([rand_herm(rng, n) for _ in range(nk)]))
+    dS = dev(np.stack([np.eye(n) + 0.01 * rand_herm(rng, n) / n for _ in range(nk)]))
+    outs = []
+    with GroupHooks() as hooks, kg.Context(0) as ctx:
+        for how in (None, "at once"):
+            w = torch.zeros((nk, n), dtype=torch.float64, device=DEV)
+            C = torch.zeros((nk, n, n), dtype=torch.complex128, device=DEV)
+            before = hooks.given_up()
+            hooks.set(how)
+            check(kg.solve_k_device(ctx, dH, dS, n, n, nk, w, C, n, opts=kg.make_opts(precision=kg.PREC_FP32_REFINE)))
+            hooks.set(None)
+            # S in complex128 and A in complex64
+            assert hooks.given_up() - before == (2 * nk if how else 0)
+            outs.append((w, C))
+    for w, C in outs[1:]:
+        assert torch.equal(w, outs[0][0]) and torch.equal(C, outs[0][1])
+
+
 # merges with chains of deflation rotations, long runs of negligible
 # components, tiny and graded blocks; the segment sizes about the deflation's
 # steps of 256 rows; tolerances as test_stedc_matches_oracle
