@@ -142,7 +142,8 @@ kgev_status kgev_create(kgev_ctx** ctx, int device);
  * option 0 use them.  The tuned values depend only on n and precision, not
  * on the batch.
  * Results are bitwise reproducible for the same n, k-point count and
- * options; the tile grouping of a column follows the launch's workgroup
+ * options on the same device (and with the same compute-unit mask of the
+ * stream, if it has one); the tile grouping of a column follows the launch's workgroup
  * count, so the same k-point solved in calls of different k-point counts
  * agrees to rounding, not necessarily bitwise.  *best_nb (optional)
  * receives the panel width.  Synchronous; uses the context's internal

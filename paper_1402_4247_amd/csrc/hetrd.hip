@@ -673,10 +673,11 @@ hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
     // Buffer offsets are 32-bit: a matrix (ld x n) of 2 GiB or more is read
     // with plain global loads instead.
     const bool buf = (double)sizeof(cx<R>) * (double)ws.lda * (double)n < 2147483648.0;
-    const int limit = hetrd_res_order(n, nb, nk, ws.groups);
+    const int cus = ws.groups && n > HETRD_RES_M ? stream_compute_units(st) : 0;
+    const int limit = hetrd_res_order(n, nb, nk, ws.groups, cus);
     for (int p = 0; p <= n - 1; p += nb) {
         if (n - p <= limit && p < n - 1) {
-            const hipError_t e = hetrd_res<R>(st, ws, p, nk);
+            const hipError_t e = hetrd_res<R>(st, ws, p, nk, cus);
             if (e != hipSuccess) return e;
             break;
         }

@@ -32,6 +32,7 @@
 // group is given up: results are bitwise reproducible.
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -321,9 +322,12 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
 // start for a bounded time, after which the group is given up (the last one to
 // arrive and the one that gives up decide by an atomic on the same word) and
 // hetrd_memory reduces that problem instead, to the same bits.  Once all have
-// started, every wait ends; the poll is bounded all the same.  A group has at most 64 members
-// of the 256 compute units, so four launches on different streams (the
-// hardware queues of a process) cannot hold each other's partly placed groups.
+// started, every wait ends; the poll is bounded all the same.  A group has at
+// most a quarter of the compute units that its stream may use (64 of the 256 of
+// a whole GPU; a partition of one or a stream with a mask has fewer), so four
+// launches on different streams (the hardware queues of a process by default)
+// cannot hold each other's partly placed groups.  More queues or several
+// processes can; their groups are given up after the wait.
 //
 // Bound by the latency of a column: the exchange (a store and a load through
 // the coherent level, 0.5-0.7 us between any two compute units), three
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
 // of a blocked column.
 constexpr uint64_t SENTINEL = 0xFFF4DEADFFF4BEEFull;   // two NaNs as well for a pair of floats
 constexpr uint32_t GIVEN_UP = 0x80000000u;
-constexpr int GROUP_MAX = 64;             // members of a group at most
+constexpr int GROUP_MAX = 64;             // members of a group at most (the shapes' largest)
 constexpr int GROUP_MIN = 160;            // orders up to this stay with panels and one workgroup
 
 template <typename T> __device__ __attribute__((always_inline)) inline T load_agent(const T* p)
@@ -983,7 +987,7 @@ hipError_t launch_group(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk
 {
     const int M = ws.n - i0, nt = (M + 15) / 16;
     const int G = (nt + KC - 1) / KC;
-    if (nt > RT * RT_W || G > GROUP_MAX) return hipErrorInvalidValue;
+    if (M > HETRD_GROUP_M || nt > RT * RT_W || G > GROUP_MAX) return hipErrorInvalidValue;
     const Exchange<R> ex(ws, 0, M);
     const int words = 2 + 3 * ex.slot_words();
     hipLaunchKernelGGL(k_exchange_init<R>, dim3((unsigned)((words + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws, M,
@@ -995,30 +999,77 @@ hipError_t launch_group(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk
     return hipGetLastError();
 }
 
-constexpr int CUS = 256;    // compute units: a workgroup of a group fills one
-
-// For each largest order: the widest share of a member (tile columns), set by
-// the registers (RT * KC tiles of 16 each in FP64), and the microseconds a
-// column takes with that share when the groups fill the chip (measured at
-// 256 x 64, 384 x 32, 512 x 16, 640 x 12, 768 x 5 and 1024 x 4 problems).
+// For each largest order: the tile rows of a wave and the widest share of a
+// member (tile columns), set by the registers (RT * KC tiles of 16 each in FP64),
+// and the microseconds a column takes with that share when the groups fill the
+// chip (measured at 256 x 64, 384 x 32, 512 x 16, 640 x 12, 768 x 5 and 1024 x 4
+// problems).
 struct GroupShape {
-    int M, KC;
+    int M, RT, KC;
     double us;
 };
-constexpr GroupShape GROUP_SHAPES[] = {{256, 4, 3.2}, {384, 3, 3.7},  {512, 2, 3.6},
-                                       {640, 2, 4.4}, {768, 1, 3.4}, {1024, 1, 3.9}};
+constexpr GroupShape GROUP_SHAPES[] = {{256, 2, 4, 3.2}, {384, 3, 3, 3.7}, {512, 4, 2, 3.6},
+                                       {640, 5, 2, 4.4}, {768, 6, 1, 3.4}, {HETRD_GROUP_M, 8, 1, 3.9}};
 
-// How often the chip is filled with whole groups.  Where groups take turns and
-// do not divide the chip, the partly placed one holds compute units idle:
+int group_members(int M, int KC) { return ((M + 15) / 16 + KC - 1) / KC; }
+
+// whether groups with this share may run on cus compute units
+bool group_allowed(int M, int KC, int cus) { return group_members(M, KC) <= std::min(GROUP_MAX, cus / 4); }
+
+// How often the compute units are filled with whole groups.  Where groups take
+// turns and do not divide them, the partly placed one holds some idle:
 // measured 2.7 times one round for 24 problems of order 640 (12 at once).
-double group_rounds(int M, int KC, int64_t nk)
+double group_rounds(int M, int KC, int64_t nk, int cus)
 {
-    const int64_t G = ((M + 15) / 16 + KC - 1) / KC, at_once = CUS / G;
+    const int64_t G = group_members(M, KC), at_once = cus / G;
     const int64_t rounds = (nk + at_once - 1) / at_once;
-    return (double)rounds + (rounds > 1 && CUS % G != 0 ? 0.7 : 0.0);
+    return (double)rounds + (rounds > 1 && cus % G != 0 ? 0.7 : 0.0);
 }
 
+// The shape and share for a trailing order: the narrowest share whose groups all
+// run at once (more compute units per column); where not even the widest do,
+// the widest, so that the groups take turns in as few rounds as possible.  The
+// sums do not depend on the share.  {0, 0}: no group may run.
+struct GroupChoice {
+    int RT, KC;
+};
+GroupChoice group_choice(int M, int64_t nk, int cus)
+{
+    for (const GroupShape& g : GROUP_SHAPES) {
+        if (M > g.M) continue;
+        for (int KC = 1; KC < g.KC; ++KC) {
+            if (g.RT == 2 && KC == 3) continue;      // (2, 3) is not instantiated
+            if (group_allowed(M, KC, cus) && group_rounds(M, KC, nk, cus) < 1.5) return {g.RT, KC};
+        }
+        return group_allowed(M, g.KC, cus) ? GroupChoice{g.RT, g.KC} : GroupChoice{0, 0};
+    }
+    return {0, 0};
+}
+
+thread_local int tl_compute_units = 0;       // set by tests
+
 }  // namespace
+
+// The compute units that work on a stream may use: the device's, without those
+// that a mask of the stream leaves out.
+int stream_compute_units(hipStream_t st)
+{
+    if (tl_compute_units > 0) return tl_compute_units;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    uint32_t mask[32] = {};
+    const uint32_t words = (uint32_t)std::min((cus + 31) / 32, 32);
+    if (hipExtStreamGetCUMask(st, words, mask) == hipSuccess) {
+        int in = 0;
+        for (uint32_t q = 0; q < words; ++q) in += __builtin_popcount(mask[q]);
+        if (in > 0) cus = std::min(cus, in);
+    } else {
+        (void)hipGetLastError();
+    }
+    return cus;
+}
 
 // The hand-over order with the least estimated time for the whole reduction:
 // blocked columns at 12 us plus 4 TB/s over the lower triangles (two launches
@@ -1027,7 +1078,7 @@ double group_rounds(int M, int KC, int64_t nk)
 // times their rounds.  512 columns: 1 problem 5.1 -> 1.75 ms, 8 problems 5.2 ->
 // 2.1 ms, 64 problems (4 rounds) 11.0 -> 8.2 ms; 1024 columns of one problem
 // 11.3 -> 4.9 ms.
-int hetrd_res_order(int n, int nb, int64_t nk, int groups)
+int hetrd_res_order(int n, int nb, int64_t nk, int groups, int cus)
 {
     int best = HETRD_RES_M;
     if (!groups || n <= GROUP_MIN) return best;
@@ -1036,10 +1087,10 @@ int hetrd_res_order(int n, int nb, int64_t nk, int groups)
         const int cap = q < 0 ? HETRD_RES_M : GROUP_SHAPES[q].M;
         const int p = n > cap ? (n - cap + nb - 1) / nb * nb : 0;      // the hand-over column
         const int M = n - p;
-        if (q >= 0 && M <= HETRD_RES_M) continue;
+        if (q >= 0 && (M <= HETRD_RES_M || !group_allowed(M, GROUP_SHAPES[q].KC, cus))) continue;
         const double dn = n, dM = M;
         double us = 12.0 * (dn - dM) + 8.0 * (double)nk / 4.0e6 * (dn * dn * dn - dM * dM * dM) / 3.0;
-        us += q < 0 ? 2.0 * dM : group_rounds(M, GROUP_SHAPES[q].KC, nk) * dM * GROUP_SHAPES[q].us;
+        us += q < 0 ? 2.0 * dM : group_rounds(M, GROUP_SHAPES[q].KC, nk, cus) * dM * GROUP_SHAPES[q].us;
         if (q < 0 || us < least) {
             least = us;
             best = cap;
@@ -1049,38 +1100,35 @@ int hetrd_res_order(int n, int nb, int64_t nk, int groups)
 }
 
 template <typename R>
-hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk)
+hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk, int cus)
 {
     const int M = ws.n - i0;
-    if (M <= 128) {
+    if (M <= HETRD_RES_M) {
         if (M <= 64)
             hipLaunchKernelGGL((hetrd_resident<R, 1, 4>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
         else
             hipLaunchKernelGGL((hetrd_resident<R, 1, 8>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
         return hipGetLastError();
     }
-    // The narrowest shares that all run at once (more compute units per column);
-    // where not even the widest do, the widest, so that the groups take turns
-    // in as few rounds as possible.  The sums do not depend on the share.
-    auto fits = [&](int KC) { return group_rounds(M, KC, nk) < 1.5; };
-    if (M <= 256) {
-        if (fits(1)) return launch_group<R, 2, 1>(st, ws, i0, nk);
-        if (fits(2)) return launch_group<R, 2, 2>(st, ws, i0, nk);
-        return launch_group<R, 2, 4>(st, ws, i0, nk);
+    const GroupChoice g = group_choice(M, nk, cus);
+    switch (10 * g.RT + g.KC) {
+    case 21: return launch_group<R, 2, 1>(st, ws, i0, nk);
+    case 22: return launch_group<R, 2, 2>(st, ws, i0, nk);
+    case 24: return launch_group<R, 2, 4>(st, ws, i0, nk);
+    case 31: return launch_group<R, 3, 1>(st, ws, i0, nk);
+    case 32: return launch_group<R, 3, 2>(st, ws, i0, nk);
+    case 33: return launch_group<R, 3, 3>(st, ws, i0, nk);
+    case 41: return launch_group<R, 4, 1>(st, ws, i0, nk);
+    case 42: return launch_group<R, 4, 2>(st, ws, i0, nk);
+    case 51: return launch_group<R, 5, 1>(st, ws, i0, nk);
+    case 52: return launch_group<R, 5, 2>(st, ws, i0, nk);
+    case 61: return launch_group<R, 6, 1>(st, ws, i0, nk);
+    case 81: return launch_group<R, 8, 1>(st, ws, i0, nk);
     }
-    if (M <= 384) {
-        if (fits(1)) return launch_group<R, 3, 1>(st, ws, i0, nk);
-        if (fits(2)) return launch_group<R, 3, 2>(st, ws, i0, nk);
-        return launch_group<R, 3, 3>(st, ws, i0, nk);
-    }
-    if (M <= 512) return fits(1) ? launch_group<R, 4, 1>(st, ws, i0, nk) : launch_group<R, 4, 2>(st, ws, i0, nk);
-    if (M <= 640) return fits(1) ? launch_group<R, 5, 1>(st, ws, i0, nk) : launch_group<R, 5, 2>(st, ws, i0, nk);
-    if (M <= 768) return launch_group<R, 6, 1>(st, ws, i0, nk);
-    if (M <= HETRD_GROUP_M) return launch_group<R, 8, 1>(st, ws, i0, nk);
     return hipErrorInvalidValue;
 }
-template hipError_t hetrd_res<double>(hipStream_t, const HetrdWs<double>&, int, int64_t);
-template hipError_t hetrd_res<float>(hipStream_t, const HetrdWs<float>&, int, int64_t);
+template hipError_t hetrd_res<double>(hipStream_t, const HetrdWs<double>&, int, int64_t, int);
+template hipError_t hetrd_res<float>(hipStream_t, const HetrdWs<float>&, int, int64_t, int);
 
 }  // namespace kgev
 
@@ -1102,3 +1150,21 @@ extern "C" int64_t kgev_internal_groups_given_up()
     if (hipMemcpyFromSymbol(&count, HIP_SYMBOL(kgev::groups_given_up), sizeof(count)) != hipSuccess) return -1;
     return count;
 }
+// what a reduction would do on cus compute units: the hand-over order, and the
+// tile rows, tile columns and members of its groups (0 where it hands over to one
+// workgroup)
+extern "C" void kgev_internal_hetrd_plan(int32_t n, int32_t nb, int64_t nk, int32_t cus, int32_t* out)
+{
+    const int order = kgev::hetrd_res_order(n, nb, nk, 1, cus);
+    const int p = n > order ? (n - order + nb - 1) / nb * nb : 0;
+    const kgev::GroupChoice g =
+        n - p > kgev::HETRD_RES_M ? kgev::group_choice(n - p, nk, cus) : kgev::GroupChoice{0, 0};
+    out[0] = n - p;
+    out[1] = g.RT;
+    out[2] = g.KC;
+    out[3] = g.KC ? kgev::group_members(n - p, g.KC) : 0;
+}
+// compute units: of a stream, and for the calling thread in place of the
+// device's (0: the device's)
+extern "C" int32_t kgev_internal_stream_units(void* stream) { return kgev::stream_compute_units((hipStream_t)stream); }
+extern "C" void kgev_internal_compute_units(int32_t cus) { kgev::tl_compute_units = cus > 0 ? cus : 0; }

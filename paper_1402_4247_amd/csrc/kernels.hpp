@@ -93,9 +93,11 @@ hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws, int64_t nk);
 // HETRD_RES_M and of a group of workgroups up to HETRD_GROUP_M; 2 <= n - i0
 constexpr int HETRD_RES_M = 128, HETRD_GROUP_M = 1024;
 template <typename R>
-hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk);
-// the order at which nk reductions of order n in panels of nb hand over to it
-int hetrd_res_order(int n, int nb, int64_t nk, int groups);
+hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk, int cus);
+// the order at which nk reductions of order n in panels of nb hand over to it on
+// cus compute units, and the compute units that a stream may use
+int hetrd_res_order(int n, int nb, int64_t nk, int groups, int cus);
+int stream_compute_units(hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // divide-and-conquer tridiagonal eigensolver (stedc.hip)

@@ -372,6 +372,30 @@ def test_given_up_group_has_the_same_bits_mixed(n, nk):
         assert torch.equal(w, outs[0][0]) and torch.equal(C, outs[0][1])
 
 
+def test_stream_compute_units():
+    import ctypes
+    lib = K().lib
+    lib.kgev_internal_stream_units.argtypes = [ctypes.c_void_p]
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    assert lib.kgev_internal_stream_units(None) == units
+    assert lib.kgev_internal_stream_units(torch.cuda.Stream().cuda_stream) == units
+
+
+# on a partition of the GPU or under a mask: smaller groups after more blocked
+# columns, or none, and none that waits for members in vain
+@pytest.mark.parametrize("n,nk,units", [(400, 2, 32), (600, 3, 64), (300, 1, 8), (1100, 1, 128)])
+def test_fewer_compute_units(n, nk, units):
+    lib = K().lib
+    with GroupHooks() as hooks:
+        before = hooks.given_up()
+        try:
+            lib.kgev_internal_compute_units(units)
+            spectrum_check(n, nk, 13 * n)
+        finally:
+            lib.kgev_internal_compute_units(0)
+        assert hooks.given_up() == before
+
+
 # merges with chains of deflation rotations, long runs of negligible
 # components, tiny and graded blocks; the segment sizes about the deflation's
 # steps of 256 rows; tolerances as test_stedc_matches_oracle
