@@ -8,6 +8,7 @@
 //           energy density matrix with weights f_kj lambda_kj (lower
 //           triangles), as one batched MFMA product per matrix plus a
 //           fixed-order sum over k-points.
+#include "chemical_potential.hpp"
 #include "common.hpp"
 #include "lanes.hpp"
 #include "kernels.hpp"
@@ -58,10 +59,10 @@ __device__ inline double block_min(double v, double* sh)
     return s;
 }
 
-// One workgroup: bracket, Newton steps, bisection (every thread takes the same
-// decision from the same block sum), then occupations, band energy and final
-// count.  Bound by the evaluations, one exponential per state each: n = 1040 x 16
-// 812 -> 270 us against bisection alone, 616 x 8 329 -> 96 us.
+// One workgroup: bracket, the search for mu (chemical_potential.hpp; every
+// thread takes the same decision from the same block sum), then occupations,
+// band energy and final count.  Bound by the evaluations, one exponential per
+// state each.
 // out = {mu, e_band, n_count}; status = 0, or KGEV_ERANGE when nelec is not
 // inside (0, g n sum wk).
 __global__ __launch_bounds__(FT) void k_fermi(const double* __restrict__ w, int64_t ldw, int n, int nk,
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(FT) void k_fermi(const double* __restrict__ w, int6
                                               double* occ, int64_t ldo, double* out, int32_t* status)
 {
     __shared__ double sh[FW];
-    double lo = INFINITY, hi = INFINITY, ws = 0.0;
+    double lo = INFINITY, hi = INFINITY, ws = 0.0, wmin = INFINITY;
     for (int k = 0; k < nk; ++k)
         for (int j = threadIdx.x; j < n; j += FT) {
             const double x = w[(int64_t)k * ldw + j];
@@ -77,6 +78,7 @@ __global__ __launch_bounds__(FT) void k_fermi(const double* __restrict__ w, int6
             hi = fmin(hi, -x);
         }
     for (int k = threadIdx.x; k < nk; k += FT) ws += wk[k];
+    for (int k = 0; k < nk; ++k) wmin = fmin(wmin, wk[k]);
     lo = block_min(lo, sh);
     hi = -block_min(hi, sh);
     ws = block_sum(ws, sh);
@@ -87,76 +89,22 @@ __global__ __launch_bounds__(FT) void k_fermi(const double* __restrict__ w, int6
     lo -= 50.0 * kT;
     hi += 50.0 * kT;
     // g sum_k wk sum_j f_kj at x and its derivative
-    auto count = [&](double x, double& slope) {
+    auto count = [&](double x, double* slope) {
         double s = 0.0, t1 = 0.0;
         for (int k = 0; k < nk; ++k) {
             double t = 0.0, u = 0.0;
             for (int j = threadIdx.x; j < n; j += FT) {
                 const double f = fermi_dirac(w[(int64_t)k * ldw + j], x, kT);
                 t += f;
-                u = fma(f, 1.0 - f, u);
+                if (slope) u = fma(f, 1.0 - f, u);
             }
             s = fma(wk[k], t, s);
-            t1 = fma(wk[k], u, t1);
+            if (slope) t1 = fma(wk[k], u, t1);
         }
-        slope = g * block_sum(t1, sh) / kT;
+        if (slope) *slope = g * block_sum(t1, sh) / kT;
         return g * block_sum(s, sh);
     };
-    // Newton steps inside the bracket (about 6) and a few more points around
-    // their limit leave bisection an interval of some ulps instead of the
-    // whole bracket's 60 halvings.  Only where the slope fixes mu: in a gap the
-    // count is flat to rounding, and mu stays where bisection of the whole
-    // bracket ends.
-    {
-        double a = lo, c = hi, x = 0.5 * (lo + hi), slope = 0.0;
-        bool good = false;
-        for (int it = 0; it < 40; ++it) {
-            const double cnt = count(x, slope);
-            if (cnt < nelec) a = x;
-            else c = x;
-            const double scale = fmax(fabs(x), kT);
-            good = slope * scale * 1e-9 > 1e-14 * nelec;
-            const double step = (nelec - cnt) / slope;
-            if (good && fabs(step) <= 8e-16 * scale) break;
-            double y = x + step;
-            if (!(y > a && y < c)) y = 0.5 * (a + c);
-            if (!(y > a && y < c)) break;
-            x = y;
-        }
-        // pinch: x - d and x + d with d from a few ulps up, until they bracket
-        double d = 4e-16 * fmax(fabs(x), kT);
-        for (int it = 0; good && it < 24; ++it, d *= 16.0) {
-            const double y = x - d;
-            if (y <= a) break;
-            if (count(y, slope) < nelec) {
-                a = y;
-                break;
-            }
-            c = y;
-        }
-        d = 4e-16 * fmax(fabs(x), kT);
-        for (int it = 0; good && it < 24; ++it, d *= 16.0) {
-            const double y = x + d;
-            if (y >= c) break;
-            if (!(count(y, slope) < nelec)) {
-                c = y;
-                break;
-            }
-            a = y;
-        }
-        if (good && a < c) {
-            lo = a;
-            hi = c;
-        }
-    }
-    for (int it = 0; it < 400; ++it) {
-        const double mid = 0.5 * (lo + hi);
-        if (!(mid > lo && mid < hi)) break;
-        double slope;
-        if (count(mid, slope) < nelec) lo = mid;
-        else hi = mid;
-    }
-    const double mu = 0.5 * (lo + hi);
+    const double mu = chemical_potential(count, wmin >= 0.0, nelec, kT, lo, hi);
     double sc = 0.0, se = 0.0;
     for (int k = 0; k < nk; ++k) {
         double tc = 0.0, te = 0.0;
