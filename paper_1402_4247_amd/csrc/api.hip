@@ -263,6 +263,20 @@ struct SolveOpts : kgev_opts {
     int32_t groups;
 };
 
+// The options as words of a batch graph's key: every field by itself (the
+// struct has padding, whose bytes nothing sets).  use_graph is 1 there and the
+// reserved fields are 0.
+void push_opts(std::vector<uintptr_t>& key, const SolveOpts& o)
+{
+    const int32_t fields[] = {o.precision, o.want_vectors, o.panel_nb,   o.refine_iters, o.streams,
+                              o.s_method,  o.hemv_slots,   o.gemm_slots, o.groups};
+    for (int32_t v : fields) key.push_back((uintptr_t)(intptr_t)v);
+    uint64_t tol;
+    static_assert(sizeof(tol) == sizeof(o.s_tol) && sizeof(uintptr_t) == sizeof(tol), "one word");
+    memcpy(&tol, &o.s_tol, sizeof(tol));
+    key.push_back((uintptr_t)tol);
+}
+
 SolveOpts resolve_opts(const kgev_opts* o)
 {
     SolveOpts r;
@@ -963,12 +977,7 @@ kgev_status kgev_solve_batch_device(kgev_ctx* ctx, const kgev_problem* probs, in
     key.push_back((uintptr_t)count);
     key.push_back((uintptr_t)w);
     key.push_back((uintptr_t)stream);
-    const unsigned char* ob = reinterpret_cast<const unsigned char*>(&o);
-    for (size_t b = 0; b < sizeof(o); b += sizeof(uintptr_t)) {
-        uintptr_t v = 0;
-        memcpy(&v, ob + b, std::min(sizeof(uintptr_t), sizeof(o) - b));
-        key.push_back(v);
-    }
+    push_opts(key, o);
     for (int64_t q = 0; q < count; ++q) {
         const kgev_problem& pr = probs[q];
         key.push_back((uintptr_t)pr.n); key.push_back((uintptr_t)pr.ld); key.push_back((uintptr_t)pr.nk);
@@ -1522,3 +1531,24 @@ kgev_status kgev_tuned_params(kgev_ctx* ctx, int64_t n, int32_t precision, int32
 }
 
 }  // extern "C"
+
+// For tests: the words a batch graph's key has from these options, at most cap
+// of them, after the stack has been written over with `dirt`; and the batch graphs
+// that a context keeps.
+extern "C" int32_t kgev_internal_opts_key(const kgev_opts* opts, int32_t dirt, uint64_t* words, int32_t cap)
+{
+    [](int32_t v) __attribute__((noinline)) {
+        volatile char junk[4096];
+        for (size_t q = 0; q < sizeof(junk); ++q) junk[q] = (char)v;
+    }(dirt);
+    return [](const kgev_opts* o, uint64_t* out, int32_t most) __attribute__((noinline)) {
+        std::vector<uintptr_t> key;
+        SolveOpts (*volatile resolve)(const kgev_opts*) = resolve_opts;
+        const SolveOpts resolved = resolve(o);
+        push_opts(key, resolved);
+        const int32_t count = std::min((int32_t)key.size(), most);
+        for (int32_t q = 0; q < count; ++q) out[q] = key[(size_t)q];
+        return count;
+    }(opts, words, cap);
+}
+extern "C" int32_t kgev_internal_batch_graphs(const kgev_ctx* ctx) { return ctx ? (int32_t)ctx->batch_graphs.size() : -1; }

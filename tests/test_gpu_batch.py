@@ -162,3 +162,31 @@ def test_batch_argument_errors():
         assert kg.solve_batch_device(ctx, [good], dwork=ws, work_bytes=need) == 0
         torch.cuda.synchronize()
         assert bool((st == 0).all())
+
+
+def test_batch_graph_is_kept_across_other_calls():
+    """The same batch finds its graph again whatever was called in between, and
+    another option makes another graph."""
+    import ctypes
+    kg = K()
+    kg.lib.kgev_internal_batch_graphs.argtypes = [ctypes.c_void_p]
+    n, nk = 40, 2
+    Hs, Ss = G.config1_batch(n, nk, 5)
+    dH, dS = dev(Hs), dev(Ss)
+    w, C, st = buffers(n, nk)
+    probs = [kg.problem(dH, dS, n, n, nk, w, C, n, st)]
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with kg.Context(0) as ctx:
+        def call(**kw):
+            check(kg.solve_batch_device(ctx, probs, opts=kg.make_opts(use_graph=True, **kw), stream=stream.cuda_stream))
+            stream.synchronize()
+            return kg.lib.kgev_internal_batch_graphs(ctx.handle)
+
+        for rep in range(4):
+            assert call() == 1, f"call {rep}"
+            # other work of the program between the calls
+            kg.workspace_bytes(100 + rep, 3, kg.make_opts(streams=1 + rep))
+            check(kg.solve_k_device(ctx, dH, dS, n, n, nk, w, C, n, opts=kg.make_opts(s_tol=1e-9 * (rep + 1))))
+            torch.cuda.synchronize()
+        assert call(s_tol=1e-11) == 2
