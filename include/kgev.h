@@ -130,14 +130,15 @@ kgev_status kgev_create(kgev_ctx** ctx, int device);
  * Autotuner of panel and tile sizes for pencils of order n.  Times, on
  * synthetic Hermitian matrices of order n (four at a time): the blocked
  * Householder reduction (Procedures 1-6 of Section III, the largest cost of
- * Eigen_HH) for the panel widths 16, 24, 32, 48 and 64; at the fastest
- * width, the reduction for the Hermitian-product tile grouping thresholds
- * (opts.hemv_slots) 1 (four tiles per workgroup throughout), 256, 768, 2048
- * and 2^30 (one tile per workgroup throughout); and the n x n x n complex
- * products of Parts 3 and 4 for the product tile thresholds (opts.gemm_slots)
- * 1 (64 x 64 tiles throughout), 64, 256, 1024 and 2^30 (32 x 32
- * throughout).  A threshold other than the default is taken only when it is
- * more than 2% faster.  The choices are recorded in the context for (n,
+ * Eigen_HH; blocked down to order 128, so that every column takes part) for the
+ * panel widths 16, 24, 32, 48 and 64; at the width chosen, the reduction for the
+ * Hermitian-product tile grouping thresholds (opts.hemv_slots) 1 (four tiles per
+ * workgroup throughout), 256, 768, 2048 and 2^30 (one tile per workgroup
+ * throughout); and the n x n x n complex products of Parts 3 and 4 for the
+ * product tile thresholds (opts.gemm_slots) 1 (64 x 64 tiles throughout), 64,
+ * 256, 1024 and 2^30 (32 x 32 throughout).  A width or threshold other than the
+ * default is taken only when it is more than 2% faster (a threshold further from
+ * the default only when it is 2% faster than the nearer ones, too).  The choices are recorded in the context for (n,
  * precision); later calls through this context leaving the corresponding
  * option 0 use them.  The tuned values depend only on n and precision, not
  * on the batch.

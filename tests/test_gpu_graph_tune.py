@@ -84,6 +84,20 @@ def test_autotune_choice_is_used_and_batch_independent():
     assert np.array_equal(outs[2][0][0], outs[0][0][0]) and np.array_equal(outs[2][1][0], outs[0][1][0])
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+def test_autotune_times_blocked_columns(precision):
+    """The tuner's reductions are blocked ones: at an order where four problems
+    would go to groups of workgroups whole, every one of them (at least two per
+    panel width and per threshold) launches the columns down to order 128."""
+    kg = K()
+    n = 600
+    with kg.Context(0) as ctx:
+        kg.profile_begin(ctx, kg.PHASE_HEMV, 1 << 30)
+        kg.autotune(ctx, n, precision)
+        prof = kg.profile_end(ctx)
+    assert prof["phase_launches"] >= 20 * (n - 128)
+
+
 @pytest.mark.parametrize("slots", [1, 1 << 30])
 def test_hermitian_product_forms_match_oracle(slots):
     """Both tile groupings of the Hermitian product (four 64 x 64 tiles per
