@@ -76,8 +76,10 @@ typedef struct {
     int32_t precision;    /* KGEV_PREC_FP64 (default) or KGEV_PREC_FP32_REFINE */
     int32_t want_vectors; /* 1 (default): eigenvalues and eigenvectors; 0: eigenvalues only */
     int32_t panel_nb;     /* Householder panel width; 0 = tuned default.  With a width (or hemv_slots)
-                             given, panels of it run down to trailing order 128; with both 0 the
-                             reduction may leave the panels earlier (the same results to rounding) */
+                             given, panels of it run down to trailing order 128; with both 0, or
+                             as kgev_autotune chose them for this order and precision in this
+                             context, the reduction may leave the panels earlier (the same results
+                             to rounding) */
     int32_t refine_iters; /* mixed precision: refinement sweeps, 1..10; 0 = default (3) */
     double s_tol;         /* S(k) is rejected when s_min <= s_tol * s_max; 0 = default 1e-12 */
     int32_t use_graph;    /* 1: capture the whole batched solve as one HIP graph on the first call with
@@ -140,7 +142,8 @@ kgev_status kgev_create(kgev_ctx** ctx, int device);
  * default is taken only when it is more than 2% faster (a threshold further from
  * the default only when it is 2% faster than the nearer ones, too).  The choices are recorded in the context for (n,
  * precision); later calls through this context leaving the corresponding
- * option 0 use them.  The tuned values depend only on n and precision, not
+ * option 0 use them, and calls that pass them by value are the same calls, to
+ * the bit.  The tuned values depend only on n and precision, not
  * on the batch.
  * Results are bitwise reproducible for the same n, k-point count and
  * options on the same device (and with the same compute-unit mask of the

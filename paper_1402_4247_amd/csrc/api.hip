@@ -257,8 +257,8 @@ DcWs dc_ws(const SolvePlan& p, void* w, const double* d, const double* e, int* s
 
 // The caller's options with the defaults filled in.  groups: the reduction may
 // hand its last columns to groups of workgroups (hetrd_res.hip); a caller
-// that names a panel width or a tile grouping gets that blocked reduction
-// down to the order one workgroup holds.
+// that names a panel width or a tile grouping other than the tuner's (apply_tuned)
+// gets that blocked reduction down to the order one workgroup holds.
 struct SolveOpts : kgev_opts {
     int32_t groups;
 };
@@ -335,6 +335,8 @@ void apply_tuned(const kgev_ctx* ctx, int64_t n, const kgev_opts* user, SolveOpt
     if (!user || user->panel_nb == 0) o.panel_nb = it->second.nb;
     if (!user || user->hemv_slots == 0) o.hemv_slots = it->second.hemv_slots;
     if (!user || user->gemm_slots == 0) o.gemm_slots = it->second.gemm_slots;
+    // a caller that passes the tuner's own values gets the call that leaves them 0
+    if (o.panel_nb == it->second.nb && o.hemv_slots == it->second.hemv_slots) o.groups = 1;
 }
 
 // the product tile policy of one call, installed for the calling thread

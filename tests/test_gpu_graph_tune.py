@@ -84,6 +84,35 @@ def test_autotune_choice_is_used_and_batch_independent():
     assert np.array_equal(outs[2][0][0], outs[0][0][0]) and np.array_equal(outs[2][1][0], outs[0][1][0])
 
 
+@pytest.mark.parametrize("n,nk,precision", [(300, 2, 0), (300, 2, 1), (700, 3, 0)])
+def test_tuned_values_passed_explicitly_are_the_same_call(n, nk, precision):
+    """At orders that go to groups of workgroups: leaving the options 0 and
+    passing what the tuner chose, some or all of it, eagerly and replayed, give
+    the same bits."""
+    kg = K()
+    Hs, Ss = G.config1_batch(n, nk, 7)
+    dH, dS = dev(Hs), dev(Ss)
+    stream = torch.cuda.Stream()
+    outs = []
+    with kg.Context(0) as ctx:
+        kg.autotune(ctx, n, precision)
+        nb, hs, gs, tuned = kg.tuned_params(ctx, n, precision)
+        assert tuned
+        forms = [dict(), dict(panel_nb=nb), dict(hemv_slots=hs), dict(panel_nb=nb, hemv_slots=hs, gemm_slots=gs)]
+        for kw in forms + [dict(use_graph=True, **f) for f in forms[:2] + forms[:2]]:
+            w = torch.zeros((nk, n), dtype=torch.float64, device=DEV)
+            C = torch.zeros((nk, n, n), dtype=torch.complex128, device=DEV)
+            st = torch.full((nk,), -9, dtype=torch.int32, device=DEV)
+            torch.cuda.synchronize()
+            run(ctx, dH, dS, n, nk, w, C, st, kg.make_opts(precision=precision, **kw),
+                stream=stream.cuda_stream if "use_graph" in kw else None)
+            torch.cuda.synchronize()
+            assert bool((st == 0).all())
+            outs.append((kw, w, C))
+    for kw, w, C in outs[1:]:
+        assert torch.equal(w, outs[0][1]) and torch.equal(C, outs[0][2]), kw
+
+
 @pytest.mark.parametrize("precision", [0, 1])
 def test_autotune_times_blocked_columns(precision):
     """The tuner's reductions are blocked ones: at an order where four problems
