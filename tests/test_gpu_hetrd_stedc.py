@@ -37,8 +37,10 @@ def gpu_hetrd(As, nb=0):
     return dd.cpu().numpy(), de.cpu().numpy(), dtau.cpu().numpy(), host(dV)
 
 
-# n <= 128 runs entirely in the LDS-resident tail kernel; larger n hands over
-# to it at the first panel start whose trailing order is at most 128
+# n <= 128 runs in one launch with the matrix in registers; with nb = 0 orders up to
+# 160 hand over to it at the first panel start whose trailing order is at most 128,
+# and larger ones to a group of workgroups, these whole; with a width given, all
+# hand over at 128
 @pytest.mark.parametrize("n,nb", [(1, 0), (2, 0), (3, 0), (17, 0), (64, 0), (65, 0), (128, 0), (129, 0), (130, 0),
                                   (161, 0), (200, 0), (200, 8), (97, 64), (250, 24), (300, 48)])
 def test_hetrd_matches_oracle(n, nb):
@@ -394,6 +396,60 @@ def test_fewer_compute_units(n, nk, units):
         finally:
             lib.kgev_internal_compute_units(0)
         assert hooks.given_up() == before
+
+
+def shares_of(n, nk):
+    """The shapes {(tile rows, tile columns)} that reduce order n whole, and for
+    each the most compute units with which it is chosen."""
+    import ctypes
+    f = K().lib.kgev_internal_hetrd_plan
+    f.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p]
+    out = {}
+    for units in range(256, 0, -1):
+        plan = (ctypes.c_int32 * 4)()
+        f(n, 32, nk, units, plan)
+        if plan[0] == n and plan[3]:
+            out.setdefault((plan[1], plan[2]), units)
+    return out
+
+
+# the widths of a member's share, at orders whose last member and last tile are
+# short and where they are not: the sums do not depend on the share
+@pytest.mark.parametrize("n,nk,shapes", [(200, 3, [(2, 1), (2, 2), (2, 4)]), (256, 1, [(2, 1), (2, 2), (2, 4)]),
+                                         (300, 2, [(3, 1), (3, 2), (3, 3)]), (384, 1, [(3, 1), (3, 2), (3, 3)]),
+                                         (500, 2, [(4, 1), (4, 2)]), (600, 2, [(5, 1), (5, 2)]),
+                                         (640, 1, [(5, 1), (5, 2)])])
+def test_group_shares_give_the_same_bits(n, nk, shapes):
+    kg = K()
+    units = shares_of(n, nk)
+    assert set(shapes) <= set(units)
+    rng = np.random.default_rng(17 * n)
+    As = np.stack([rand_herm(rng, n) for _ in range(nk)])
+    dH = dev(As)
+    dS = dev(np.stack([np.eye(n) + 0.01 * rand_herm(rng, n) / n for _ in range(nk)]))
+    outs = []
+    with GroupHooks() as hooks, kg.Context(0) as ctx:
+        before = hooks.given_up()
+        for shape in shapes:
+            try:
+                kg.lib.kgev_internal_compute_units(units[shape])
+                d, e, tau, V = gpu_hetrd(As)
+                # complex64, through the mixed-precision solve
+                w = torch.zeros((nk, n), dtype=torch.float64, device=DEV)
+                C = torch.zeros((nk, n, n), dtype=torch.complex128, device=DEV)
+                check(kg.solve_k_device(ctx, dH, dS, n, n, nk, w, C, n,
+                                        opts=kg.make_opts(precision=kg.PREC_FP32_REFINE)))
+                torch.cuda.synchronize()
+            finally:
+                kg.lib.kgev_internal_compute_units(0)
+            outs.append((d, e, tau, V, w.cpu().numpy(), C.cpu().numpy()))
+        assert hooks.given_up() == before
+    for q in range(nk):
+        T = np.diag(outs[0][0][q]) + np.diag(outs[0][1][q, : n - 1], 1) + np.diag(outs[0][1][q, : n - 1], -1)
+        assert mx(np.linalg.eigvalsh(T) - np.linalg.eigvalsh(As[q])) <= 64 * n * EPS * np.linalg.norm(As[q])
+    for shape, out in zip(shapes[1:], outs[1:]):
+        for name, a, b in zip(("d", "e", "tau", "V", "mixed w", "mixed C"), outs[0], out):
+            assert np.array_equal(a, b), f"{name}: {shape}"
 
 
 # merges with chains of deflation rotations, long runs of negligible

@@ -92,3 +92,26 @@ def test_invalid_stream_count():
         for bad in (-1, 9):
             o = kg.make_opts(want_vectors=False, streams=bad)
             assert kg.solve_k_device(ctx, dH, dS, n, n, nk, w, None, n, opts=o) == -10
+
+
+@pytest.mark.parametrize("n,nk,streams", [(200, 6, 3), (300, 8, 4), (700, 12, 2)])
+def test_groups_above_order_160_agree_to_rounding(n, nk, streams):
+    """Above order 160 the order at which the reduction leaves its panels depends
+    on the problems per stream, so the split agrees with one stream to rounding,
+    and with itself to the bit."""
+    kg = K()
+    Hs, Ss = G.config2(n, nk, 2002)
+    dH, dS = dev(Hs), dev(Ss)
+    with kg.Context(0) as ctx:
+        w1, C1, s1 = solve(ctx, dH, dS, n, nk, kg.make_opts(streams=1))
+        w2, C2, s2 = solve(ctx, dH, dS, n, nk, kg.make_opts(streams=streams))
+        w3, C3, s3 = solve(ctx, dH, dS, n, nk, kg.make_opts(streams=streams))
+        torch.cuda.synchronize()
+    assert bool((s1 == 0).all()) and torch.equal(s1, s2) and torch.equal(s1, s3)
+    assert torch.equal(w2, w3) and torch.equal(C2, C3)
+    scale = w1.abs().max()
+    assert float((w1 - w2).abs().max() / scale) <= 1e-12
+    H, S = torch.from_numpy(Hs).to(DEV), torch.from_numpy(Ss).to(DEV)
+    C = C2.transpose(-1, -2).contiguous()
+    res = (torch.matmul(H, C) - torch.matmul(S, C) * w2[:, None, :]).norm(dim=(1, 2)) / H.norm(dim=(1, 2))
+    assert float(res.max()) <= 1e-12
