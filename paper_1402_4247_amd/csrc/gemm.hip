@@ -372,8 +372,9 @@ template <int T, int GK> struct DmaTile {
 
 // 64 lanes x 16 bytes from each lane's address to LDS at lds + 16 * lane
 // (written as assembly because the compiler would wait for all of them before
-// any LDS read; no register receives anything; m0 is not allocated and set
-// anew by whatever uses it)
+// any LDS read; no register receives anything; m0 is reserved, so that the compiler
+// takes it for no value of its own and refuses it as a clobber, and no other
+// instruction of these kernels uses it)
 __device__ __attribute__((always_inline)) inline void load_to_lds(uint32_t lds, const double2* p)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(p) : "memory");

@@ -155,4 +155,13 @@ __device__ inline double dpp_wave_min(double v)
     return v;
 }
 
+// LDS written by a wave and then read by other lanes of the same wave: a
+// wave-scope fence and a scheduling barrier, no workgroup barrier
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace kgev

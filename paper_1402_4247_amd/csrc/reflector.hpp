@@ -28,13 +28,4 @@ __device__ __attribute__((always_inline)) inline void reflector_core(cx<R> alpha
     scale = mk<R>(dr * iden, -di * iden);
 }
 
-// LDS written by a wave and then read by other lanes of the same wave: a
-// wave-scope fence and a scheduling barrier, no workgroup barrier
-__device__ inline void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 }  // namespace kgev

@@ -102,15 +102,6 @@ __global__ __launch_bounds__(256) void dc_init(DcWs ws, int tl)
 // d (double) of lane i: a wave-uniform read of a lane-distributed array
 __device__ inline double rdl(double v, int i) { return lane_read(v, i); }
 
-// LDS written by a wave and then read by other lanes of the same wave: a
-// wave-scope fence and a scheduling barrier, no workgroup barrier
-__device__ inline void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // ---------------------------------------------------------------------------
 // Leaf eigensolver: one wave per leaf segment (at most LEAF rows) of the torn
 // tridiagonal, by the parallel cyclic Jacobi method (Golub & Van Loan §8.5):

@@ -6,7 +6,6 @@
 #include "common.hpp"
 #include "lanes.hpp"
 #include "kernels.hpp"
-#include "reflector.hpp"
 
 namespace kgev {
 
