@@ -486,3 +486,32 @@ def test_stedc_halves(n, coupling):
     rng = np.random.default_rng(n)
     d = np.tile([1.0, 2.0, 3.0, 3.0], (n + 3) // 4)[:n] + 1e-3 * rng.integers(0, 3, n)
     test_stedc_matches_oracle("halves", d, coupling * rng.uniform(0.1, 0.4, n - 1))
+
+
+# chains of deflation rotations at the edges of the 64 candidates and 64 starts
+# that are read at a time, with the lists in LDS and (n > 2700) in memory: one
+# chain over everything, a chain per pair of equal poles (the halves of a Toeplitz
+# matrix with an even order have the same spectrum), and many short ones
+@pytest.mark.parametrize("kind", ["one chain", "pairs", "short chains"])
+@pytest.mark.parametrize("n", [34, 63, 64, 65, 66, 128, 130, 132, 258, 700, 2750])
+def test_stedc_chains(n, kind):
+    rng = np.random.default_rng(n)
+    if kind == "one chain":
+        d, e = np.ones(n), np.full(n - 1, 1e-13)
+    elif kind == "pairs":
+        d, e = np.full(n, 0.3), np.full(n - 1, -1.7)
+    else:
+        d, e = np.sort(rng.integers(0, n // 4 + 1, n)).astype(float), 1e-15 * rng.standard_normal(n - 1)
+    w, Z, st = gpu_stedc(d[None], e[None])
+    assert np.all(st == 0)
+    nt = max(np.abs(d).max(), np.abs(e).max())
+    if kind == "pairs":
+        assert mx(w[0] - np.sort(0.3 + 2 * -1.7 * np.cos(np.arange(1, n + 1) * np.pi / (n + 1)))) <= 16 * n * EPS * nt
+    Zd = torch.from_numpy(Z[0].copy()).to(DEV)
+    TZ = torch.from_numpy(d).to(DEV)[:, None] * Zd
+    ed = torch.from_numpy(e).to(DEV)[:, None]
+    TZ[1:] += ed * Zd[:-1]
+    TZ[:-1] += ed * Zd[1:]
+    norm = np.sqrt((d ** 2).sum() + 2 * (e ** 2).sum())
+    assert float((TZ - Zd * torch.from_numpy(w[0]).to(DEV)).norm()) <= 16 * n * EPS * norm
+    assert float((Zd.T @ Zd - torch.eye(n, dtype=torch.float64, device=DEV)).abs().max()) <= 16 * n * EPS
