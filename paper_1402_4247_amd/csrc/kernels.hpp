@@ -111,7 +111,8 @@ struct DcWs {
     double* Q[2]; int64_t sQ;  // n x n per problem; set by stedc()
     double* Vsec;        // n x n per problem
     int* kcnt; int* ndcnt; double* rho;   // per segment, stored at its first index
-    int* ksplit;         // per segment, at its first two: poles of the first half alone, these and the mixed ones
+    int* ksplit;         // per segment, at its first: rotations; then at its first two: poles of the first half
+                         // alone, these and the mixed ones
     int* perm; double* sd; double* sz;
     int* ndx; double* ndd; double* ndz;
     int* dfx; double* dfd;

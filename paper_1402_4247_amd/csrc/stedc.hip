@@ -262,6 +262,42 @@ __global__ __launch_bounds__(64) void dc_leaf(DcWs ws, int tl)
 }
 
 // ---------------------------------------------------------------------------
+constexpr int DEFLATE_T = 256;
+
+// The deflation rotations, in order, on the columns of Q: rows DEFLATE_T * block .. of the
+// segment, one thread per row.  Consecutive rotations chain through their second
+// column (the pending candidate), so that column is carried in a register: no
+// rotation waits for the store of the one before it to come back from memory.
+// Segments of more than DEFLATE_T rows are rotated in the launch of the roots, which
+// don't need Q, by a workgroup per DEFLATE_T rows: one for all rows took 60 of 91 ms
+// for a Toeplitz matrix of order 6000 (now 12.5 in all).  Smaller ones gain nothing
+// from more workgroups: 64 rows x 1000 problems 0.51 against 0.48 ms.
+__device__ inline void dc_rotate(const DcWs& ws, const Seg& g, int64_t b, int64_t n, int block, int rb, int nr)
+{
+    const int64_t s = g.s;
+    const int r = block * DEFLATE_T + threadIdx.x;
+    if (r >= (int)(g.e - g.s)) return;
+    double* Qr = ws.Q[rb] + b * ws.sQ;
+    const int* rota = ws.rota + b * n + s;
+    const int* rotb = ws.rotb + b * n + s;
+    const double* rotc = ws.rotc + b * n + s;
+    const double* rots = ws.rots + b * n + s;
+    const int64_t row = s + r;
+    int cur = -1;            // column held in cv (not yet stored), or -1
+    double cv = 0.0;
+    for (int q = 0; q < nr; ++q) {
+        const int ca = rota[q], cb = rotb[q];
+        const double x = ca == cur ? cv : Qr[row + (s + ca) * n];
+        const double y = cb == cur ? cv : Qr[row + (s + cb) * n];
+        if (cur >= 0 && cur != ca && cur != cb) Qr[row + (s + cur) * n] = cv;
+        Qr[row + (s + ca) * n] = rotc[q] * x + rots[q] * y;
+        cur = cb;
+        cv = rotc[q] * y - rots[q] * x;
+    }
+    if (cur >= 0) Qr[row + (s + cur) * n] = cv;
+}
+
+// ---------------------------------------------------------------------------
 // Deflation for one merge (one workgroup per segment and problem).  The lists
 // (sorted poles sd, components sz, columns perm, indices kidx) stay in LDS when
 // the segment fits: 24 bytes a row.
@@ -276,7 +312,7 @@ __global__ __launch_bounds__(64) void dc_leaf(DcWs ws, int tl)
 // compacted by prefix counts in the order of a serial scan (the same results,
 // bit for bit).  One thread scanning all candidates took 0.17 us each: 25 us
 // at 128 rows, 64 us at 333, 333 us at 2000.
-__global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int lds_cap)
+__global__ __launch_bounds__(DEFLATE_T) void dc_deflate(DcWs ws, int t, int rb, int lds_cap, int rotate)
 {
     __shared__ double sh[8];
     __shared__ int s_cnt[2][4], s_nrot;
@@ -288,7 +324,7 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
     if (ns <= 0) return;
     const int64_t s = g.s;
     const double* Dr = ws.D[rb] + b * n;
-    double* Qr = ws.Q[rb] + b * ws.sQ;
+    const double* Qr = ws.Q[rb] + b * ws.sQ;
     int* kc = ws.kcnt + b * n;
     int* ndc = ws.ndcnt + b * n;
     const bool in_lds = ns <= lds_cap;
@@ -513,27 +549,9 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
         kc[s] = K;
         ndc[s] = nd;
         ws.rho[b * n + s] = rho;
+        ws.ksplit[b * n + s] = s_nrot;     // (for dc_secular; then dc_zhat's)
     }
-    const int nr = s_nrot;
-    // apply the deflation rotations, in order, to the columns of Q (rows s..e).
-    // Consecutive rotations chain through their second column (the pending
-    // candidate), so that column is carried in a register: no rotation waits
-    // for the store of the one before it to come back from memory.
-    for (int r = tid; r < ns; r += 256) {
-        const int64_t row = s + r;
-        int cur = -1;            // column held in cv (not yet stored), or -1
-        double cv = 0.0;
-        for (int q = 0; q < nr; ++q) {
-            const int ca = rota[q], cb = rotb[q];
-            const double x = ca == cur ? cv : Qr[row + (s + ca) * n];
-            const double y = cb == cur ? cv : Qr[row + (s + cb) * n];
-            if (cur >= 0 && cur != ca && cur != cb) Qr[row + (s + cur) * n] = cv;
-            Qr[row + (s + ca) * n] = rotc[q] * x + rots[q] * y;
-            cur = cb;
-            cv = rotc[q] * y - rots[q] * x;
-        }
-        if (cur >= 0) Qr[row + (s + cur) * n] = cv;
-    }
+    if (rotate) dc_rotate(ws, g, b, n, 0, rb, s_nrot);
 }
 
 // ---------------------------------------------------------------------------
@@ -553,7 +571,7 @@ __global__ __launch_bounds__(256) void dc_deflate(DcWs ws, int t, int rb, int ld
 // LCAO pencils where starting at the middle of the bracket and a one-pole
 // model for the last root took up to 28.
 constexpr int SEC_LANES = 16;
-constexpr int SEC_T = 256;
+constexpr int SEC_T = DEFLATE_T;     // (a launch has workgroups of both kinds)
 constexpr int SEC_CAP = 4000;
 
 __device__ inline double root_sum(double v)
@@ -613,17 +631,23 @@ __global__ __launch_bounds__(256) void dc_square(DcWs ws)
     ws.zhat[blockIdx.y * (int64_t)ws.n + q] = z * z;
 }
 
-__global__ __launch_bounds__(SEC_T) void dc_secular(DcWs ws, int t, int cap)
+__global__ __launch_bounds__(SEC_T) void dc_secular(DcWs ws, int t, int cap, int rb, int row_blocks)
 {
     extern __shared__ double dyn[];      // cap poles, cap z^2
     const int64_t b = blockIdx.z;
     const int64_t n = ws.n;
     const Seg g = seg_of(blockIdx.y, n, t);
     if (g.e - g.s < 2) return;
+    // the first workgroups of a row rotate Q's columns, which the roots don't need
+    if ((int)blockIdx.x < row_blocks) {
+        dc_rotate(ws, g, b, n, blockIdx.x, rb, ws.ksplit[b * n + g.s]);
+        return;
+    }
     const int64_t s = g.s;
     const int K = ws.kcnt[b * n + s];
-    if (blockIdx.x * (SEC_T / SEC_LANES) >= K) return;
-    const int gt = blockIdx.x * SEC_T + threadIdx.x;
+    const int block = (int)blockIdx.x - row_blocks;
+    if (block * (SEC_T / SEC_LANES) >= K) return;
+    const int gt = block * SEC_T + threadIdx.x;
     const int j = gt / SEC_LANES, sub = gt % SEC_LANES;
     const double* dl = ws.ndd + b * n + s;
     const double* zl = ws.ndz + b * n + s;
@@ -1014,12 +1038,15 @@ hipError_t stedc(hipStream_t st, const DcWs& ws0, double* w, double* Z, double* 
         const int64_t nsmax = ((n + segs - 1) / segs) + 1;
         const int cap = (int)std::min<int64_t>(nsmax, 2700);
         const size_t dyn_bytes = (size_t)cap * (2 * sizeof(double) + 2 * sizeof(int));
-        hipLaunchKernelGGL(dc_deflate, dim3(segs, (unsigned)nk), dim3(256), dyn_bytes, st, ws, t, rb, cap);
+        hipLaunchKernelGGL(dc_deflate, dim3(segs, (unsigned)nk), dim3(DEFLATE_T), dyn_bytes, st, ws, t, rb, cap,
+                           (int)(nsmax <= DEFLATE_T));
         const int scap = (int)std::min<int64_t>(nsmax, SEC_CAP);
         if (nsmax > SEC_CAP)
             hipLaunchKernelGGL(dc_square, dim3((unsigned)((n + 255) / 256), (unsigned)nk), dim3(256), 0, st, ws);
-        hipLaunchKernelGGL(dc_secular, dim3((unsigned)((nsmax * SEC_LANES + SEC_T - 1) / SEC_T), segs, (unsigned)nk),
-                           dim3(SEC_T), (size_t)scap * 2 * sizeof(double), st, ws, t, scap);
+        const unsigned row_blocks = nsmax <= DEFLATE_T ? 0u : (unsigned)((nsmax + DEFLATE_T - 1) / DEFLATE_T);
+        hipLaunchKernelGGL(dc_secular,
+                           dim3(row_blocks + (unsigned)((nsmax * SEC_LANES + SEC_T - 1) / SEC_T), segs, (unsigned)nk),
+                           dim3(SEC_T), (size_t)scap * 2 * sizeof(double), st, ws, t, scap, rb, (int)row_blocks);
         const unsigned gxs = (unsigned)((nsmax * SEC_LANES + 63) / 64);
         hipLaunchKernelGGL(dc_zhat_order, dim3(2 * gxs, segs, (unsigned)nk), dim3(64), 0, st, ws, t, wb, (int)gxs);
         hipLaunchKernelGGL(dc_vectors_place, dim3((unsigned)(2 * nsmax), segs, (unsigned)nk), dim3(64), 0, st, ws, t, rb,
