@@ -664,6 +664,16 @@ __global__ __launch_bounds__(256, 2) void hetrd_update(HetrdWs<R> ws, int i, int
 
 }  // namespace
 
+namespace {
+// reductions of order 1: T is the matrix
+template <typename R>
+__global__ __launch_bounds__(256) void hetrd_order1(HetrdWs<R> ws, int64_t nk)
+{
+    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (b < nk) ws.d[b] = ws.A[b * ws.sA].x;
+}
+}  // namespace
+
 template <typename R>
 hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
 {
@@ -681,8 +691,8 @@ hipError_t hetrd(hipStream_t st, const HetrdWs<R>& ws0, int64_t nk)
             if (e != hipSuccess) return e;
             break;
         }
-        if (p == n - 1)      // order 1: its diagonal, from the panel products' workgroup
-            hipLaunchKernelGGL((hetrd_zhemv<R, false>), dim3(1, (unsigned)nk), dim3(256), 0, st, ws, p, p, 1, 0);
+        if (p == n - 1)      // (n = 1)
+            hipLaunchKernelGGL(hetrd_order1<R>, dim3((unsigned)((nk + 255) / 256)), dim3(256), 0, st, ws, nk);
         const int iend = min(p + nb, n - 1);
         for (int i = p; i < iend; ++i) {
             const int o = i + 1, m = n - o;

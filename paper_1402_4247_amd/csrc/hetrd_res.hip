@@ -255,7 +255,7 @@ __global__ __launch_bounds__(RT_T) void hetrd_resident(HetrdWs<R> ws, int i0)
         lds_barrier();
         // ---- B
         nrm = 0;
-        if (w * WAVE < MP) {
+        if (MP % WAVE == 0 ? w * WAVE < MP : tid < MP) {
             const int s = tid;
             const bool live = s >= c1 && s < M;
             const cx<R> tau = sref[0], scale = sref[1];
@@ -1104,10 +1104,19 @@ hipError_t hetrd_res(hipStream_t st, const HetrdWs<R>& ws, int i0, int64_t nk, i
 {
     const int M = ws.n - i0;
     if (M <= HETRD_RES_M) {
-        if (M <= 64)
-            hipLaunchKernelGGL((hetrd_resident<R, 1, 4>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
+        // A column costs about the same at any order that a form holds: 4000
+        // problems of order 2 took 51 us with the form for 64, 20 with that for 16,
+        // of order 8 207 and 72; 4000 of order 65 2.6 ms with that for 128, 2.2 with
+        // that for 80.
+        const dim3 grid((unsigned)nk), block(RT_T);
+        if (M <= 16)
+            hipLaunchKernelGGL((hetrd_resident<R, 1, 1>), grid, block, 0, st, ws, i0);
+        else if (M <= 64)
+            hipLaunchKernelGGL((hetrd_resident<R, 1, 4>), grid, block, 0, st, ws, i0);
+        else if (M <= 80)
+            hipLaunchKernelGGL((hetrd_resident<R, 1, 5>), grid, block, 0, st, ws, i0);
         else
-            hipLaunchKernelGGL((hetrd_resident<R, 1, 8>), dim3((unsigned)nk), dim3(RT_T), 0, st, ws, i0);
+            hipLaunchKernelGGL((hetrd_resident<R, 1, 8>), grid, block, 0, st, ws, i0);
         return hipGetLastError();
     }
     const GroupChoice g = group_choice(M, nk, cus);
