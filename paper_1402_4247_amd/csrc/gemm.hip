@@ -546,11 +546,20 @@ hipError_t launch_tiles(CGemmArgs<R> p, hipStream_t st, const ProfLaunch& pl)
     p.tri = (p.lower && BM == BN && p.tiles_m == p.tiles_n) ? 1 : 0;
     const int64_t total = (p.tri ? (int64_t)p.tiles_m * (p.tiles_m + 1) / 2 : (int64_t)p.tiles_m * p.tiles_n) * p.batch;
     if constexpr (std::is_same_v<R, double> && TB != 2) {
-        if (dma_operands(p)) {
+        // Not where C is read, at most two K steps are multiplied and at most four
+        // workgroups a compute unit are launched: such a product is bound by the
+        // latency of C, with nothing to load ahead (k = 8, 16, 32 and 64 against the
+        // kernel above: 333^2 x 6 11.6, 11.8, 13.3 and 15.7 us against 11.0, 11.2, 12.6
+        // and 16.7; 1000^2 x 4, in K steps of 8, 34.2, 33.4, 37 and 44 against 32.6,
+        // 32.9, 39 and 54; but 1000^2 x 8 with k = 8 56.9 against 63.0).  The bits are
+        // the same.
+        constexpr int GK = BM == 64 ? 8 : 16;
+        const bool reads_c = p.beta.x != 0 || p.beta.y != 0;
+        if (dma_operands(p) && !(reads_c && p.nseg * p.k <= 2 * GK && total <= 1024)) {
             if constexpr (BM == 64)
-                launch_timed(pl, zgemm_dma<64, 8, 3, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
+                launch_timed(pl, zgemm_dma<64, GK, 3, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
             else
-                launch_timed(pl, zgemm_dma<32, 16, 4, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
+                launch_timed(pl, zgemm_dma<32, GK, 4, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
             return hipGetLastError();
         }
     }

@@ -549,7 +549,7 @@ __global__ __launch_bounds__(DEFLATE_T) void dc_deflate(DcWs ws, int t, int rb, 
         kc[s] = K;
         ndc[s] = nd;
         ws.rho[b * n + s] = rho;
-        ws.ksplit[b * n + s] = s_nrot;     // (for dc_secular; then dc_zhat's)
+        if (!rotate) ws.ksplit[b * n + s] = s_nrot;     // (for dc_secular; then dc_zhat's)
     }
     if (rotate) dc_rotate(ws, g, b, n, 0, rb, s_nrot);
 }

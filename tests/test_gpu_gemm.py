@@ -113,3 +113,36 @@ def test_zgemm_loads_to_lds(ta, tb, m, n, k, batch):
     ref = (0.75 - 0.5j) * (A @ B) + (0.25 + 1.0j) * C
     bound = 8 * k * EPS * (abs(0.75 - 0.5j) * (np.abs(A) @ np.abs(B)) + abs(0.25 + 1.0j) * np.abs(C))
     assert np.all(np.abs(got[0].cpu().numpy().swapaxes(-1, -2) - ref) <= 2 * bound)
+
+
+# which kernel takes a product: at the edges of two steps of the inner dimension
+# (16 for 64 x 64 tiles, 32 for 32 x 32) with and without C read, against the
+# products of operands on 8-byte boundaries, which have one kernel
+@pytest.mark.parametrize("beta", [0.0, 0.25 + 1.0j])
+@pytest.mark.parametrize("m,n,batch", [(70, 33, 2), (65, 64, 130)])
+@pytest.mark.parametrize("k", [1, 7, 8, 9, 15, 16, 17, 31, 32, 33, 34])
+def test_zgemm_small_inner_dimension(m, n, batch, k, beta):
+    kg = K()
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m + 100 * k)
+    a, b, c = (torch.randn(s, dtype=torch.complex128, device=DEV, generator=g)
+               for s in ((batch, k, m), (batch, k, n), (batch, n, m)))
+    got = []
+    with kg.Context(0) as ctx:
+        for shift in (0, 1):
+            ops = []
+            for x in (a, b, c):
+                buf = torch.empty(x.numel() * 2 + 2, dtype=torch.float64, device=DEV)
+                buf[shift:shift + x.numel() * 2] = torch.view_as_real(x).reshape(-1)
+                ops.append(buf[shift:])
+            da, db, dc = ops
+            check(kg.zgemm_device(ctx, "N", "C", m, n, k, 0.75 - 0.5j, da, m, m * k, db, n, n * k, beta, dc, m, m * n,
+                                  batch), "zgemm")
+            torch.cuda.synchronize()
+            got.append(dc[:2 * c.numel()].clone())
+    assert torch.equal(got[0], got[1])
+    A, B, C = (x.cpu().numpy().swapaxes(-1, -2) for x in (a, b, c))
+    ref = (0.75 - 0.5j) * (A @ B.conj().swapaxes(-1, -2)) + beta * C
+    bound = 8 * k * EPS * (abs(0.75 - 0.5j) * (np.abs(A) @ np.abs(B).swapaxes(-1, -2)) + abs(beta) * np.abs(C))
+    out = torch.view_as_complex(got[0].reshape(batch, n, m, 2)).cpu().numpy().swapaxes(-1, -2)
+    assert np.all(np.abs(out - ref) <= 2 * bound)
