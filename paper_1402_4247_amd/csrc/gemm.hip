@@ -546,16 +546,15 @@ hipError_t launch_tiles(CGemmArgs<R> p, hipStream_t st, const ProfLaunch& pl)
     p.tri = (p.lower && BM == BN && p.tiles_m == p.tiles_n) ? 1 : 0;
     const int64_t total = (p.tri ? (int64_t)p.tiles_m * (p.tiles_m + 1) / 2 : (int64_t)p.tiles_m * p.tiles_n) * p.batch;
     if constexpr (std::is_same_v<R, double> && TB != 2) {
-        // Not where C is read, at most two K steps are multiplied and at most four
-        // workgroups a compute unit are launched: such a product is bound by the
-        // latency of C, with nothing to load ahead (k = 8, 16, 32 and 64 against the
-        // kernel above: 333^2 x 6 11.6, 11.8, 13.3 and 15.7 us against 11.0, 11.2, 12.6
-        // and 16.7; 1000^2 x 4, in K steps of 8, 34.2, 33.4, 37 and 44 against 32.6,
-        // 32.9, 39 and 54; but 1000^2 x 8 with k = 8 56.9 against 63.0).  The bits are
-        // the same.
+        // Not for 32 x 32 tiles where C is read, at most two K steps are multiplied and
+        // more workgroups are launched than run at once (two a compute unit, by LDS):
+        // there is nothing to load ahead, and the kernel above has them all in flight.
+        // 333^2 x 6 (726 workgroups) with k = 16, 32, 48: 11.8, 13.3, 14.2 us against
+        // 11.2, 12.6, 14.7; 500^2 x 3 10.9, 12.4, 13.5 against 10.7, 12.0, 13.9.  The bits are
+        // the same.  (64 x 64 tiles gain at any k: 1000^2 x 3, k = 8 22 against 29 us.)
         constexpr int GK = BM == 64 ? 8 : 16;
-        const bool reads_c = p.beta.x != 0 || p.beta.y != 0;
-        if (dma_operands(p) && !(reads_c && p.nseg * p.k <= 2 * GK && total <= 1024)) {
+        const bool short_sum = BM == 32 && (p.beta.x != 0 || p.beta.y != 0) && p.nseg * p.k <= 2 * GK && total > 512;
+        if (dma_operands(p) && !short_sum) {
             if constexpr (BM == 64)
                 launch_timed(pl, zgemm_dma<64, GK, 3, TA, TB>, dim3((unsigned)total), dim3(G_THREADS), st, p);
             else

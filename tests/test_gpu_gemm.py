@@ -116,10 +116,11 @@ def test_zgemm_loads_to_lds(ta, tb, m, n, k, batch):
 
 
 # which kernel takes a product: at the edges of two steps of the inner dimension
-# (16 for 64 x 64 tiles, 32 for 32 x 32) with and without C read, against the
-# products of operands on 8-byte boundaries, which have one kernel
+# (32 for 32 x 32 tiles, 16 for 64 x 64) with and without C read, fewer and more than
+# 512 workgroups of 32 x 32 tiles, and 64 x 64 tiles, against the products of
+# operands on 8-byte boundaries, which have one kernel
 @pytest.mark.parametrize("beta", [0.0, 0.25 + 1.0j])
-@pytest.mark.parametrize("m,n,batch", [(70, 33, 2), (65, 64, 130)])
+@pytest.mark.parametrize("m,n,batch", [(70, 33, 2), (97, 65, 60), (65, 64, 130)])
 @pytest.mark.parametrize("k", [1, 7, 8, 9, 15, 16, 17, 31, 32, 33, 34])
 def test_zgemm_small_inner_dimension(m, n, batch, k, beta):
     kg = K()
