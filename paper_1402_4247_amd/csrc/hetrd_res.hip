@@ -1051,7 +1051,8 @@ thread_local int tl_compute_units = 0;       // set by tests
 }  // namespace
 
 // The compute units that work on a stream may use: the device's, without those
-// that a mask of the stream leaves out.
+// that a mask of the stream leaves out (the runtime's own streams, whose handles
+// are small numbers, have the process's mask).
 int stream_compute_units(hipStream_t st)
 {
     if (tl_compute_units > 0) return tl_compute_units;
@@ -1061,6 +1062,7 @@ int stream_compute_units(hipStream_t st)
         return 0;
     uint32_t mask[32] = {};
     const uint32_t words = (uint32_t)std::min((cus + 31) / 32, 32);
+    if (st == hipStreamLegacy || st == hipStreamPerThread) st = nullptr;
     if (hipExtStreamGetCUMask(st, words, mask) == hipSuccess) {
         int in = 0;
         for (uint32_t q = 0; q < words; ++q) in += __builtin_popcount(mask[q]);

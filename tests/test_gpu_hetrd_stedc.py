@@ -379,7 +379,8 @@ def test_stream_compute_units():
     lib = K().lib
     lib.kgev_internal_stream_units.argtypes = [ctypes.c_void_p]
     units = torch.cuda.get_device_properties(0).multi_processor_count
-    assert lib.kgev_internal_stream_units(None) == units
+    for handle in (None, 1, 2):          # the null, the legacy and the per-thread stream
+        assert lib.kgev_internal_stream_units(handle) == units
     assert lib.kgev_internal_stream_units(torch.cuda.Stream().cuda_stream) == units
 
 

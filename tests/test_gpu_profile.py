@@ -4,7 +4,7 @@ that of the timed launches (for the Hermitian product, 16 m (m + 1) / 2 bytes
 per k-point, m the trailing order of the column).  The Hermitian product is
 launched for the columns of the blocked reduction; the last panels, from the
 first panel start whose trailing matrix has at most 128 rows, are reduced by
-one LDS-resident launch that is not part of the phase."""
+one launch (the matrix in registers) that is not part of the phase."""
 import pytest
 import torch
 
