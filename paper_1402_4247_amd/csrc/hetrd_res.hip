@@ -742,7 +742,7 @@ __global__ __launch_bounds__(RT_T) void hetrd_group(HetrdWs<R> ws, int i0, int G
 //
 // Reached only when other work holds the GPU's compute units for longer than
 // the members' wait.  Bound by one compute unit's traffic to memory, which the
-// matrix crosses twice a column: 2.8 ms at order 200, 23 ms at 512 and 172 ms at
+// matrix crosses twice a column: 2.6 ms at order 200, 23 ms at 512 and 172 ms at
 // 1024, after the wait.  (In place on the lower triangle, one thread per row and
 // other bits than a group's: 6.4, 39 and 297 ms.)
 __device__ unsigned int groups_given_up;     // for tests
